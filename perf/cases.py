@@ -8,8 +8,9 @@ dynamics, and the loss |D^-1 phi|^2 with its gradients.  Lattices run from 8^4 (
 whole cost) to 48^3 x 96 (one field is over half a gigabyte); 4^4 blocks are the usual ones, 2^4
 blocks serve extents that are no multiple of 8.
 
-Single-precision results come back as what they are, FP32 fields in the library's own layout; the
-others as canonical complex128 tensors.  `exact` works the same quantities out in 64 bits with plain
+Results come back at the precision that they have: single-precision ones as FP32 fields in the
+library's own layout, the half-precision preconditioner's rounded to half precision, the others as
+canonical complex128 tensors.  `exact` works the same quantities out in 64 bits with plain
 torch on the canonical fields.
 """
 import math
@@ -227,8 +228,11 @@ def run(st):
     if do == "dirac_f16in":
         return _f32(st, s.apply_packed_f16in(st["q"], st["x"]))
     if do == "sap":
+        if case["prec"] == "f16":
+            # z = M_SAP r to half precision, which is what a program keeps of it
+            return torch.view_as_real(s.precondition(st["in"][0], prec=dd.DD_F16, out=st["z"])).to(torch.float16)
         # z = M_SAP r, then into the FP32 field that a Krylov loop goes on with
-        s.precondition(st["in"][0], prec=dd.DD_F16 if case["prec"] == "f16" else dd.DD_F32, out=st["z"])
+        s.precondition(st["in"][0], prec=dd.DD_F32, out=st["z"])
         return _f32(st, s.pack(st["z"], dd.DD_F32, out=st["zf"]))
     if do == "force":
         force, dcsw = s.force(st["in"][0], st["in"][1], su3=case["su3"])
@@ -500,7 +504,8 @@ def exact(case, seed):
     if do in ("dirac_f32", "dirac_f16in"):
         return _block_major(_Operator(case, U, inverse=True).A(b), case["block"])
     if do == "sap":
-        return _block_major(_Operator(case, U, inverse=True).sap(b, case["block"], case["n_sap"], case["n_jac"]), case["block"])
+        z = _Operator(case, U, inverse=True).sap(b, case["block"], case["n_sap"], case["n_jac"])
+        return torch.view_as_real(z) if case["prec"] == "f16" else _block_major(z, case["block"])
     op = _Operator(case, U)
     if do == "solve":
         # on the largest lattices plain torch takes too long for it
