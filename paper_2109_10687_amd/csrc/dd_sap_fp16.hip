@@ -569,7 +569,7 @@ DD_HDI int sap_blocks_per_wg(int bvol) { return bvol < 64 ? 64 / bvol : 1; }
 template <int B, bool ONE>
 DD_INL void sap_half_pk_body(Geom gin, int w, int colour, int flags, SpinorField<2> bsrc, SpinorField<2> sw,
                              SpinorField<2> xw, const __half2 *u16, const __half2 *cpsap, Phase4 ph, float kappa,
-                             int n_jac, h2 *ft, SapRhs rhs)
+                             int n_jac, h2 *ft, const SapRhs &rhs, int rhs0 = 0, int rhs1 = 1)
 {
     extern __shared__ uint4 smem_pk[];
     const Geom g = fixed_shape<B>(gin);
@@ -616,9 +616,9 @@ DD_INL void sap_half_pk_body(Geom gin, int w, int colour, int flags, SpinorField
 
     // ONE: the fields as given, a single right-hand side (no loop for the compiler to hoist
     // the neighbour blocks' addresses out of, which would spill them)
-    const int nrhs = ONE ? 1 : rhs.n;
-    for (int ri = 0; ri < nrhs; ++ri) {
-        if (ri > 0) wg_barrier();  // the previous right-hand side is done with LDS
+    const int ri0 = ONE ? 0 : rhs0, ri1 = ONE ? 1 : rhs1;
+    for (int ri = ri0; ri < ri1; ++ri) {
+        if (ri > ri0) wg_barrier();  // the previous right-hand side is done with LDS
         const long long ridx = ONE ? 0 : rhs.idx[ri];
         const long long off = ONE ? 0 : ridx * rhs.sp_stride;
         const SpinorField<2> b_r = rhs_field(bsrc, off), s_r = rhs_field(sw, off), x_r = rhs_field(xw, off);
@@ -779,8 +779,16 @@ __global__ void __launch_bounds__(256) k_sap_half_pk(Geom gin, int colour, int f
                                                      const __half2 *cpsap, Phase4 ph, float kappa, int n_jac, h2 *ft,
                                                      SapRhs rhs)
 {
-    sap_half_pk_body<B, ONE>(gin, xcd_remap(blockIdx.x, gridDim.x), colour, flags, bsrc, sw, xw, u16, cpsap, ph, kappa,
-                        n_jac, ft, rhs);
+    int w = xcd_remap(blockIdx.x, gridDim.x), r0 = 0, r1 = 1;
+    if constexpr (!ONE) {
+        // workgroup (block, group of right-hand sides): the groups of a block are consecutive on one XCD
+        const int item = w / rhs.groups, per = (rhs.n + rhs.groups - 1) / rhs.groups;
+        r0 = (w - item * rhs.groups) * per;
+        r1 = r0 + per < rhs.n ? r0 + per : rhs.n;
+        w = item;
+        if (r0 >= r1) return;  // the whole workgroup: n need not be a multiple of the groups
+    }
+    sap_half_pk_body<B, ONE>(gin, w, colour, flags, bsrc, sw, xw, u16, cpsap, ph, kappa, n_jac, ft, rhs, r0, r1);
 }
 
 // The same half-sweep on several lattices of one block shape in one launch: the work items
@@ -822,6 +830,22 @@ size_t sap_pk_lds_bytes(const Geom &g)
     return (size_t)g.bvol * (3 * sizeof(uint4) + 36 * sizeof(__half2));
 }
 
+// Groups into which the n right-hand sides of a batch are split, each group a workgroup of its own
+// per block (items workgroups cover the blocks).  A workgroup that is alone on its CU takes 6.5 us
+// to start and stage its block and 15.2 us per right-hand side, three side by side 28 us per
+// right-hand side of each: small lattices are bound by that latency, so every right-hand side gets
+// a workgroup of its own (12 of them on 16^3x32, 256 blocks per colour: 189.5 us per half-sweep in
+// one group, 114 us in 12; 8^4: 190 and 22 us).  Once the launch is many times the 768 workgroups
+// the chip holds, sharing the staged links and C_inv is worth more: the smallest even split that
+// still leaves 6144 of them (12 right-hand sides on 32^4: 844 us in one group, 799 us in 3, 849 us
+// in 12).
+static int sap_rhs_groups(int items, int n)
+{
+    for (int G = 1; G < n; ++G)
+        if (n % G == 0 && (long long)items * G >= 6144) return G;
+    return n;
+}
+
 hipError_t launch_sap_half_pk(const Geom &g, hipStream_t st, const SapArgs &a, int colour, int flags)
 {
     if (a.prec != 2 || !a.faces) return hipErrorInvalidValue;
@@ -842,7 +866,9 @@ hipError_t launch_sap_half_pk(const Geom &g, hipStream_t st, const SapArgs &a, i
                         : (one ? k_sap_half_pk<0, true> : k_sap_half_pk<0, false>);
     const int bpw = sap_blocks_per_wg(g.bvol);  // (g.nblk / 2 is a multiple of 8: every direction holds an even
                                                  // number of blocks)
-    hipLaunchKernelGGL(kern, dim3(g.nblk / 2 / bpw), dim3(g.bvol * bpw), bpw * sap_pk_lds_bytes(g), st, g, colour, flags,
+    const int items = g.nblk / 2 / bpw;
+    rhs.groups = one ? 1 : sap_rhs_groups(items, rhs.n);
+    hipLaunchKernelGGL(kern, dim3(items * rhs.groups), dim3(g.bvol * bpw), bpw * sap_pk_lds_bytes(g), st, g, colour, flags,
                        sfh((void *)a.b), sfh(a.s), sfh(a.x), (const __half2 *)a.links, (const __half2 *)a.cinv, a.phase,
                        (float)a.kappa, a.n_jac, (h2 *)a.faces, rhs);
     return hipGetLastError();

@@ -189,6 +189,21 @@ def test_sap_batch_matches_single_and_oracle(name, fp16_arith):
     s.close()
 
 
+@pytest.mark.parametrize("dims, n", [((8, 8, 8, 8), 1), ((8, 8, 8, 8), 16), ((24, 16, 32, 32), 16), ((32, 32, 32, 32), 9)])
+def test_sap_batch_groups_match_single(dims, n):
+    """The batched half-sweep gives every (block, right-hand side) a workgroup of its own on small
+    lattices and splits the right-hand sides into even groups on large ones (two of them per workgroup
+    on 24x16x32x32 with 16, three on 32^4 with 9): each result equals sap_precondition on that
+    right-hand side alone, bit for bit."""
+    s = dd.Solver(dd.Params(dims=dims, kappa=0.125, csw=1.5, n_sap=1, n_jac=2),
+                  synth.su3_links(dims, 0.3, 341, device="cuda"))
+    bs = synth.gaussian_spinor(dims, 342, device="cuda", batch=n)
+    xb = s.precondition_batch(bs)
+    for r in range(n):
+        assert torch.equal(xb[r], s.precondition(bs[r], prec=dd.DD_F16)), r
+    s.close()
+
+
 def test_solve_multi_more_lattices_than_one_table_holds():
     """Twenty lattices in one lockstep solve: more than one table launch of the vector kernels
     (16 lattices each) and of the shared half-sweep (12 each).  Every lattice must reach the
