@@ -78,6 +78,19 @@ template <typename R> DD_HDI cx<R> cmulc(cx<R> a, cx<R> b)
 {
     return {a.re * b.re + a.im * b.im, a.re * b.im - a.im * b.re};
 }
+// s + a b and s + conj(a) b, each component a chain of two fused multiply-adds onto s: written as a
+// product that is then added, the compiler forms the product first (a multiply and one fused
+// multiply-add) and adds it, three instructions instead of two
+DD_HDI float fma_(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+DD_HDI double fma_(double a, double b, double c) { return __builtin_fma(a, b, c); }
+template <typename R> DD_HDI cx<R> cmac(cx<R> s, cx<R> a, cx<R> b)
+{
+    return {fma_(-a.im, b.im, fma_(a.re, b.re, s.re)), fma_(a.im, b.re, fma_(a.re, b.im, s.im))};
+}
+template <typename R> DD_HDI cx<R> cmacc(cx<R> s, cx<R> a, cx<R> b)
+{
+    return {fma_(a.im, b.im, fma_(a.re, b.re, s.re)), fma_(-a.im, b.re, fma_(a.re, b.im, s.im))};
+}
 template <typename R> DD_HDI cx<R> itimes(cx<R> a) { return {-a.im, a.re}; }
 template <typename R> DD_HDI R norm2(cx<R> a) { return a.re * a.re + a.im * a.im; }
 
@@ -392,9 +405,9 @@ template <> struct LinkField<0> {
 // third row of an SU(3) matrix from its first two: conj(row0 x row1)
 template <typename R> DD_INL void su3_row3(Mat3<R> &U)
 {
-    U.m[2][0] = conj(U.m[0][1] * U.m[1][2] - U.m[0][2] * U.m[1][1]);
-    U.m[2][1] = conj(U.m[0][2] * U.m[1][0] - U.m[0][0] * U.m[1][2]);
-    U.m[2][2] = conj(U.m[0][0] * U.m[1][1] - U.m[0][1] * U.m[1][0]);
+    U.m[2][0] = conj(cmac(U.m[0][1] * U.m[1][2], -U.m[0][2], U.m[1][1]));
+    U.m[2][1] = conj(cmac(U.m[0][2] * U.m[1][0], -U.m[0][0], U.m[1][2]));
+    U.m[2][2] = conj(cmac(U.m[0][0] * U.m[1][1], -U.m[0][1], U.m[1][0]));
 }
 
 // FP32 links: rows 0 and 1 as stored (12 reals, elem(l, s, 24, mu * 6 + a * 3 + b)), row 2
@@ -488,19 +501,30 @@ template <> struct CloverField<2> {
 // index of the upper entry (i < j) of a 6x6 Hermitian block, row by row
 DD_HDI int upper_index(int i, int j) { return i * 6 - i * (i + 1) / 2 + (j - i - 1); }
 
-// w = N u for one Hermitian 6x6 block
+// w = N u for one Hermitian 6x6 block; a row's five off-diagonal terms go to two sums in turn,
+// which keeps the chains of fused multiply-adds, and their rounding errors, short
 template <typename R> DD_INL void herm6(const R *d, const cx<R> *h, const cx<R> *u, cx<R> *w)
 {
+    cx<R> t[6];
 #pragma unroll
     for (int i = 0; i < 6; ++i) w[i] = d[i] * u[i];
 #pragma unroll
     for (int i = 0; i < 6; ++i)
 #pragma unroll
         for (int j = i + 1; j < 6; ++j) {
-            cx<R> hij = h[upper_index(i, j)];
-            w[i] = w[i] + hij * u[j];
-            w[j] = w[j] + cmulc(hij, u[i]);
+            const cx<R> hij = h[upper_index(i, j)];
+            // the k-th off-diagonal term of a row: k = j - 1 in row i, k = i in row j
+            if ((j - 1) & 1)
+                w[i] = cmac(w[i], hij, u[j]);
+            else
+                t[i] = j - 1 == 0 ? hij * u[j] : cmac(t[i], hij, u[j]);
+            if (i & 1)
+                w[j] = cmacc(w[j], hij, u[i]);
+            else
+                t[j] = i == 0 ? cmulc(hij, u[i]) : cmacc(t[j], hij, u[i]);
         }
+#pragma unroll
+    for (int i = 0; i < 6; ++i) w[i] = w[i] + t[i];
 }
 
 // out = Q diag(N+, N-) Q in, Q = [[1, 1], [1, -1]] on the spin pairs (0,1)/(2,3):
@@ -533,10 +557,10 @@ template <typename R> DD_INL void mat_half(const Mat3<R> &U, bool dag, const Hal
     for (int a = 0; a < 2; ++a)
 #pragma unroll
         for (int i = 0; i < 3; ++i) {
-            cx<R> acc = {R(0), R(0)};
-#pragma unroll
-            for (int j = 0; j < 3; ++j) acc = acc + (dag ? cmulc(U.m[j][i], h.v[a][j]) : U.m[i][j] * h.v[a][j]);
-            k.v[a][i] = acc;
+            // the third product is formed apart: a chain of six terms rounds worse
+            const cx<R> p0 = dag ? cmulc(U.m[0][i], h.v[a][0]) : U.m[i][0] * h.v[a][0];
+            const cx<R> p2 = dag ? cmulc(U.m[2][i], h.v[a][2]) : U.m[i][2] * h.v[a][2];
+            k.v[a][i] = (dag ? cmacc(p0, U.m[1][i], h.v[a][1]) : cmac(p0, U.m[i][1], h.v[a][1])) + p2;
         }
 }
 
