@@ -298,15 +298,15 @@ dd_status dd_set_csw(dd_ctx *ctx, double csw);
  *     c_SW != 0, from the four-leaf field strength when c_SW = 0).
  * The hop term carries the boundary phases; the clover term differentiates
  * every leaf through the link (24 per link).  FP64 throughout.  The first
- * call allocates a work field of 864 bytes per site, kept until dd_destroy
+ * call allocates a work field of 480 bytes per site, kept until dd_destroy
  * (DD_ERR_NOMEM if that fails).  Uses the context's internal FP64 work
  * vectors.  Synchronises the stream. */
 dd_status dd_force(dd_ctx *ctx, void *out_dev, double *dcsw, const void *psi_dev, const void *chi_dev, int su3);
 
 /* dd_force for callers that cannot allocate device memory: code under HIP graph
  * capture, tight serving loops, harnesses that forbid hipMalloc.  Same arguments,
- * kernels and results as dd_force, but the work field (54 complex doubles = 864
- * bytes per site) lives in a fixed 64 MiB device array that the library holds on
+ * kernels and results as dd_force, but the work field (room for 864 bytes per
+ * site) lives in a fixed 64 MiB device array that the library holds on
  * every GPU it runs on until the process ends, instead of a field the first call
  * allocates; the call makes no hipMalloc, hipFree or other allocating call.
  * Lattices of at most 77672 sites (64 MiB / 864 B; 16^4 fits) -- a larger one

@@ -457,8 +457,8 @@ dd_status dd_set_csw(dd_ctx *c, double csw)
     return DD_OK;
 }
 
-// the force of dd_force and dd_force_noalloc with the work field y (54 complex doubles
-// per site); timed = false launches without the kernel timers (whose event pool may grow)
+// the force of dd_force and dd_force_noalloc with the work field y (FORCE_Y_ELEMS
+// double2 per site); timed = false launches without the kernel timers (whose event pool may grow)
 static dd_status force_entry(dd_ctx *c, void *out_dev, double *dcsw, const void *psi_dev, const void *chi_dev,
                              int su3, void *y, bool timed_launch)
 {
@@ -466,8 +466,8 @@ static dd_status force_entry(dd_ctx *c, void *out_dev, double *dcsw, const void 
     dd::ForceArgs a{};
     a.psi = c->f64[0];
     a.chi = c->f64[1];
-    HIPCK(c, dd::launch_pack_spinor(g, c->stream, DD_F64, c->f64[0], psi_dev));
-    HIPCK(c, dd::launch_pack_spinor(g, c->stream, DD_F64, c->f64[1], chi_dev));
+    a.psi_can = psi_dev;
+    a.chi_can = chi_dev;
     a.u64 = c->U64;
     a.y = y;
     a.out = out_dev;
@@ -480,12 +480,12 @@ static dd_status force_entry(dd_ctx *c, void *out_dev, double *dcsw, const void 
     a.clov64 = c->clov64;
     a.phase = c->phase;
     a.su3 = su3;
-    // per site: psi, chi, four links and the six Y planes read twice over (once
-    // written), the output links written; flops of the hop outer products, the
+    // per site: psi, chi, four links, the six Y planes written and read, the output
+    // links written; flops of the hop outer products, the
     // 24 leaves per link (nine 3x3 products per plaquette) and the dcsw traces
     const double V = (double)g.V;
     const bool csw_from_clover = c->prm.csw != 0.0;
-    const double bytes = V * (2 * 192.0 + 4 * 144.0 + 2 * 864.0 + 4 * 144.0 +
+    const double bytes = V * (2 * 192.0 + 4 * 144.0 + 2 * 16.0 * dd::FORCE_Y_ELEMS + 4 * 144.0 +
                               (dcsw ? (csw_from_clover ? 576.0 : 4 * 144.0) : 0.0));
     const double flops = V * (4 * FORCE_LINK_FLOPS + FORCE_Y_FLOPS +
                               (dcsw ? (csw_from_clover ? FORCE_DCSW_CLOVER_FLOPS : FORCE_DCSW_FLOPS) : 0.0));
@@ -507,7 +507,7 @@ dd_status dd_force(dd_ctx *c, void *out_dev, double *dcsw, const void *psi_dev, 
     if (!c || !out_dev || !psi_dev || !chi_dev) return fail(c, DD_ERR_ARG, "null argument");
     if (su3 != 0 && su3 != 1) return fail(c, DD_ERR_ARG, "su3 must be 0 or 1");
     if (!c->gauge) return fail(c, DD_ERR_STATE, "no gauge field loaded");
-    if (!c->yforce && hipMalloc(&c->yforce, (size_t)c->g.V * 54 * 16) != hipSuccess) {
+    if (!c->yforce && hipMalloc(&c->yforce, (size_t)c->g.V * dd::FORCE_Y_ELEMS * 16) != hipSuccess) {
         (void)hipGetLastError();
         c->yforce = nullptr;
         return fail(c, DD_ERR_NOMEM, "force work field");
@@ -520,12 +520,12 @@ dd_status dd_force_noalloc(dd_ctx *c, void *out_dev, double *dcsw, const void *p
     if (!c || !out_dev || !psi_dev || !chi_dev) return fail(c, DD_ERR_ARG, "null argument");
     if (su3 != 0 && su3 != 1) return fail(c, DD_ERR_ARG, "su3 must be 0 or 1");
     if (!c->gauge) return fail(c, DD_ERR_STATE, "no gauge field loaded");
-    const size_t need = (size_t)c->g.V * 54 * 16;
+    const size_t need = (size_t)c->g.V * dd::FORCE_NOALLOC_SITE;
     if (need > dd::FORCE_SCRATCH_BYTES)
         return fail(c, DD_ERR_ARG, "lattice too large for dd_force_noalloc: " + std::to_string(c->g.V) +
                                        " sites need " + std::to_string(need) + " bytes of work space, the fixed "
                                        "array holds " + std::to_string(dd::FORCE_SCRATCH_BYTES) + " (at most " +
-                                       std::to_string(dd::FORCE_SCRATCH_BYTES / (54 * 16)) + " sites)");
+                                       std::to_string(dd::FORCE_SCRATCH_BYTES / dd::FORCE_NOALLOC_SITE) + " sites)");
     if (!c->yscratch)
         return fail(c, DD_ERR_HIP, std::string("work array address: ") + hipGetErrorString(c->yscratch_err));
     return force_entry(c, out_dev, dcsw, psi_dev, chi_dev, su3, c->yscratch, false);

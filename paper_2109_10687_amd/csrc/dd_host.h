@@ -56,7 +56,7 @@ struct dd_ctx {
     void *clov64 = nullptr, *cinv32 = nullptr, *cinv16 = nullptr;
     void *CPsap = nullptr;  // SAP-ready FP16 C_inv (launch_sap_prep)
     void *faces = nullptr;  // face hop terms of the packed-FP16 SAP half-sweeps
-    void *yforce = nullptr;  // force work field (54 complex per site), allocated by the first dd_force
+    void *yforce = nullptr;  // force work field (FORCE_Y_ELEMS double2 per site), allocated by the first dd_force
     void *yscratch = nullptr;       // the fixed device array that dd_force_noalloc uses instead
     hipError_t yscratch_err = hipSuccess;  // the result of looking its address up in dd_create
     // batched right-hand sides: contiguous arrays of per-RHS internal fields, allocated by the

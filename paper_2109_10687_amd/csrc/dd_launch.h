@@ -163,11 +163,13 @@ struct SapLatTab {
     int n;
 };
 
+constexpr int FORCE_Y_ELEMS = 30;
 struct ForceArgs {
-    const void *psi, *chi;  // FP64 internal-layout spinors
+    const void *psi_can, *chi_can;  // canonical spinors
+    void *psi, *chi;        // the same in the FP64 internal layout, written by the launch
     const void *u64;        // FP64 links
     const void *clov64;     // FP64 clover blocks 1 + C (dL/dc_SW when c_SW != 0)
-    void *y;                // work: 54 complex per site (six planes of 3x3)
+    void *y;                // work: FORCE_Y_ELEMS double2 per site (six anti-Hermitian 3x3 planes)
     void *out;              // canonical [4][Lt][Lz][Ly][Lx][3][3] complex double
     double *partials;       // per-workgroup partial sums of dL/dc_SW (nullptr: skip)
     double *dcsw;           // device scalar receiving dL/dc_SW
@@ -275,10 +277,11 @@ hipError_t launch_dirac_mrhs(const Geom &g, hipStream_t st, const MrhsArgs &a, i
 // fermion force of L = |D^{-1} phi|^2 from psi = D^{-1} phi and chi = D^{-dagger} psi
 hipError_t launch_force(const Geom &g, hipStream_t st, const ForceArgs &a);
 
-// the force's work field (54 complex doubles per site) in a fixed device array, for
+// the force's work field in a fixed device array, for
 // the entry point that allocates nothing: its size, and its address on the current
 // device (looked up once per device)
 constexpr size_t FORCE_SCRATCH_BYTES = (size_t)64 << 20;
+constexpr size_t FORCE_NOALLOC_SITE = 864;  // bytes per site that its size limit is stated in (the field takes fewer)
 constexpr int MAX_DEVICES = 64;
 hipError_t force_scratch_address(void **ptr);
 
