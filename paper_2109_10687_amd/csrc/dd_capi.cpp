@@ -201,6 +201,7 @@ dd_status dirac_apply(dd_ctx *c, void *out, const void *in, dd_prec prec, dd_op 
     if (!c || !out || !in) return fail(c, DD_ERR_ARG, "null argument");
     dd_status st = check_op(c, prec, op);
     if (st != DD_OK) return st;
+    if (prec == DD_F64) return k_dirac_can(c, out, in, op);
     void *ti = c->f64[5], *to = c->f64[6];
     HIPCK(c, dd::launch_pack_spinor(c->g, c->stream, prec, ti, in));
     if ((st = k_dirac(c, to, ti, prec, prec, prec, op)) != DD_OK) return st;

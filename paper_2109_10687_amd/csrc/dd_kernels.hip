@@ -459,6 +459,174 @@ __global__ void __launch_bounds__(256) k_dirac_ts(Geom gin, SpinorField<POUT> ou
     }
 }
 
+// the sums of a spinor are complete here, and volatile statements that follow come after them
+DD_INL void settle(Spinor<double> &s)
+{
+#pragma unroll
+    for (int a = 0; a < 4; ++a)
+        asm volatile("" : "+v"(s.v[a][0].re), "+v"(s.v[a][0].im), "+v"(s.v[a][1].re), "+v"(s.v[a][1].im),
+                     "+v"(s.v[a][2].re), "+v"(s.v[a][2].im));
+}
+
+// ---- D and D^dagger on canonical spinors (FP64), no pack and unpack passes
+// A workgroup takes a 4^3 x TT tile of the lattice (every extent is a multiple of 4), one site per
+// thread.  The canonical layout keeps a site's 12 components together (192 bytes), so the tile is
+// staged in LDS from runs of four sites (768 bytes) and in-tile neighbours come from there; the
+// others are read site by site, whole 64-byte pieces wherever they lie.  The result goes back
+// through LDS and leaves in the same runs.  Links and clover blocks are in the internal layout of
+// the context's blocks, whatever their shape.  HBM-bound (1536 B per site): 24^3x48 in 210 us,
+// 4.86 TB/s, where pack, apply and unpack took 51 + 253 + 59 us; the apply alone is faster too,
+// because a face site of the internal layout drags in a whole line per component (on an x or y
+// face four times its bytes), and with the loads of one hop in flight at a time it holds two
+// wavefronts per SIMD instead of one.  Tiles in z pairs lose 3 % here (32^3x64: 677 and 697 us).
+template <int OP, int TT, bool CUBE4>
+__global__ void __launch_bounds__(64 * TT, 2) k_dirac_can(Geom gin, double2 *out, const double2 *in, const double2 *u64,
+                                                       const double2 *clov, Phase4 ph, double kappa)
+{
+    const Geom g = fixed_shape<(CUBE4 ? 4 : 0)>(gin);
+    constexpr int N = 64 * TT, SS = 13;  // sites of a tile; double2 per staged site (13: no bank conflicts)
+    __shared__ double2 tile[N * SS];
+    const int tid = threadIdx.x;
+    // tile coordinates (x fastest)
+    const unsigned nx = (unsigned)g.L[0] >> 2, ny = (unsigned)g.L[1] >> 2, nz = (unsigned)g.L[2] >> 2;
+    unsigned w = (unsigned)xcd_remap(blockIdx.x, gridDim.x);
+    int o[4];
+    o[0] = 4 * (int)(w % nx);
+    w /= nx;
+    o[1] = 4 * (int)(w % ny);
+    w /= ny;
+    o[2] = 4 * (int)(w % nz);
+    o[3] = TT * (int)(w / nz);
+    auto lex = [&](int x, int y, int z, int t) {
+        return x + g.L[0] * (y + (long long)g.L[1] * (z + (long long)g.L[2] * t));
+    };
+    // staging order: row r = (t, z, y) of four sites, 48 double2 each
+    auto run = [&](int k, long long &n, int &site, int &e) {
+        const int r = k / 48, q = k - 48 * r, sx = q / 12;
+        e = q - 12 * sx;
+        site = 4 * r + sx;
+        n = lex(o[0] + sx, o[1] + (r & 3), o[2] + (r >> 2 & 3), o[3] + (r >> 4));
+    };
+#pragma unroll
+    for (int k = 0; k < 12; ++k) {
+        long long n;
+        int site, e;
+        run(k * N + tid, n, site, e);
+        tile[site * SS + e] = in[n * 12 + e];
+    }
+    // this thread's site
+    const int xc[4] = {tid & 3, tid >> 2 & 3, tid >> 4 & 3, tid >> 6};
+    int X[4], l = 0, sb = 0;
+#pragma unroll
+    for (int mu = 0; mu < 4; ++mu) {
+        X[mu] = o[mu] + xc[mu];
+        sb += (X[mu] & (g.b[mu] - 1)) << g.sh[mu];
+    }
+    const int lb[4] = {g.sh[1], g.sh[2] - g.sh[1], g.sh[3] - g.sh[2], g.lbvol - g.sh[3]};  // log2 of the block extents
+#pragma unroll
+    for (int mu = 0; mu < 4; ++mu) l += (X[mu] >> lb[mu]) * g.bstride[mu];
+    const LinkField<0> U{u64};
+    Spinor<double> acc;
+    zero(acc);
+    wg_barrier();
+    auto from = [&](const double2 *p, Spinor<double> &x) {
+#pragma unroll
+        for (int c = 0; c < 3; ++c)
+#pragma unroll
+            for (int a = 0; a < 4; ++a) {
+                const double2 t = p[c * 4 + a];
+                x.v[OP == 2 ? a ^ 2 : a][c] = {t.x, t.y};  // D^dagger: gamma_5 swaps the spin pairs
+            }
+    };
+#pragma unroll
+    for (int mu = 0; mu < 4; ++mu) {
+        const int ext = mu == 3 ? TT : 4;
+#pragma unroll
+        for (int dir = 1; dir >= -1; dir -= 2) {
+            // a hop's loads stay behind the hop before it: the compiler would otherwise start them
+            // all at once and spill (84 VGPRs a hop)
+            settle(acc);
+            asm volatile("" : "+v"(l), "+v"(sb), "+v"(X[0]), "+v"(X[1]), "+v"(X[2]), "+v"(X[3]));
+            const int c = xc[mu] + dir;
+            int Y = X[mu] + dir;
+            bool wrap = false;
+            if (Y < 0) Y += g.L[mu], wrap = true;
+            if (Y >= g.L[mu]) Y -= g.L[mu], wrap = true;
+            Spinor<double> psi;
+            if (c >= 0 && c < ext) {
+                from(tile + (tid + dir * (1 << 2 * mu)) * SS, psi);
+            } else {
+                const long long n = lex(mu == 0 ? Y : X[0], mu == 1 ? Y : X[1], mu == 2 ? Y : X[2], mu == 3 ? Y : X[3]);
+                from(in + n * 12, psi);
+            }
+            Mat3<double> W;
+            if (dir > 0) {
+                U.load(g, l, sb, mu, W);
+            } else {
+                const int lj = l + ((Y >> lb[mu]) - (X[mu] >> lb[mu])) * g.bstride[mu];
+                const int sj = sb + (((Y & (g.b[mu] - 1)) - (X[mu] & (g.b[mu] - 1))) << g.sh[mu]);
+                U.load(g, lj, sj, mu, W);
+            }
+            const cx<double> phase = {ph.re[mu], dir > 0 ? ph.im[mu] : -ph.im[mu]};
+            hop(mu, dir, W, psi, wrap, phase, acc);
+        }
+    }
+    // (1 + C) x, one chiral block after the other (72 VGPRs of clover entries each)
+    cx<double> r[2][6], v[2][6];
+    {
+        Spinor<double> x;
+        from(tile + tid * SS, x);
+#pragma unroll
+        for (int a = 0; a < 2; ++a)
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                v[0][a * 3 + c] = x.v[a][c] + x.v[a + 2][c];
+                v[1][a * 3 + c] = x.v[a][c] - x.v[a + 2][c];
+            }
+    }
+#pragma unroll
+    for (int b = 0; b < 2; ++b) {
+        settle(acc);
+        if (b == 1)
+            asm volatile("" : "+v"(l), "+v"(sb) : "v"(r[0][0].re), "v"(r[0][1].re), "v"(r[0][2].re), "v"(r[0][3].re),
+                         "v"(r[0][4].re), "v"(r[0][5].re), "v"(r[0][0].im), "v"(r[0][1].im), "v"(r[0][2].im),
+                         "v"(r[0][3].im), "v"(r[0][4].im), "v"(r[0][5].im));
+        else
+            asm volatile("" : "+v"(l), "+v"(sb));
+        double d[6];
+        cx<double> h[15];
+#pragma unroll
+        for (int j = 0; j < 3; ++j) {
+            const double2 q = ld_stream(&clov[elem(g, l, sb, 36, b * 18 + j)]);
+            d[2 * j] = q.x;
+            d[2 * j + 1] = q.y;
+        }
+#pragma unroll
+        for (int j = 0; j < 15; ++j) {
+            const double2 q = ld_stream(&clov[elem(g, l, sb, 36, b * 18 + 3 + j)]);
+            h[j] = {q.x, q.y};
+        }
+        herm6(d, h, v[b], r[b]);
+    }
+    wg_barrier();
+#pragma unroll
+    for (int c = 0; c < 3; ++c)
+#pragma unroll
+        for (int a = 0; a < 4; ++a) {
+            const int b = OP == 2 ? a ^ 2 : a, q = (b & 1) * 3 + c;
+            const cx<double> y = (b < 2 ? r[0][q] + r[1][q] : r[0][q] - r[1][q]) - kappa * acc.v[b][c];
+            tile[tid * SS + c * 4 + a] = make_double2(y.re, y.im);
+        }
+    wg_barrier();
+#pragma unroll
+    for (int k = 0; k < 12; ++k) {
+        long long n;
+        int site, e;
+        run(k * N + tid, n, site, e);
+        st_stream(&out[n * 12 + e], tile[site * SS + e]);
+    }
+}
+
 // A = I - kappa C_inv H (FP32 links and C_inv, FP32 output, input at precision PIN) on
 // several lattices in one persistent launch: the work items are (lattice, 256-site
 // chunk) pairs numbered lattice by lattice; each workgroup takes the next item from
@@ -1347,6 +1515,26 @@ hipError_t launch_dirac(const Geom &g, hipStream_t st, const DiracArgs &a)
     } else {
         return hipErrorInvalidValue;
     }
+    return hipGetLastError();
+}
+
+hipError_t launch_dirac_can(const Geom &g, hipStream_t st, void *out, const void *in, const void *u64,
+                            const void *clov64, int op, double kappa, const Phase4 &ph)
+{
+    if (op != 0 && op != 2) return hipErrorInvalidValue;
+    const bool cube4 = g.b[0] == 4 && g.b[1] == 4 && g.b[2] == 4 && g.b[3] == 4;
+    // 4^4 tiles, except that a lattice of fewer than 256 of them leaves CUs idle and takes 4^3 tiles, a
+    // wavefront each (8^4: 9.7 against 12.4 us, 8x16^3: 15.0 against 17.0, 16^4 24.0 against 22.3); with
+    // other block shapes the longer index arithmetic makes them no faster (12x8x8x12: 20 against 16 us)
+    const bool big = !cube4 || g.V / 256 >= 256;
+    auto run = [&](auto kern, int tt) {
+        hipLaunchKernelGGL(kern, dim3((unsigned)(g.V / (64 * tt))), dim3(64 * tt), 0, st, g, (double2 *)out,
+                           (const double2 *)in, (const double2 *)u64, (const double2 *)clov64, ph, kappa);
+    };
+    if (op == 0)
+        !cube4 ? run(k_dirac_can<0, 4, false>, 4) : big ? run(k_dirac_can<0, 4, true>, 4) : run(k_dirac_can<0, 1, true>, 1);
+    else
+        !cube4 ? run(k_dirac_can<2, 4, false>, 4) : big ? run(k_dirac_can<2, 4, true>, 4) : run(k_dirac_can<2, 1, true>, 1);
     return hipGetLastError();
 }
 

@@ -216,6 +216,9 @@ hipError_t launch_pack_links(const Geom &g, hipStream_t st, const void *src, voi
 hipError_t launch_clover(const Geom &g, hipStream_t st, const void *u64, const SigmaBlocks &sig, double kcsw,
                          void *clov64, void *cinv32, void *cinv16, int *bad);
 hipError_t launch_dirac(const Geom &g, hipStream_t st, const DiracArgs &a);
+// out = D in (op 0) or D^dagger in (op 2) on canonical spinors, FP64 links and clover blocks
+hipError_t launch_dirac_can(const Geom &g, hipStream_t st, void *out, const void *in, const void *u64,
+                            const void *clov64, int op, double kappa, const Phase4 &ph);
 size_t sap_lds_bytes(const Geom &g, int prec);
 hipError_t launch_sap_half(const Geom &g, hipStream_t st, const SapArgs &a, int colour, int flags);
 // the same half-sweep with FP16 storage and packed FP16 block-local arithmetic; the cross-block

@@ -148,6 +148,18 @@ dd_status k_dirac(dd_ctx *c, void *out, const void *in, int pin, int pout, int p
     return DD_OK;
 }
 
+dd_status k_dirac_can(dd_ctx *c, void *out, const void *in, int op)
+{
+    const double V = (double)c->g.V;
+    hipError_t e = timed(c, DD_KT_DIRAC_F64, V * (2 * sp_b(0) + 4 * lk_b(0) + cl_b(0)),
+                         V * (hops_in(c->g) + hops_out(c->g) + CLOVF), [&] {
+                             return dd::launch_dirac_can(c->g, c->stream, out, in, c->U64, c->clov64, op, c->prm.kappa,
+                                                         c->phase);
+                         });
+    if (e != hipSuccess) return fail(c, DD_ERR_HIP, std::string("dirac launch: ") + hipGetErrorString(e));
+    return DD_OK;
+}
+
 // x = M_SAP b at storage precision prec (1 FP32, 2 FP16), work vector s; rhs.n > 0 sweeps the
 // listed right-hand sides of a batch in each launch (packed FP16 only), faces: their face terms
 // algorithmic bytes and counted flops per swept site of one half-sweep with these flags

@@ -90,6 +90,26 @@ def test_dirac_Ddag_fp64(name):
     assert rel_max(got, want) < 1e-13
 
 
+@pytest.mark.parametrize("dims, block", [((8, 8, 8, 8), (4, 4, 4, 4)), ((16, 16, 16, 16), (4, 4, 4, 4)),
+                                         ((12, 4, 8, 20), (2, 2, 2, 2)), ((8, 16, 16, 4), (4, 8, 4, 2)),
+                                         ((32, 4, 8, 4), (16, 2, 4, 2))])
+def test_dirac_fp64_canonical_tiles(dims, block):
+    """The FP64 apply walks the canonical fields in 4^3 or 4^4 tiles whatever the block shape is: the
+    lattices on both sides of that choice, blocks smaller than, as large as and larger than a tile in
+    a direction, with every boundary phase complex.  The bar of the FP64 apply."""
+    phases = (np.exp(0.3j), np.exp(-0.5j), np.exp(1.1j), -np.exp(0.2j))
+    U = synth.su3_links(dims, 0.4, 151)
+    orc = O.Oracle(O.Params(dims=dims, kappa=0.13, csw=1.3, block=block, phases=phases), U.numpy())
+    s = dd.Solver(dd.Params(dims=dims, kappa=0.13, csw=1.3, block=block, phases=phases), U.cuda())
+    x = synth.gaussian_spinor(dims, 152)
+    xg = x.cuda()
+    D = s.apply(xg, op=dd.DD_OP_D, prec=dd.DD_F64)
+    assert rel_max(D.cpu().numpy(), orc.D(x.numpy())) < 1e-13
+    got = s.apply(xg, op=dd.DD_OP_DDAG, prec=dd.DD_F64).cpu().numpy()
+    assert rel_max(got, g5(orc.D(g5(x.numpy())))) < 1e-13
+    s.close()
+
+
 @pytest.mark.parametrize("name", list(CASES))
 def test_dirac_A_fp32(name):
     c = case(name)
