@@ -416,13 +416,17 @@ class Solver:
     def new_spinor(self):
         return torch.zeros(self.shape + (3, 4), dtype=torch.complex128, device="cuda")
 
+    def _out(self):
+        """A spinor for a call that writes all of it."""
+        return torch.empty(self.shape + (3, 4), dtype=torch.complex128, device="cuda")
+
     def apply(self, x, op=DD_OP_D, prec=DD_F64, out=None):
-        out = self.new_spinor() if out is None else out
+        out = self._out() if out is None else out
         dirac_apply(self.ctx, out, x, prec, op, self.shape)
         return out
 
     def precondition(self, b, prec=DD_F32, out=None):
-        out = self.new_spinor() if out is None else out
+        out = self._out() if out is None else out
         sap_precondition(self.ctx, out, b, prec, self.shape)
         return out
 
@@ -465,7 +469,7 @@ class Solver:
 
     def amsap(self, b, prec=DD_F32, out=None):
         """A M_SAP b (Alg. 3; fused into the SAP's last half-sweeps at FP32)."""
-        out = self.new_spinor() if out is None else out
+        out = self._out() if out is None else out
         sap_precondition_amsap(self.ctx, out, b, prec, self.shape)
         return out
 
@@ -502,7 +506,7 @@ class Solver:
         return out
 
     def unpack(self, f, prec, out=None):
-        out = self.new_spinor() if out is None else out
+        out = self._out() if out is None else out
         dd_unpack_spinor(self.ctx, out, f, prec)
         return out
 
