@@ -46,13 +46,12 @@ struct DiracArgs {
     Phase4 phase;
 };
 
-// the right-hand sides one packed-FP16 SAP launch sweeps, a group one after another in each workgroup:
+// the right-hand sides one packed-FP16 SAP launch sweeps, a workgroup per block and right-hand side:
 // right-hand side idx[k] has its spinor fields sp_stride bytes and its face terms face_stride
 // bytes after those of right-hand side 0 (n = 0: the single fields of the arguments)
 constexpr int SAP_RHS_MAX = 16;
 struct SapRhs {
     int n;
-    int groups;  // workgroups per block, each taking its share of the right-hand sides (set by the launch)
     int idx[SAP_RHS_MAX];
     long long sp_stride, face_stride;
 };

@@ -384,20 +384,25 @@ DD_INL void combine_pair(const SpH &a, float fa, const SpH &b, float fb, const S
     }
 }
 
-// acc += f (1 - s gamma_mu) rebuilt from the pair-form half spinor k, accumulated in
-// FP32 straight from the FP16 parts (mixed-precision FMAs)
-DD_INL void recon_mix(int mu, int s, const PC (&k)[3], float f, Spinor<float> &acc)
+// acc += f (1 - s gamma_mu) rebuilt from the pair-form half spinor k (s = 1 where fwd, else -1),
+// accumulated in FP32 straight from the FP16 parts (mixed-precision FMAs)
+DD_INL void recon_mix(int mu, bool fwd, const PC (&k)[3], float f, Spinor<float> &acc)
 {
-    const float fs = s > 0 ? f : -f;
+    const float fs = fwd ? f : -f;
     auto add = [](cx<float> &a, float fr, float fi) { a = {a.re + fr, a.im + fi}; };
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
         const float r0 = __low2float(k[c].re), r1 = __high2float(k[c].re);
         const float i0 = __low2float(k[c].im), i1 = __high2float(k[c].im);
         if (mu == 3) {  // twice the pair (the factor 2 of 1 - s gamma_4, see proj_pair)
-            const int o = s > 0 ? 2 : 0;
-            add(acc.v[o][c], 2.f * f * r0, 2.f * f * i0);
-            add(acc.v[o + 1][c], 2.f * f * r1, 2.f * f * i1);
+            const float g2 = 2.f * f;
+            if (fwd) {
+                add(acc.v[2][c], g2 * r0, g2 * i0);
+                add(acc.v[3][c], g2 * r1, g2 * i1);
+            } else {
+                add(acc.v[0][c], g2 * r0, g2 * i0);
+                add(acc.v[1][c], g2 * r1, g2 * i1);
+            }
             continue;
         }
         add(acc.v[0][c], f * r0, f * i0);
@@ -415,7 +420,8 @@ DD_INL void recon_mix(int mu, int s, const PC (&k)[3], float f, Spinor<float> &a
     }
 }
 
-// LDS: the Jacobi iterate as 3 x uint4 per site (one colour: u.re, u.im, l.re, l.im)
+// LDS: the Jacobi iterate as 3 x uint4 per site (one colour: u.re, u.im, l.re, l.im), and a zero
+// spinor as site bvol
 DD_INL void lds_put(uint4 *xs, int bvol, int s, const SpH &p)
 {
 #pragma unroll
@@ -425,7 +431,7 @@ DD_INL void lds_put(uint4 *xs, int bvol, int s, const SpH &p)
         v.y = *reinterpret_cast<const unsigned *>(&p.u[c].im);
         v.z = *reinterpret_cast<const unsigned *>(&p.l[c].re);
         v.w = *reinterpret_cast<const unsigned *>(&p.l[c].im);
-        xs[c * bvol + s] = v;
+        xs[c * (bvol + 1) + s] = v;
     }
 }
 
@@ -433,7 +439,7 @@ DD_INL void lds_get(const uint4 *xs, int bvol, int s, SpH &p)
 {
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
-        const uint4 v = xs[c * bvol + s];
+        const uint4 v = xs[c * (bvol + 1) + s];
         p.u[c].re = *reinterpret_cast<const h2 *>(&v.x);
         p.u[c].im = *reinterpret_cast<const h2 *>(&v.y);
         p.l[c].re = *reinterpret_cast<const h2 *>(&v.z);
@@ -451,23 +457,26 @@ DD_INL void lds_link(const h2 *ul, int bvol, int s, int mu, h2 (&U)[3][3])
 }
 
 // acc = H_in x in pair form (hops inside the block, Dirichlet at its faces); bvol is
-// the block volume (a compile-time constant where the kernel is specialised for it)
-DD_INL void inblock_pair(const uint4 *xs, const h2 *ul, const Geom &g, int bvol, const Site &st, SpH &acc)
+// the block volume (a compile-time constant where the kernel is specialised for it).
+// nb[2 mu + side]: the site of the hop from +mu (side 0) or -mu (side 1), bvol (the zero
+// spinor) where that leaves the block: no branch splits the LDS reads of one hop from the
+// arithmetic of the one before it.  Where a wavefront is a t slice (B = 4) the t hops branch.
+template <int B>
+DD_INL void inblock_pair(const uint4 *xs, const h2 *ul, const Geom &g, int bvol, const Site &st, const int (&nb)[8],
+                         SpH &acc)
 {
     zero(acc);
 #pragma unroll
     for (int mu = 0; mu < 4; ++mu) {
-        const int stride = 1 << g.sh[mu];
 #pragma unroll
-        for (int dir = 1; dir >= -1; dir -= 2) {
-            const int c = st.c[mu] + dir;
-            if (c < 0 || c >= g.b[mu]) continue;
-            const int m = st.s + dir * stride;
+        for (int side = 0; side < 2; ++side) {
+            const int m = nb[2 * mu + side];
+            if (B == 4 && mu == 3 && __builtin_amdgcn_readfirstlane(m) == bvol) continue;
             SpH p;
             lds_get(xs, bvol, m, p);
             h2 U[3][3];
-            lds_link(ul, bvol, dir > 0 ? st.s : m, mu, U);
-            hop_pair(mu, dir, U, p, acc);
+            lds_link(ul, bvol, side == 0 ? st.s : (m < bvol ? m : st.s), mu, U);
+            hop_pair(mu, side == 0 ? 1 : -1, U, p, acc);
         }
     }
 }
@@ -554,10 +563,7 @@ DD_INL SpinorField<2> rhs_field(const SpinorField<2> &f, long long off)
 // k_sap_half<2>, except that the cross-block term comes from the face hop terms of the
 // previous half-sweep (faces: the terms, then one scale per block) and that x is written
 // only by the tails of Alg. 1 (a middle half-sweep's x is only ever read through those
-// terms).  FACES_OUT leaves this half-sweep's terms for the next one.  The workgroup sweeps
-// its block for every right-hand side of `rhs` in turn (b, s, x and the face terms of each
-// at their own offsets) with the block's links staged and its C_inv loaded once.  B > 0
-// (4 or 2) fixes the block shape to B^4 at compile time: the block extents, in-block strides and the
+// terms).  FACES_OUT leaves this half-sweep's terms for the next one.  B > 0 (4 or 2) fixes the block shape to B^4 at compile time: the block extents, in-block strides and the
 // block volume become constants, so every LDS offset of the sweeps is an immediate instead
 // of a register and the face index arithmetic folds; B = 0 takes the shape from the geometry.
 // blocks per workgroup of the packed-FP16 half-sweep: blocks of fewer than 64 sites share
@@ -566,10 +572,10 @@ DD_HDI int sap_blocks_per_wg(int bvol) { return bvol < 64 ? 64 / bvol : 1; }
 
 // The body of the half-sweep for the w-th block of the swept colour; the kernels below
 // take w from their launch (one lattice) or from a table of lattices.
-template <int B, bool ONE>
+template <int B>
 DD_INL void sap_half_pk_body(Geom gin, int w, int colour, int flags, SpinorField<2> bsrc, SpinorField<2> sw,
                              SpinorField<2> xw, const __half2 *u16, const __half2 *cpsap, Phase4 ph, float kappa,
-                             int n_jac, h2 *ft, const SapRhs &rhs, int rhs0 = 0, int rhs1 = 1)
+                             int n_jac, h2 *ft)
 {
     extern __shared__ uint4 smem_pk[];
     const Geom g = fixed_shape<B>(gin);
@@ -579,8 +585,8 @@ DD_INL void sap_half_pk_body(Geom gin, int w, int colour, int flags, SpinorField
     const int bpw = sap_blocks_per_wg(bvol);
     const int q = bpw > 1 ? (int)(threadIdx.x >> g.lbvol) : 0;
     const int tid = bpw > 1 ? (int)(threadIdx.x & (bvol - 1)) : (int)threadIdx.x;  // site in the block
-    uint4 *xs = smem_pk + (size_t)q * 12 * bvol;            // 3 x bvol uint4
-    h2 *ul = reinterpret_cast<h2 *>(xs + 3 * bvol);         // 36 x bvol half2
+    uint4 *xs = smem_pk + (size_t)q * (12 * bvol + 3);      // 3 x (bvol + 1) uint4
+    h2 *ul = reinterpret_cast<h2 *>(xs + 3 * (bvol + 1));   // 36 x bvol half2
     __shared__ float wmax[4];
     const int P = face_offset(g, 3, 1) + (bvol >> log2b(g, 3));  // face sites of a block
     wg_skew();
@@ -593,8 +599,7 @@ DD_INL void sap_half_pk_body(Geom gin, int w, int colour, int flags, SpinorField
     block_coords(g, st.l, st.B);
 
     // stage the block's links in LDS as full 3x3 FP16 matrices (row 2 rebuilt from the two stored
-    // rows) and load its C_inv pair coefficients from the SAP-ready copy, once for all right-hand
-    // sides; all loads first, then row 2 and the LDS stores: where the pointers come from a table
+    // rows) and load its C_inv pair coefficients from the SAP-ready copy; all loads first, then row 2 and the LDS stores: where the pointers come from a table
     // (the multi-lattice kernel) the loads are flat, and an LDS store right after each would wait
     // for it
     ClovPair CP;
@@ -612,183 +617,190 @@ DD_INL void sap_half_pk_body(Geom gin, int w, int colour, int flags, SpinorField
                 for (int b = 0; b < 3; ++b) ul[(mu * 9 + a * 3 + b) * bvol + st.s] = lk[mu][a][b];
         }
     }
+    if (tid < 3) xs[tid * (bvol + 1) + bvol] = make_uint4(0, 0, 0, 0);  // read after the first barrier
+    int nb[8];
+#pragma unroll
+    for (int mu = 0; mu < 4; ++mu) {
+        nb[2 * mu] = st.c[mu] + 1 < g.b[mu] ? st.s + (1 << g.sh[mu]) : bvol;
+        nb[2 * mu + 1] = st.c[mu] > 0 ? st.s - (1 << g.sh[mu]) : bvol;
+    }
     const bool pre = (flags & SAP_PRE) != 0;
 
-    // ONE: the fields as given, a single right-hand side (no loop for the compiler to hoist
-    // the neighbour blocks' addresses out of, which would spill them)
-    const int ri0 = ONE ? 0 : rhs0, ri1 = ONE ? 1 : rhs1;
-    for (int ri = ri0; ri < ri1; ++ri) {
-        if (ri > ri0) wg_barrier();  // the previous right-hand side is done with LDS
-        const long long ridx = ONE ? 0 : rhs.idx[ri];
-        const long long off = ONE ? 0 : ridx * rhs.sp_stride;
-        const SpinorField<2> b_r = rhs_field(bsrc, off), s_r = rhs_field(sw, off), x_r = rhs_field(xw, off);
-        h2 *ft_r = ONE ? ft : (h2 *)((char *)ft + ridx * rhs.face_stride);
-        float *fs_r = reinterpret_cast<float *>(ft_r + (long long)g.nblk * 6 * P);  // one scale per block
+    float *fs = reinterpret_cast<float *>(ft + (long long)g.nblk * 6 * P);  // one scale per block
 
-        // s_c as stored: pair form relative to the site scale ssc
-        SpH sraw;
-        const float ssc = load_pair((flags & SAP_FIRST) ? b_r : s_r, g, st.l, st.s, sraw);
+    // s_c as stored: pair form relative to the site scale ssc
+    SpH sraw;
+    const float ssc = load_pair((flags & SAP_FIRST) ? bsrc : sw, g, st.l, st.s, sraw);
 
-        // With PRE, h = H_{c c'} x_{c'} at this site: the hops from the neighbouring blocks, taken
-        // from the terms they left at the shared faces -- on the +mu face the projection of the
-        // neighbour's x, multiplied here by this site's U_mu; on the -mu face the finished
-        // backward term -- summed in FP32 with each neighbour block's scale.
-        Spinor<float> hc;
-        zero(hc);
-        if (pre) {
+    // With PRE, h = H_{c c'} x_{c'} at this site: the hops from the neighbouring blocks, taken
+    // from the terms they left at the shared faces -- on the +mu face the projection of the
+    // neighbour's x, multiplied here by this site's U_mu; on the -mu face the finished
+    // backward term -- summed in FP32 with each neighbour block's scale.  A site lies on at most
+    // one face per direction (extents are at least 2), so one masked pass per direction takes
+    // both sides, its sign a per-lane value; the terms of all directions are loaded before the
+    // first is used, so their latencies overlap.
+    Spinor<float> hc;
+    zero(hc);
+    if (pre) {
+        PC tk[4][3];
+        float tsc[4];
 #pragma unroll
-            for (int mu = 0; mu < 4; ++mu) {
-                const int c = st.c[mu];
-                int kk = 0, w8 = 0;
+        for (int mu = 0; mu < 4; ++mu) {
+            const int c = st.c[mu];
+            const bool fwd = c == g.b[mu] - 1;
+            if (!fwd && c != 0) continue;
+            int kk = 0, w8 = 0;
 #pragma unroll
-                for (int nu = 0; nu < 4; ++nu) {
-                    if (nu == mu) continue;
-                    kk += st.c[nu] << w8;
-                    w8 += log2b(g, nu);
-                }
-                if (c == g.b[mu] - 1) {  // forward hop from block l + mu, whose -mu face holds the projection
-                    const bool edge = st.B[mu] == g.NB[mu] - 1;
-                    const int lj = st.l + (edge ? (1 - g.NB[mu]) : 1) * g.bstride[mu];
-                    PC t[3], k[3];
-                    const float sc = face_in(ft_r, fs_r, lj, face_offset(g, mu, 1) + kk, P, t);
-                    h2 U[3][3];
-                    lds_link(ul, bvol, st.s, mu, U);  // this site's own link, staged by this thread
-                    mat_pair(U, false, t, k);
-                    if (edge) phase_pair(k, (float)ph.re[mu], (float)ph.im[mu]);
-                    recon_mix(mu, 1, k, sc, hc);
-                }
-                if (c == 0) {  // backward hop from block l - mu, whose +mu face holds U^dagger times the projection
-                    const bool edge = st.B[mu] == 0;
-                    const int lj = st.l - (edge ? (1 - g.NB[mu]) : 1) * g.bstride[mu];
-                    PC k[3];
-                    const float sc = face_in(ft_r, fs_r, lj, face_offset(g, mu, 0) + kk, P, k);
-                    if (edge) phase_pair(k, (float)ph.re[mu], (float)-ph.im[mu]);
-                    recon_mix(mu, -1, k, sc, hc);
-                }
+            for (int nu = 0; nu < 4; ++nu) {
+                if (nu == mu) continue;
+                kk += st.c[nu] << w8;
+                w8 += log2b(g, nu);
             }
+            // forward hop from block l + mu, whose -mu face holds the projection; backward hop from
+            // block l - mu, whose +mu face holds U^dagger times the projection
+            const int dB = fwd ? (st.B[mu] == g.NB[mu] - 1 ? 1 - g.NB[mu] : 1) : (st.B[mu] == 0 ? g.NB[mu] - 1 : -1);
+            const int slot = kk + (fwd ? face_offset(g, mu, 1) : face_offset(g, mu, 0));
+            tsc[mu] = face_in(ft, fs, st.l + dB * g.bstride[mu], slot, P, tk[mu]);
         }
+#pragma unroll
+        for (int mu = 0; mu < 4; ++mu) {
+            const int c = st.c[mu];
+            const bool fwd = c == g.b[mu] - 1;
+            if (!fwd && c != 0) continue;
+            if (fwd) {
+                PC k[3];
+                h2 U[3][3];
+                lds_link(ul, bvol, st.s, mu, U);  // this site's own link, staged by this thread
+                mat_pair(U, false, tk[mu], k);
+#pragma unroll
+                for (int q3 = 0; q3 < 3; ++q3) tk[mu][q3] = k[q3];
+            }
+            if (st.B[mu] == (fwd ? g.NB[mu] - 1 : 0))
+                phase_pair(tk[mu], (float)ph.re[mu], (float)(fwd ? ph.im[mu] : -ph.im[mu]));
+            recon_mix(mu, fwd, tk[mu], tsc[mu], hc);
+        }
+    }
 
-        // block normalisation: scale s_c and h to max |component| <= 1 (a stored FP16
-        // spinor has max |component| = 1 relative to its scale)
-        float m = ssc;
+    // block normalisation: scale s_c and h to max |component| <= 1 (a stored FP16
+    // spinor has max |component| = 1 relative to its scale)
+    float m = ssc;
 #pragma unroll
-        for (int a = 0; a < 4; ++a)
+    for (int a = 0; a < 4; ++a)
 #pragma unroll
-            for (int c = 0; c < 3; ++c) m = fmaxf(m, fmaxf(fabsf(hc.v[a][c].re), fabsf(hc.v[a][c].im)));
-        const int wv = bvol < 64 ? bvol : 64;  // lanes of one block in one wavefront
-        for (int o2 = wv / 2; o2 >= 1; o2 >>= 1) m = fmaxf(m, __shfl_xor(m, o2, wv));
-        if (bvol >= 64 && (threadIdx.x & 63) == 0) wmax[threadIdx.x >> 6] = m;
-        wg_barrier();  // also: every link is staged
-        if (bvol >= 64) {  // smaller blocks have their maximum from the shuffles
-            m = 0.f;
-            for (int k = 0; k < bvol / 64; ++k) m = fmaxf(m, wmax[k]);
-        }
-        const float sc = m > 0.f ? 1.f / m : 0.f;
+        for (int c = 0; c < 3; ++c) m = fmaxf(m, fmaxf(fabsf(hc.v[a][c].re), fabsf(hc.v[a][c].im)));
+    const int wv = bvol < 64 ? bvol : 64;  // lanes of one block in one wavefront
+    for (int o2 = wv / 2; o2 >= 1; o2 >>= 1) m = fmaxf(m, __shfl_xor(m, o2, wv));
+    if (bvol >= 64 && (threadIdx.x & 63) == 0) wmax[threadIdx.x >> 6] = m;
+    wg_barrier();  // also: every link is staged
+    if (bvol >= 64) {  // smaller blocks have their maximum from the shuffles
+        m = 0.f;
+        for (int k = 0; k < bvol / 64; ++k) m = fmaxf(m, wmax[k]);
+    }
+    const float sc = m > 0.f ? 1.f / m : 0.f;
 
-        // x0 = s_c + kappa C_inv h (normalised): the first Jacobi step from x = 0; every later
-        // step is x <- x0 + kappa C_inv H_in x
-        SpH x0, x, acc, t;
-        scale_pair(sraw, ssc * sc, x0);
-        const h2 K = __float2half2_rn(kappa);
-        if (pre) {
-            SpH hp;
-            to_pair(hc, sc, hp);
-            clover_pair(CP, hp, t);
+    // x0 = s_c + kappa C_inv h (normalised): the first Jacobi step from x = 0; every later
+    // step is x <- x0 + kappa C_inv H_in x
+    SpH x0, x, acc, t;
+    scale_pair(sraw, ssc * sc, x0);
+    const h2 K = __float2half2_rn(kappa);
+    if (pre) {
+        SpH hp;
+        to_pair(hc, sc, hp);
+        clover_pair(CP, hp, t);
 #pragma unroll
-            for (int c = 0; c < 3; ++c) {
-                x0.u[c] = PC{fma2(K, t.u[c].re, x0.u[c].re), fma2(K, t.u[c].im, x0.u[c].im)};
-                x0.l[c] = PC{fma2(K, t.l[c].re, x0.l[c].re), fma2(K, t.l[c].im, x0.l[c].im)};
-            }
+        for (int c = 0; c < 3; ++c) {
+            x0.u[c] = PC{fma2(K, t.u[c].re, x0.u[c].re), fma2(K, t.u[c].im, x0.u[c].im)};
+            x0.l[c] = PC{fma2(K, t.l[c].re, x0.l[c].re), fma2(K, t.l[c].im, x0.l[c].im)};
         }
-        x = x0;
-        for (int j = 0; j < n_jac; ++j) {
-            wg_barrier();
-            lds_put(xs, bvol, st.s, x);
-            wg_barrier();
-            inblock_pair(xs, ul, g, bvol, st, acc);
-            clover_pair(CP, acc, t);
+    }
+    x = x0;
+    for (int j = 0; j < n_jac; ++j) {
+        if (j > 0) wg_barrier();  // the readers of the last iterate are done
+        lds_put(xs, bvol, st.s, x);
+        wg_barrier();
+        inblock_pair<B>(xs, ul, g, bvol, st, nb, acc);
+        clover_pair(CP, acc, t);
 #pragma unroll
-            for (int c = 0; c < 3; ++c) {
-                x.u[c] = PC{fma2(K, t.u[c].re, x0.u[c].re), fma2(K, t.u[c].im, x0.u[c].im)};
-                x.l[c] = PC{fma2(K, t.l[c].re, x0.l[c].re), fma2(K, t.l[c].im, x0.l[c].im)};
-            }
+        for (int c = 0; c < 3; ++c) {
+            x.u[c] = PC{fma2(K, t.u[c].re, x0.u[c].re), fma2(K, t.u[c].im, x0.u[c].im)};
+            x.l[c] = PC{fma2(K, t.l[c].re, x0.l[c].re), fma2(K, t.l[c].im, x0.l[c].im)};
         }
-        const float inv = m;  // undo the normalisation
-        if (!(flags & SAP_TAIL)) {
-            // s_c <- (s_c + kappa C_inv h) + b_c - x_c + kappa C_inv H_in x_c, in FP32
-            wg_barrier();
-            lds_put(xs, bvol, st.s, x);
-            wg_barrier();
-            inblock_pair(xs, ul, g, bvol, st, acc);
-            clover_pair(CP, acc, t);
-            SpH braw;
-            const float sb = load_pair(b_r, g, st.l, st.s, braw);
-            Spinor<float> snew;
-            combine_pair(x0, inv, braw, sb, x, -inv, t, kappa * inv, snew);
-            s_r.store(g, st.l, st.s, snew);
-        } else {
-            Spinor<float> xf;
-            from_pair(x, inv, xf);
-            x_r.store(g, st.l, st.s, xf);
-            if (flags & SAP_FACES_OUT) {
-                wg_barrier();
-                lds_put(xs, bvol, st.s, x);
-            }
-        }
+    }
+    const float inv = m;  // undo the normalisation
+    if (!(flags & SAP_TAIL)) {
+        // s_c <- (s_c + kappa C_inv h) + b_c - x_c + kappa C_inv H_in x_c, in FP32
+        wg_barrier();
+        lds_put(xs, bvol, st.s, x);
+        wg_barrier();
+        inblock_pair<B>(xs, ul, g, bvol, st, nb, acc);
+        clover_pair(CP, acc, t);
+        SpH braw;
+        const float sb = load_pair(bsrc, g, st.l, st.s, braw);
+        Spinor<float> snew;
+        combine_pair(x0, inv, braw, sb, x, -inv, t, kappa * inv, snew);
+        sw.store(g, st.l, st.s, snew);
+    } else {
+        Spinor<float> xf;
+        from_pair(x, inv, xf);
+        xw.store(g, st.l, st.s, xf);
         if (flags & SAP_FACES_OUT) {
-            // this block's face terms from x in LDS (put there by the s update, or just above),
-            // spread evenly over the workgroup
             wg_barrier();
-            const bool equal_faces = g.b[0] == g.b[1] && g.b[1] == g.b[2] && g.b[2] == g.b[3];
-            const int lnf = g.lbvol - log2b(g, 0);  // log2 of the sites per face
-            for (int p = tid; p < P; p += bvol) {
-                int q = 0, base = 0;
-                if (equal_faces) {  // hypercubic block: face q holds sites q * nf ... q * nf + nf - 1
-                    q = p >> lnf;
-                    base = q << lnf;
-                } else {
+            lds_put(xs, bvol, st.s, x);
+        }
+    }
+    if (flags & SAP_FACES_OUT) {
+        // this block's face terms from x in LDS (put there by the s update, or just above),
+        // spread evenly over the workgroup
+        wg_barrier();
+        const bool equal_faces = g.b[0] == g.b[1] && g.b[1] == g.b[2] && g.b[2] == g.b[3];
+        const int lnf = g.lbvol - log2b(g, 0);  // log2 of the sites per face
+        for (int p = tid; p < P; p += bvol) {
+            int q = 0, base = 0;
+            if (equal_faces) {  // hypercubic block: face q holds sites q * nf ... q * nf + nf - 1
+                q = p >> lnf;
+                base = q << lnf;
+            } else {
 #pragma unroll
-                    for (int qq = 0; qq < 7; ++qq) {
-                        const int n = bvol >> log2b(g, qq >> 1);
-                        if (q == qq && p >= base + n) {
-                            base += n;
-                            q = qq + 1;
-                        }
+                for (int qq = 0; qq < 7; ++qq) {
+                    const int n = bvol >> log2b(g, qq >> 1);
+                    if (q == qq && p >= base + n) {
+                        base += n;
+                        q = qq + 1;
                     }
                 }
-                const int kk = p - base;
-                switch (q) {  // faces in order +x, -x, +y, -y, +z, -z, +t, -t
-                case 0: face_out<0, 0>(g, st.l, kk, p, P, xs, ul, bvol, ft_r); break;
-                case 1: face_out<0, 1>(g, st.l, kk, p, P, xs, ul, bvol, ft_r); break;
-                case 2: face_out<1, 0>(g, st.l, kk, p, P, xs, ul, bvol, ft_r); break;
-                case 3: face_out<1, 1>(g, st.l, kk, p, P, xs, ul, bvol, ft_r); break;
-                case 4: face_out<2, 0>(g, st.l, kk, p, P, xs, ul, bvol, ft_r); break;
-                case 5: face_out<2, 1>(g, st.l, kk, p, P, xs, ul, bvol, ft_r); break;
-                case 6: face_out<3, 0>(g, st.l, kk, p, P, xs, ul, bvol, ft_r); break;
-                default: face_out<3, 1>(g, st.l, kk, p, P, xs, ul, bvol, ft_r); break;
-                }
             }
-            if (tid == 0) fs_r[st.l] = inv;
+            const int kk = p - base;
+            switch (q) {  // faces in order +x, -x, +y, -y, +z, -z, +t, -t
+            case 0: face_out<0, 0>(g, st.l, kk, p, P, xs, ul, bvol, ft); break;
+            case 1: face_out<0, 1>(g, st.l, kk, p, P, xs, ul, bvol, ft); break;
+            case 2: face_out<1, 0>(g, st.l, kk, p, P, xs, ul, bvol, ft); break;
+            case 3: face_out<1, 1>(g, st.l, kk, p, P, xs, ul, bvol, ft); break;
+            case 4: face_out<2, 0>(g, st.l, kk, p, P, xs, ul, bvol, ft); break;
+            case 5: face_out<2, 1>(g, st.l, kk, p, P, xs, ul, bvol, ft); break;
+            case 6: face_out<3, 0>(g, st.l, kk, p, P, xs, ul, bvol, ft); break;
+            default: face_out<3, 1>(g, st.l, kk, p, P, xs, ul, bvol, ft); break;
+            }
         }
+        if (tid == 0) fs[st.l] = inv;
     }
 }
 
-template <int B, bool ONE>
+template <int B>
 __global__ void __launch_bounds__(256) k_sap_half_pk(Geom gin, int colour, int flags, SpinorField<2> bsrc,
                                                      SpinorField<2> sw, SpinorField<2> xw, const __half2 *u16,
                                                      const __half2 *cpsap, Phase4 ph, float kappa, int n_jac, h2 *ft,
                                                      SapRhs rhs)
 {
-    int w = xcd_remap(blockIdx.x, gridDim.x), r0 = 0, r1 = 1;
-    if constexpr (!ONE) {
-        // workgroup (block, group of right-hand sides): the groups of a block are consecutive on one XCD
-        const int item = w / rhs.groups, per = (rhs.n + rhs.groups - 1) / rhs.groups;
-        r0 = (w - item * rhs.groups) * per;
-        r1 = r0 + per < rhs.n ? r0 + per : rhs.n;
-        w = item;
-        if (r0 >= r1) return;  // the whole workgroup: n need not be a multiple of the groups
-    }
-    sap_half_pk_body<B, ONE>(gin, w, colour, flags, bsrc, sw, xw, u16, cpsap, ph, kappa, n_jac, ft, rhs, r0, r1);
+    // work item (block, right-hand side): the right-hand sides of a block are consecutive on one XCD.
+    // A workgroup that is alone on its CU takes some 8 us to start, stage its block and finish, and
+    // 1.7 us per Jacobi step, so a workgroup that took the right-hand sides in turn left small
+    // lattices bound by that latency: 12 of them on 16^3x32 (256 blocks per colour) took 189.5 us per
+    // half-sweep, now 114; on 8^4 190 and 22.  On 32^4, where sharing the staged links and C_inv
+    // between right-hand sides is worth most, the two forms are level.
+    const int item = xcd_remap(blockIdx.x, gridDim.x), w = item / rhs.n;
+    const long long ridx = rhs.idx[item - w * rhs.n], off = ridx * rhs.sp_stride;
+    sap_half_pk_body<B>(gin, w, colour, flags, rhs_field(bsrc, off), rhs_field(sw, off), rhs_field(xw, off), u16, cpsap,
+                        ph, kappa, n_jac, (h2 *)((char *)ft + ridx * rhs.face_stride));
 }
 
 // The same half-sweep on several lattices of one block shape in one launch: the work items
@@ -804,10 +816,7 @@ __global__ void __launch_bounds__(256) k_sap_half_pk_multi(SapLatTab t, int colo
     int k = 0;
     while (k + 1 < t.n && w >= t.e[k + 1].item0) ++k;
     const SapLat &L = t.e[k];
-    SapRhs one{};
-    one.n = 1;
-    sap_half_pk_body<B, true>(L.g, w - L.item0, colour, flags, L.b, L.s, L.x, L.u16, L.cpsap, L.ph, L.kappa, L.n_jac, L.ft,
-                        one);
+    sap_half_pk_body<B>(L.g, w - L.item0, colour, flags, L.b, L.s, L.x, L.u16, L.cpsap, L.ph, L.kappa, L.n_jac, L.ft);
 }
 
 // face sites of one block, and the bytes of the face terms of a lattice (6 half2 per face
@@ -826,24 +835,8 @@ size_t sap_face_bytes(const Geom &g)
 
 size_t sap_pk_lds_bytes(const Geom &g)
 {
-    // the Jacobi iterate and the staged links
-    return (size_t)g.bvol * (3 * sizeof(uint4) + 36 * sizeof(__half2));
-}
-
-// Groups into which the n right-hand sides of a batch are split, each group a workgroup of its own
-// per block (items workgroups cover the blocks).  A workgroup that is alone on its CU takes 6.5 us
-// to start and stage its block and 15.2 us per right-hand side, three side by side 28 us per
-// right-hand side of each: small lattices are bound by that latency, so every right-hand side gets
-// a workgroup of its own (12 of them on 16^3x32, 256 blocks per colour: 189.5 us per half-sweep in
-// one group, 114 us in 12; 8^4: 190 and 22 us).  Once the launch is many times the 768 workgroups
-// the chip holds, sharing the staged links and C_inv is worth more: the smallest even split that
-// still leaves 6144 of them (12 right-hand sides on 32^4: 844 us in one group, 799 us in 3, 849 us
-// in 12).
-static int sap_rhs_groups(int items, int n)
-{
-    for (int G = 1; G < n; ++G)
-        if (n % G == 0 && (long long)items * G >= 6144) return G;
-    return n;
+    // the Jacobi iterate with its zero spinor, and the staged links
+    return (size_t)g.bvol * (3 * sizeof(uint4) + 36 * sizeof(__half2)) + 3 * sizeof(uint4);
 }
 
 hipError_t launch_sap_half_pk(const Geom &g, hipStream_t st, const SapArgs &a, int colour, int flags)
@@ -855,20 +848,16 @@ hipError_t launch_sap_half_pk(const Geom &g, hipStream_t st, const SapArgs &a, i
     const bool cube4 = g.b[0] == 4 && g.b[1] == 4 && g.b[2] == 4 && g.b[3] == 4;
     const bool cube2 = g.b[0] == 2 && g.b[1] == 2 && g.b[2] == 2 && g.b[3] == 2;
     SapRhs rhs = a.rhs;
-    const bool one = rhs.n <= 0;  // one right-hand side (the fields as given)
-    if (one) {
+    if (rhs.n <= 0) {  // the fields as given
         rhs = SapRhs{};
         rhs.n = 1;
     }
     if (rhs.n > SAP_RHS_MAX) return hipErrorInvalidValue;
-    auto kern = cube4   ? (one ? k_sap_half_pk<4, true> : k_sap_half_pk<4, false>)
-                : cube2 ? (one ? k_sap_half_pk<2, true> : k_sap_half_pk<2, false>)
-                        : (one ? k_sap_half_pk<0, true> : k_sap_half_pk<0, false>);
     const int bpw = sap_blocks_per_wg(g.bvol);  // (g.nblk / 2 is a multiple of 8: every direction holds an even
                                                  // number of blocks)
     const int items = g.nblk / 2 / bpw;
-    rhs.groups = one ? 1 : sap_rhs_groups(items, rhs.n);
-    hipLaunchKernelGGL(kern, dim3(items * rhs.groups), dim3(g.bvol * bpw), bpw * sap_pk_lds_bytes(g), st, g, colour, flags,
+    auto kern = cube4 ? k_sap_half_pk<4> : cube2 ? k_sap_half_pk<2> : k_sap_half_pk<0>;
+    hipLaunchKernelGGL(kern, dim3(items * rhs.n), dim3(g.bvol * bpw), bpw * sap_pk_lds_bytes(g), st, g, colour, flags,
                        sfh((void *)a.b), sfh(a.s), sfh(a.x), (const __half2 *)a.links, (const __half2 *)a.cinv, a.phase,
                        (float)a.kappa, a.n_jac, (h2 *)a.faces, rhs);
     return hipGetLastError();

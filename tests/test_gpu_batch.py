@@ -190,10 +190,9 @@ def test_sap_batch_matches_single_and_oracle(name, fp16_arith):
 
 
 @pytest.mark.parametrize("dims, n", [((8, 8, 8, 8), 1), ((8, 8, 8, 8), 16), ((24, 16, 32, 32), 16), ((32, 32, 32, 32), 9)])
-def test_sap_batch_groups_match_single(dims, n):
-    """The batched half-sweep gives every (block, right-hand side) a workgroup of its own on small
-    lattices and splits the right-hand sides into even groups on large ones (two of them per workgroup
-    on 24x16x32x32 with 16, three on 32^4 with 9): each result equals sap_precondition on that
+def test_sap_batch_workgroups_match_single(dims, n):
+    """The batched half-sweep gives every block and right-hand side a workgroup of its own, from one
+    right-hand side on 8 blocks per colour to 9 on 2048: each result equals sap_precondition on that
     right-hand side alone, bit for bit."""
     s = dd.Solver(dd.Params(dims=dims, kappa=0.125, csw=1.5, n_sap=1, n_jac=2),
                   synth.su3_links(dims, 0.3, 341, device="cuda"))
