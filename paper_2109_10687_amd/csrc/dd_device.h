@@ -11,12 +11,16 @@
 //   A field with E complex elements per site stores element e of site (l, s)
 //   at ((l*E + e) * bvol + s): consecutive lanes read consecutive addresses.
 //   spinor   E = 12, element k = spin*3 + colour
-//   link     E = 4*9  (element (mu*9 + a*3 + b)),  FP16 copy E = 4*6 (rows 0,1)
+//   link     E = 4*9  (element (mu*9 + a*3 + b)),  FP32 copy E = 4*6 (rows 0,1)
 //   clover   E = 36: two 6x6 Hermitian blocks (gamma_5-diagonal basis), each
 //            3 complex holding the 6 real diagonal entries pairwise, then the
 //            15 upper off-diagonal entries row by row.
-//   FP16 spinors carry one FP32 scale per site (max |component|), stored after
-//   the 12*V half2 elements.
+//   FP16 spinors hold a site's twelve components as three 16-byte groups, one per colour c:
+//   (psi_0.re, psi_1.re), (psi_0.im, psi_1.im), (psi_2.re, psi_3.re), (psi_2.im, psi_3.im);
+//   group c of site (l, s) is at 16-byte index ((3 l + c) * bvol + s).  They carry one FP32 scale
+//   per site (max |component|), stored after the V * 3 groups.
+//   FP16 links hold the two stored rows of a link as three 8-byte groups of two entries, group
+//   k of U_mu(l, s) at 8-byte index ((12 l + 3 mu + k) * bvol + s).
 #pragma once
 
 #include <hip/hip_fp16.h>
@@ -267,6 +271,17 @@ DD_INL __half2 ld_stream(const __half2 *p)
     unsigned int v = __builtin_nontemporal_load((const unsigned int *)p);
     return *reinterpret_cast<__half2 *>(&v);
 }
+typedef unsigned u4nt_t __attribute__((ext_vector_type(4)));
+DD_INL uint4 ld_stream(const uint4 *p)
+{
+    const u4nt_t v = __builtin_nontemporal_load((const u4nt_t *)p);
+    return make_uint4(v.x, v.y, v.z, v.w);
+}
+DD_INL void st_stream(uint4 *p, uint4 x)
+{
+    const u4nt_t v = {x.x, x.y, x.z, x.w};
+    __builtin_nontemporal_store(v, (u4nt_t *)p);
+}
 DD_INL void st_stream(double2 *p, double2 x)
 {
     d2nt_t v = {x.x, x.y};
@@ -344,19 +359,28 @@ template <> struct SpinorField<1> {
     }
 };
 
+// a colour's 16-byte group of an FP16 spinor: the four spins of colour c, times sc
+template <typename R> DD_INL void unpack16(const uint4 &v, float sc, int c, Spinor<R> &x)
+{
+    auto f = [](unsigned u) { return __half22float2(*reinterpret_cast<const __half2 *>(&u)); };
+    const float2 ur = f(v.x), ui = f(v.y), lr = f(v.z), li = f(v.w);
+    x.v[0][c] = {R(ur.x * sc), R(ui.x * sc)};
+    x.v[1][c] = {R(ur.y * sc), R(ui.y * sc)};
+    x.v[2][c] = {R(lr.x * sc), R(li.x * sc)};
+    x.v[3][c] = {R(lr.y * sc), R(li.y * sc)};
+}
+
 template <> struct SpinorField<2> {
-    __half2 *p;    // 12 * V half2
-    float *scale;  // V scales, right after the half2 block
+    __half2 *p;    // 3 * V 16-byte groups
+    float *scale;  // V scales, right after them
+    // group 0 of a site (the others bvol groups apart)
+    DD_INL uint4 *site(const Geom &g, int l, int s) const { return reinterpret_cast<uint4 *>(p) + elem(g, l, s, 3, 0); }
     template <typename R> DD_INL void load(const Geom &g, int l, int s, Spinor<R> &x) const
     {
-        float sc = scale[((long long)l << g.lbvol) + s];
+        const float sc = scale[((long long)l << g.lbvol) + s];
+        const uint4 *v = site(g, l, s);
 #pragma unroll
-        for (int a = 0; a < 4; ++a)
-#pragma unroll
-            for (int c = 0; c < 3; ++c) {
-                float2 t = __half22float2(p[elem(g, l, s, 12, a * 3 + c)]);
-                x.v[a][c] = {R(t.x * sc), R(t.y * sc)};
-            }
+        for (int c = 0; c < 3; ++c) unpack16(v[c << g.lbvol], sc, c, x);
     }
     template <typename R> DD_INL void store(const Geom &g, int l, int s, const Spinor<R> &x, bool stream = false) const
     {
@@ -373,16 +397,20 @@ template <> struct SpinorField<2> {
             st_stream(&scale[((long long)l << g.lbvol) + s], m);
         else
             scale[((long long)l << g.lbvol) + s] = m;
+        auto pk = [&](R a, R b) {
+            const __half2 v = __floats2half2_rn((float)a * inv, (float)b * inv);
+            return *reinterpret_cast<const unsigned *>(&v);
+        };
+        uint4 *v = site(g, l, s);
 #pragma unroll
-        for (int a = 0; a < 4; ++a)
-#pragma unroll
-            for (int c = 0; c < 3; ++c) {
-                __half2 v = __floats2half2_rn((float)x.v[a][c].re * inv, (float)x.v[a][c].im * inv);
-                if (stream)
-                    st_stream(&p[elem(g, l, s, 12, a * 3 + c)], v);
-                else
-                    p[elem(g, l, s, 12, a * 3 + c)] = v;
-            }
+        for (int c = 0; c < 3; ++c) {
+            const uint4 q = make_uint4(pk(x.v[0][c].re, x.v[1][c].re), pk(x.v[0][c].im, x.v[1][c].im),
+                                       pk(x.v[2][c].re, x.v[3][c].re), pk(x.v[2][c].im, x.v[3][c].im));
+            if (stream)
+                st_stream(&v[c << g.lbvol], q);
+            else
+                v[c << g.lbvol] = q;
+        }
     }
 };
 
@@ -433,17 +461,27 @@ template <> struct LinkField<1> {
     }
 };
 
+// group 0 of an FP16 link (the others bvol groups apart)
+DD_INL const uint2 *link16_site(const __half2 *p, const Geom &g, int l, int s, int mu)
+{
+    return reinterpret_cast<const uint2 *>(p) + elem(g, l, s, 12, 3 * mu);
+}
+
 template <> struct LinkField<2> {
     const __half2 *p;
     template <typename R> DD_INL void load(const Geom &g, int l, int s, int mu, Mat3<R> &U) const
     {
+        const uint2 *v = link16_site(p, g, l, s, mu);
+        auto put = [&](int e, unsigned u) {
+            const float2 t = __half22float2(*reinterpret_cast<const __half2 *>(&u));
+            U.m[e / 3][e % 3] = {R(t.x), R(t.y)};
+        };
 #pragma unroll
-        for (int a = 0; a < 2; ++a)
-#pragma unroll
-            for (int b = 0; b < 3; ++b) {
-                float2 t = __half22float2(p[elem(g, l, s, 24, mu * 6 + a * 3 + b)]);
-                U.m[a][b] = {R(t.x), R(t.y)};
-            }
+        for (int k = 0; k < 3; ++k) {
+            const uint2 t = v[k << g.lbvol];
+            put(2 * k, t.x);
+            put(2 * k + 1, t.y);
+        }
         su3_row3(U);
     }
 };

@@ -65,7 +65,7 @@ __global__ void __launch_bounds__(256) k_unpack_spinor(Geom g, double2 *dst, Spi
 // canonical links [4][Lt][Lz][Ly][Lx][3][3] -> FP64 (18 reals), FP32 and FP16 (rows 0 and
 // 1, 12 reals); flags non-finite entries
 __global__ void __launch_bounds__(256)
-    k_pack_links(Geom g, const double2 *src, double2 *u64, float2 *u32, __half2 *u16, int *bad)
+    k_pack_links(Geom g, const double2 *src, double2 *u64, float2 *u32, uint2 *u16, int *bad)
 {
     long long i = (long long)blockIdx.x * 256 + threadIdx.x;
     if (i >= g.V) return;
@@ -75,6 +75,7 @@ __global__ void __launch_bounds__(256)
     int nonfinite = 0;
     for (int mu = 0; mu < 4; ++mu) {
         const double2 *m = src + ((long long)mu * g.V + n) * 9;
+        unsigned h[6];
 #pragma unroll
         for (int e = 0; e < 9; ++e) {
             double2 t = m[e];
@@ -82,9 +83,12 @@ __global__ void __launch_bounds__(256)
             u64[elem(g, st.l, st.s, 36, mu * 9 + e)] = t;
             if (e < 6) {
                 u32[elem(g, st.l, st.s, 24, mu * 6 + e)] = make_float2((float)t.x, (float)t.y);
-                u16[elem(g, st.l, st.s, 24, mu * 6 + e)] = __floats2half2_rn((float)t.x, (float)t.y);
+                const __half2 v = __floats2half2_rn((float)t.x, (float)t.y);
+                h[e] = *reinterpret_cast<const unsigned *>(&v);
             }
         }
+#pragma unroll
+        for (int k = 0; k < 3; ++k) u16[elem(g, st.l, st.s, 12, 3 * mu + k)] = make_uint2(h[2 * k], h[2 * k + 1]);
     }
     if (nonfinite) atomicOr(bad, 1);
 }
@@ -301,37 +305,35 @@ __global__ void __launch_bounds__(256) k_dirac(Geom gin, SpinorField<POUT> out, 
 // The hop order and arithmetic are those of dirac_site; results agree to FP32 (FP64) rounding,
 // not bit for bit, since the compiler fuses multiply-adds differently in the two kernels.
 template <int P> struct StoreT;
-template <> struct StoreT<0> { using T = double2; };
-template <> struct StoreT<1> { using T = float2; };
-template <> struct StoreT<2> { using T = __half2; };
+template <> struct StoreT<0> { using T = double2; static constexpr int N = 12; };
+template <> struct StoreT<1> { using T = float2; static constexpr int N = 12; };
+template <> struct StoreT<2> { using T = uint4; static constexpr int N = 3; };
 
-// one site's spinor as stored: 12 elements (256 apart in a 4^4 block) and the FP16 scale
+// one site's spinor as stored: its elements (256 apart in a 4^4 block) and the FP16 scale
 template <int P> struct RawSp {
-    typename StoreT<P>::T e[12];
+    typename StoreT<P>::T e[StoreT<P>::N];
     float sc;
 };
 
 template <int P> DD_INL void raw_load(const typename StoreT<P>::T *p, const float *sp, RawSp<P> &r)
 {
 #pragma unroll
-    for (int e = 0; e < 12; ++e) r.e[e] = p[e * 256];
+    for (int e = 0; e < StoreT<P>::N; ++e) r.e[e] = p[e * 256];
     r.sc = P == 2 ? *sp : 1.f;
 }
 
 // the conversion SpinorField<P>::load applies
 template <int P, typename R> DD_INL void raw_to(const RawSp<P> &r, Spinor<R> &x)
 {
+    if constexpr (P == 2) {
 #pragma unroll
-    for (int a = 0; a < 4; ++a)
+        for (int c = 0; c < 3; ++c) unpack16(r.e[c], r.sc, c, x);
+    } else {
 #pragma unroll
-        for (int c = 0; c < 3; ++c) {
-            if constexpr (P == 2) {
-                float2 t = __half22float2(r.e[a * 3 + c]);
-                x.v[a][c] = {R(t.x * r.sc), R(t.y * r.sc)};
-            } else {
-                x.v[a][c] = {R(r.e[a * 3 + c].x), R(r.e[a * 3 + c].y)};
-            }
-        }
+        for (int a = 0; a < 4; ++a)
+#pragma unroll
+            for (int c = 0; c < 3; ++c) x.v[a][c] = {R(r.e[a * 3 + c].x), R(r.e[a * 3 + c].y)};
+    }
 }
 
 template <int PIN, int POUT, int PG, int OP>
@@ -341,7 +343,8 @@ __global__ void __launch_bounds__(256) k_dirac_ts(Geom gin, SpinorField<POUT> ou
     using R = typename Acc<PIN, PG>::T;
     using T = typename StoreT<PIN>::T;
     const Geom g = fixed_shape<4>(gin);
-    __shared__ T tile[12][256];                     // this block's input
+    constexpr int NE = StoreT<PIN>::N;
+    __shared__ T tile[NE][256];                     // this block's input
     __shared__ float tsc[PIN == 2 ? 256 : 1];
     __shared__ cx<R> carry[2][6][64];               // backward t hop terms, by step parity
     wg_skew();
@@ -378,9 +381,9 @@ __global__ void __launch_bounds__(256) k_dirac_ts(Geom gin, SpinorField<POUT> ou
         // stage the block
         {
             RawSp<PIN> own;
-            raw_load<PIN>(&in.p[elem(g, st.l, sl, 12, 0)], scale_at(((long long)st.l << 8) + sl), own);
+            raw_load<PIN>((const T *)in.p + elem(g, st.l, sl, NE, 0), scale_at(((long long)st.l << 8) + sl), own);
 #pragma unroll
-            for (int e = 0; e < 12; ++e) tile[e][sl] = own.e[e];
+            for (int e = 0; e < NE; ++e) tile[e][sl] = own.e[e];
             if constexpr (PIN == 2) tsc[sl] = own.sc;
         }
         wg_barrier();
@@ -404,7 +407,7 @@ __global__ void __launch_bounds__(256) k_dirac_ts(Geom gin, SpinorField<POUT> ou
                 const int lj = (int)(j >> 8), sj = (int)(j & 255);
                 // one load path for both sources: LDS and HBM hold the elements 256 apart
                 RawSp<PIN> r;
-                raw_load<PIN>(inblk ? &tile[0][sj] : &in.p[elem(g, lj, sj, 12, 0)],
+                raw_load<PIN>(inblk ? &tile[0][sj] : (const T *)in.p + elem(g, lj, sj, NE, 0),
                               inblk ? &tsc[PIN == 2 ? sj : 0] : scale_at(j), r);
                 Spinor<R> psi;
                 raw_to<PIN>(r, psi);
@@ -677,7 +680,12 @@ template <> struct SapLinks<2> {
     const __half2 *p;
     DD_INL void stage(T *lds, const Geom &g, int l, int s) const
     {
-        for (int e = 0; e < E; ++e) lds[e * g.bvol + s] = p[elem(g, l, s, E, e)];
+        const uint2 *v = link16_site(p, g, l, s, 0);
+        for (int k = 0; k < E / 2; ++k) {
+            const uint2 t = v[k << g.lbvol];
+            lds[2 * k * g.bvol + s] = *reinterpret_cast<const __half2 *>(&t.x);
+            lds[(2 * k + 1) * g.bvol + s] = *reinterpret_cast<const __half2 *>(&t.y);
+        }
     }
     DD_INL void load(const T *lds, const Geom &g, int, int s, int mu, Mat3<float> &U) const
     {
@@ -898,11 +906,13 @@ template <> struct Elem<1> {
 template <> struct Elem<2> {  // read only: the scale belongs to the whole site
     DD_INL static cx<double> get(const SpinorField<2> &f, const Geom &g, long long o)
     {
-        long long blk12 = o >> g.lbvol;  // l*12 + e
-        long long site = ((blk12 / 12) << g.lbvol) + (o & (g.bvol - 1));
-        float sc = f.scale[site];
-        float2 t = __half22float2(f.p[o]);
-        return {(double)(t.x * sc), (double)(t.y * sc)};
+        const long long blk12 = o >> g.lbvol;  // l*12 + e, e = 3 spin + colour
+        const int l = (int)(blk12 / 12), e = (int)(blk12 - 12LL * l), a = e / 3, c = e - 3 * a;
+        const int s = (int)(o & (g.bvol - 1));
+        const float sc = f.scale[((long long)l << g.lbvol) + s];
+        const __half2 *v = reinterpret_cast<const __half2 *>(f.site(g, l, s) + (c << g.lbvol)) + (a & 2);
+        const float2 re = __half22float2(v[0]), im = __half22float2(v[1]);
+        return {(double)((a & 1 ? re.y : re.x) * sc), (double)((a & 1 ? im.y : im.x) * sc)};
     }
 };
 
@@ -1445,7 +1455,7 @@ hipError_t launch_unpack_spinor(const Geom &g, hipStream_t st, int prec, void *d
 hipError_t launch_pack_links(const Geom &g, hipStream_t st, const void *src, void *u64, void *u32, void *u16, int *bad)
 {
     hipLaunchKernelGGL(k_pack_links, dim3(grid_sites(g.V, 256)), dim3(256), 0, st, g, (const double2 *)src,
-                       (double2 *)u64, (float2 *)u32, (__half2 *)u16, bad);
+                       (double2 *)u64, (float2 *)u32, (uint2 *)u16, bad);
     return hipGetLastError();
 }
 

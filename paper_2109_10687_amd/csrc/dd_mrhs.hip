@@ -354,8 +354,8 @@ __global__ void __launch_bounds__(256) k_dirac_rhs_vec(Geom gin, MrhsArgs a)
 // tile, and a right-hand side costs its own spinor, its cross-block neighbours (with their
 // links) and the output.
 template <int PIN> struct ResT;
-template <> struct ResT<1> { using T = float2; };
-template <> struct ResT<2> { using T = __half2; };
+template <> struct ResT<1> { using T = float2; static constexpr int N = 12; };
+template <> struct ResT<2> { using T = uint4; static constexpr int N = 3; };
 
 template <int PIN>
 __global__ void __launch_bounds__(256) k_dirac_rhs_res(Geom gin, MrhsArgs a)
@@ -363,7 +363,8 @@ __global__ void __launch_bounds__(256) k_dirac_rhs_res(Geom gin, MrhsArgs a)
     using T = typename ResT<PIN>::T;
     const Geom g = fixed_shape<4>(gin);
     __shared__ float2 lk[4][6][256];  // rows 0 and 1 of U_mu at each site of the block
-    __shared__ T tile[12][256];       // the right-hand side in turn, as stored
+    constexpr int NE = ResT<PIN>::N;
+    __shared__ T tile[NE][256];       // the right-hand side in turn, as stored
     __shared__ float tsc[PIN == 2 ? 256 : 1];
     const int w = xcd_remap(blockIdx.x, gridDim.x);
     const int s = threadIdx.x;
@@ -380,7 +381,7 @@ __global__ void __launch_bounds__(256) k_dirac_rhs_res(Geom gin, MrhsArgs a)
         if constexpr (PIN == 1)
             return nullptr;
         else
-            return (const float *)(elems(r) + RS);
+            return (const float *)(elems(r) + 3 * g.V);
     };
     // the block's fields, once for the tile
 #pragma unroll
@@ -402,17 +403,17 @@ __global__ void __launch_bounds__(256) k_dirac_rhs_res(Geom gin, MrhsArgs a)
             cl.h[b][jj] = {t.x, t.y};
         }
     }
-    // one stored spinor from 12 elements 256 apart (LDS or global) and its scale
+    // one stored spinor from its elements 256 apart (LDS or global) and its scale
     auto get = [&](const T *p, const float *sp, Spinor<float> &x) {
         const float sc = PIN == 2 ? *sp : 1.f;
 #pragma unroll
-        for (int e = 0; e < 12; ++e) {
-            float2 t;
-            if constexpr (PIN == 2)
-                t = __half22float2(p[e * 256]);
-            else
-                t = p[e * 256];
-            x.v[e / 3][e % 3] = {t.x * sc, t.y * sc};
+        for (int e = 0; e < NE; ++e) {
+            if constexpr (PIN == 2) {
+                unpack16(p[e * 256], sc, e, x);
+            } else {
+                const float2 t = p[e * 256];
+                x.v[e / 3][e % 3] = {t.x * sc, t.y * sc};
+            }
         }
     };
     for (int r = 0; r < a.nrhs; ++r) {
@@ -423,9 +424,9 @@ __global__ void __launch_bounds__(256) k_dirac_rhs_res(Geom gin, MrhsArgs a)
         asm volatile("" : "+v"(sl));
         decode(g, ((long long)w << 8) + sl, st);
         {
-            const T *p = elems(r) + elem(g, st.l, s, 12, 0);
+            const T *p = elems(r) + elem(g, st.l, s, NE, 0);
 #pragma unroll
-            for (int e = 0; e < 12; ++e) tile[e][s] = p[e * 256];
+            for (int e = 0; e < NE; ++e) tile[e][s] = p[e * 256];
             if constexpr (PIN == 2) tsc[s] = scales(r)[((long long)st.l << 8) + s];
         }
         wg_barrier();
@@ -450,7 +451,7 @@ __global__ void __launch_bounds__(256) k_dirac_rhs_res(Geom gin, MrhsArgs a)
                         W.m[e / 3][e % 3] = {t.x, t.y};
                     }
                 } else {
-                    get(elems(r) + elem(g, lj, sj, 12, 0), PIN == 2 ? scales(r) + j : nullptr, psi);
+                    get(elems(r) + elem(g, lj, sj, NE, 0), PIN == 2 ? scales(r) + j : nullptr, psi);
 #pragma unroll
                     for (int e = 0; e < 6; ++e) {
                         const float2 t = dir > 0 ? lk[mu][e][s] : a.u[elem(g, lj, sj, 24, mu * 6 + e)];

@@ -40,6 +40,8 @@ struct SpH {  // spinor in pair form: u[c] = (psi0, psi1)[c], l[c] = (psi2, psi3
     PC u[3], l[3];
 };
 
+DD_INL h2 as_h2(unsigned v) { return *reinterpret_cast<const h2 *>(&v); }
+DD_INL unsigned bits_of(h2 a) { return *reinterpret_cast<const unsigned *>(&a); }
 DD_INL h2 lo2(h2 a) { return __low2half2(a); }
 DD_INL h2 hi2(h2 a) { return __high2half2(a); }
 DD_INL h2 swp(h2 a) { return __lowhigh2highlow(a); }
@@ -184,34 +186,55 @@ DD_INL void clov_pairs_ld(const CloverField<2> &Ci, const Geom &g, int l, int s,
 }
 
 // The SAP-ready copy of C_inv holds these coefficients per site, 18 half2 per chiral
-// block: Ad[0..2], Au[0..2] (re, im), Bd[0..2], Bu[0..2] (re, im)
-DD_INL void clov_pairs_put(__half2 *p, const Geom &g, int l, int s, const ClovPair &P)
+// block: Ad[0..2], Au[0..2] (re, im), Bd[0..2], Bu[0..2] (re, im); the 36 of a site as nine
+// 16-byte groups, group k of (block l, site s) at 16-byte index ((9 l + k) bvol + s)
+DD_INL void clov_pairs_flat(const ClovPair &P, h2 (&v)[36])
 {
 #pragma unroll
     for (int blk = 0; blk < 2; ++blk)
 #pragma unroll
         for (int c = 0; c < 3; ++c) {
             const int o = blk * 18;
-            p[elem(g, l, s, 36, o + c)] = P.Ad[blk][c];
-            p[elem(g, l, s, 36, o + 3 + 2 * c)] = P.Au[blk][c].re;
-            p[elem(g, l, s, 36, o + 4 + 2 * c)] = P.Au[blk][c].im;
-            p[elem(g, l, s, 36, o + 9 + c)] = P.Bd[blk][c];
-            p[elem(g, l, s, 36, o + 12 + 2 * c)] = P.Bu[blk][c].re;
-            p[elem(g, l, s, 36, o + 13 + 2 * c)] = P.Bu[blk][c].im;
+            v[o + c] = P.Ad[blk][c];
+            v[o + 3 + 2 * c] = P.Au[blk][c].re;
+            v[o + 4 + 2 * c] = P.Au[blk][c].im;
+            v[o + 9 + c] = P.Bd[blk][c];
+            v[o + 12 + 2 * c] = P.Bu[blk][c].re;
+            v[o + 13 + 2 * c] = P.Bu[blk][c].im;
         }
+}
+
+DD_INL void clov_pairs_put(__half2 *p, const Geom &g, int l, int s, const ClovPair &P)
+{
+    h2 v[36];
+    clov_pairs_flat(P, v);
+    uint4 *q = reinterpret_cast<uint4 *>(p) + elem(g, l, s, 9, 0);
+#pragma unroll
+    for (int k = 0; k < 9; ++k)
+        q[k << g.lbvol] = make_uint4(bits_of(v[4 * k]), bits_of(v[4 * k + 1]), bits_of(v[4 * k + 2]), bits_of(v[4 * k + 3]));
 }
 
 DD_INL void clov_pairs_get(const __half2 *p, const Geom &g, int l, int s, ClovPair &P)
 {
+    h2 v[36];
+    const uint4 *q = reinterpret_cast<const uint4 *>(p) + elem(g, l, s, 9, 0);
+#pragma unroll
+    for (int k = 0; k < 9; ++k) {
+        const uint4 t = ld_stream(&q[k << g.lbvol]);
+        v[4 * k] = as_h2(t.x);
+        v[4 * k + 1] = as_h2(t.y);
+        v[4 * k + 2] = as_h2(t.z);
+        v[4 * k + 3] = as_h2(t.w);
+    }
 #pragma unroll
     for (int blk = 0; blk < 2; ++blk)
 #pragma unroll
         for (int c = 0; c < 3; ++c) {
             const int o = blk * 18;
-            P.Ad[blk][c] = ld_stream(&p[elem(g, l, s, 36, o + c)]);
-            P.Au[blk][c] = PC{ld_stream(&p[elem(g, l, s, 36, o + 3 + 2 * c)]), ld_stream(&p[elem(g, l, s, 36, o + 4 + 2 * c)])};
-            P.Bd[blk][c] = ld_stream(&p[elem(g, l, s, 36, o + 9 + c)]);
-            P.Bu[blk][c] = PC{ld_stream(&p[elem(g, l, s, 36, o + 12 + 2 * c)]), ld_stream(&p[elem(g, l, s, 36, o + 13 + 2 * c)])};
+            P.Ad[blk][c] = v[o + c];
+            P.Au[blk][c] = PC{v[o + 3 + 2 * c], v[o + 4 + 2 * c]};
+            P.Bd[blk][c] = v[o + 9 + c];
+            P.Bu[blk][c] = PC{v[o + 12 + 2 * c], v[o + 13 + 2 * c]};
         }
 }
 
@@ -305,12 +328,12 @@ DD_INL void from_pair(const SpH &p, float sc, Spinor<float> &x)
 // site's scale); returns the scale
 DD_INL float load_pair(const SpinorField<2> &f, const Geom &g, int l, int s, SpH &p)
 {
+    const uint4 *v = f.site(g, l, s);
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
-        const h2 a0 = f.p[elem(g, l, s, 12, c)], a1 = f.p[elem(g, l, s, 12, 3 + c)];
-        const h2 a2 = f.p[elem(g, l, s, 12, 6 + c)], a3 = f.p[elem(g, l, s, 12, 9 + c)];
-        p.u[c] = PC{__lows2half2(a0, a1), __highs2half2(a0, a1)};
-        p.l[c] = PC{__lows2half2(a2, a3), __highs2half2(a2, a3)};
+        const uint4 t = v[c << g.lbvol];
+        p.u[c] = PC{as_h2(t.x), as_h2(t.y)};
+        p.l[c] = PC{as_h2(t.z), as_h2(t.w)};
     }
     return f.scale[((long long)l << g.lbvol) + s];
 }
@@ -332,10 +355,15 @@ DD_INL void scale_pair(const SpH &a, float f, SpH &r)
 // FMAs) and rounded once (link_row2)
 DD_INL void link_rows(const __half2 *u16, const Geom &g, int l, int s, int mu, h2 (&U)[3][3])
 {
+    const uint2 *v = link16_site(u16, g, l, s, mu);
+    uint2 t[3];
 #pragma unroll
-    for (int a = 0; a < 2; ++a)
+    for (int k = 0; k < 3; ++k) t[k] = v[k << g.lbvol];
 #pragma unroll
-        for (int b = 0; b < 3; ++b) U[a][b] = u16[elem(g, l, s, 24, mu * 6 + a * 3 + b)];
+    for (int k = 0; k < 3; ++k) {
+        U[(2 * k) / 3][(2 * k) % 3] = as_h2(t[k].x);
+        U[(2 * k + 1) / 3][(2 * k + 1) % 3] = as_h2(t[k].y);
+    }
 }
 
 DD_INL void link_row2(h2 (&U)[3][3])
@@ -528,20 +556,20 @@ DD_INL void face_out(const Geom &g, int l, int kk, int p, int P, const uint4 *xs
     } else {
         proj_pair(MU, +1, xp, k);
     }
-    h2 *dst = ft + (long long)l * 6 * P + p;
+    uint2 *dst = reinterpret_cast<uint2 *>(ft) + (long long)l * 3 * P + p;
 #pragma unroll
-    for (int c = 0; c < 3; ++c) {
-        dst[(2 * c) * P] = k[c].re;
-        dst[(2 * c + 1) * P] = k[c].im;
-    }
+    for (int c = 0; c < 3; ++c) dst[c * P] = make_uint2(bits_of(k[c].re), bits_of(k[c].im));
 }
 
 // the face term at slot `slot` of block l and the scale of that block
 DD_INL float face_in(const h2 *ft, const float *fs, int l, int slot, int P, PC (&k)[3])
 {
-    const h2 *src = ft + (long long)l * 6 * P + slot;
+    const uint2 *src = reinterpret_cast<const uint2 *>(ft) + (long long)l * 3 * P + slot;
 #pragma unroll
-    for (int c = 0; c < 3; ++c) k[c] = PC{src[(2 * c) * P], src[(2 * c + 1) * P]};
+    for (int c = 0; c < 3; ++c) {
+        const uint2 t = src[c * P];
+        k[c] = PC{as_h2(t.x), as_h2(t.y)};
+    }
     return fs[l];
 }
 
@@ -786,7 +814,7 @@ DD_INL void sap_half_pk_body(Geom gin, int w, int colour, int flags, SpinorField
 }
 
 template <int B>
-__global__ void __launch_bounds__(256) k_sap_half_pk(Geom gin, int colour, int flags, SpinorField<2> bsrc,
+__global__ void __launch_bounds__(256, B == 0 ? 2 : 1) k_sap_half_pk(Geom gin, int colour, int flags, SpinorField<2> bsrc,
                                                      SpinorField<2> sw, SpinorField<2> xw, const __half2 *u16,
                                                      const __half2 *cpsap, Phase4 ph, float kappa, int n_jac, h2 *ft,
                                                      SapRhs rhs)
@@ -810,7 +838,7 @@ __global__ void __launch_bounds__(256) k_sap_half_pk(Geom gin, int colour, int f
 // value in the kernel arguments, so the fields' pointers are known to be global ones (from a
 // table in device memory every access would be a flat one).
 template <int B>
-__global__ void __launch_bounds__(256) k_sap_half_pk_multi(SapLatTab t, int colour, int flags)
+__global__ void __launch_bounds__(256, B == 0 ? 2 : 1) k_sap_half_pk_multi(SapLatTab t, int colour, int flags)
 {
     const int w = xcd_remap(blockIdx.x, gridDim.x);
     int k = 0;
