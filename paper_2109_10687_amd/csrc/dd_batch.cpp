@@ -54,7 +54,6 @@ dd_status reduce_to(dd_ctx *c, dd::BlasArgs a, int nv, int off)
 
 dd_status fetch_red(dd_ctx *c, int n, double *out)
 {
-    HIPCK(c, hipMemcpyAsync(c->red_host, c->red, n * sizeof(double), hipMemcpyDeviceToHost, c->stream));
     HIPCK(c, hipStreamSynchronize(c->stream));
     for (int k = 0; k < n; ++k) out[k] = c->red_host[k];
     return DD_OK;
@@ -147,28 +146,47 @@ dd_status k_dirac_mrhs(dd_ctx *c, void *out, const void *in, int n, int pin)
 // BK_Y (flexible accumulation as in the single right-hand-side solver).
 dd_status solve_batch32(dd_ctx *c, int n, bool sap, std::vector<BRhs> &R, int maxiter)
 {
-    const size_t f32 = spinor_bytes(c->g, DD_F32);
     dd_status st;
-    HIPCK(c, hipMemsetAsync(c->bk[BK_Y], 0, n * f32, c->stream));
-    for (int r = 0; r < n; ++r)
-        if ((st = reduce_to(c, mkb(dd::BLAS_NORM2, {bf(c, BK_SRC, r)}, {1}), 1, r)) != DD_OK) return st;
     double red[3 * BATCH_MAX];
-    if ((st = fetch_red(c, n, red)) != DD_OK) return st;
+    // one vector kernel on the right-hand sides rs (arguments from mk(r)), its nv sums to red[3 r ..]
+    // once fetched: one table launch, or one launch each for the kinds without a table form (M = I)
+    auto vec = [&](int kind, const std::vector<int> &rs, const std::function<dd::BlasArgs(int)> &mk, int nv) -> dd_status {
+        if (!sap && kind != dd::BLAS_START && kind != dd::BLAS_DOT && kind != dd::BLAS_DOT_NORM) {
+            dd_status s2;
+            for (int r : rs)
+                if ((s2 = nv > 0 ? reduce_to(c, mk(r), nv, 3 * r) : blas(c, mk(r))) != DD_OK) return s2;
+            return DD_OK;
+        }
+        std::vector<VecJob> jobs;
+        for (int r : rs) jobs.push_back({c, mk(r), r});
+        HIPCK(c, vec_table(c, c->stream, kind, jobs, nv, c->red));
+        return DD_OK;
+    };
+    auto active = [&]() {
+        std::vector<int> rs;
+        for (int r = 0; r < n; ++r)
+            if (R[r].active) rs.push_back(r);
+        return rs;
+    };
+    std::vector<int> all(n);
+    for (int r = 0; r < n; ++r) all[r] = r;
+    if ((st = vec(dd::BLAS_START, all, [&](int r) {
+             return mkb(dd::BLAS_START, {bf(c, BK_SRC, r), bf(c, BK_R, r), bf(c, BK_P, r), bf(c, BK_RT, r), bf(c, BK_P16, r),
+                                         bf(c, BK_Y, r)}, {1, 1, 1, 1, 2, 1});
+         }, 1)) != DD_OK)
+        return st;
+    if ((st = fetch_red(c, 3 * n, red)) != DD_OK) return st;
     int nact = 0;
     for (int r = 0; r < n; ++r) {
         BRhs &b = R[r];
         b.o = SolveOut{};
-        b.bn2 = b.rn2 = red[r];
-        b.rho0 = red[r];
+        b.bn2 = b.rn2 = red[3 * r];
+        b.rho0 = red[3 * r];
         b.st = DD_OK;
         b.stall = Stall{c->prm.stall_window};
-        if (!is_fin(red[r])) return fail(c, DD_ERR_NONFINITE, "inner source holds NaN or Inf");
-        b.active = red[r] > 0.0;
+        if (!is_fin(b.bn2)) return fail(c, DD_ERR_NONFINITE, "inner source holds NaN or Inf");
+        b.active = b.bn2 > 0.0;
         nact += b.active;
-        if (!b.active) continue;
-        for (int k : {BK_R, BK_P, BK_RT})
-            if ((st = copy(c, bf(c, k, r), 1, bf(c, BK_SRC, r), 1)) != DD_OK) return st;
-        if (sap && (st = copy(c, bf(c, BK_P16, r), 2, bf(c, BK_SRC, r), 1)) != DD_OK) return st;
     }
     const int mp = sap ? BK_MP16 : BK_P, mr = sap ? BK_MR16 : BK_R;
     // M = the FP16-storage SAP of each right-hand side (as in the single right-hand-side
@@ -200,37 +218,35 @@ dd_status solve_batch32(dd_ctx *c, int n, bool sap, std::vector<BRhs> &R, int ma
     for (int it = 0; it < maxiter && nact > 0; ++it) {
         if ((st = precond(BK_P16, BK_MP16)) != DD_OK) return st;
         if ((st = k_dirac_mrhs(c, c->bk[BK_Q], c->bk[mp], n, sap ? DD_F16 : DD_F32)) != DD_OK) return st;
-        for (int r = 0; r < n; ++r)
-            if (R[r].active &&
-                (st = reduce_to(c, mkb(dd::BLAS_DOT, {bf(c, BK_RT, r), bf(c, BK_Q, r)}, {1, 1}), 2, 2 * r)) != DD_OK)
-                return st;
-        if ((st = fetch_red(c, 2 * n, red)) != DD_OK) return st;
+        if ((st = vec(dd::BLAS_DOT, active(), [&](int r) {
+                 return mkb(dd::BLAS_DOT, {bf(c, BK_RT, r), bf(c, BK_Q, r)}, {1, 1});
+             }, 2)) != DD_OK)
+            return st;
+        if ((st = fetch_red(c, 3 * n, red)) != DD_OK) return st;
         std::vector<cplx> alpha(n);
         for (int r = 0; r < n; ++r) {
             BRhs &b = R[r];
             if (!b.active) continue;
             b.o.iters = it + 1;
-            cplx rq(red[2 * r], red[2 * r + 1]);
+            cplx rq(red[3 * r], red[3 * r + 1]);
             if (rq == 0.0 || !is_fin(rq)) {
                 stop(b, DD_BREAKDOWN, rq == 0.0 ? 1 : 4);
                 continue;
             }
             alpha[r] = b.rho0 / rq;
-            if (sap)
-                st = reduce_to(c, mkb(dd::BLAS_UPDATE1_H, {bf(c, BK_R, r), bf(c, BK_Q, r), bf(c, BK_R16, r)}, {1, 1, 2},
-                                      {alpha[r].real(), alpha[r].imag()}),
-                               1, r);
-            else
-                st = reduce_to(c, mkb(dd::BLAS_UPDATE1, {bf(c, BK_Y, r), bf(c, mp, r), bf(c, BK_R, r), bf(c, BK_Q, r)},
-                                      {1, 1, 1}, {alpha[r].real(), alpha[r].imag()}),
-                               1, r);
-            if (st != DD_OK) return st;
         }
-        if ((st = fetch_red(c, n, red)) != DD_OK) return st;
+        if ((st = vec(dd::BLAS_UPDATE1_H, active(), [&](int r) {
+                 return sap ? mkb(dd::BLAS_UPDATE1_H, {bf(c, BK_R, r), bf(c, BK_Q, r), bf(c, BK_R16, r)}, {1, 1, 2},
+                                  {alpha[r].real(), alpha[r].imag()})
+                            : mkb(dd::BLAS_UPDATE1, {bf(c, BK_Y, r), bf(c, mp, r), bf(c, BK_R, r), bf(c, BK_Q, r)},
+                                  {1, 1, 1}, {alpha[r].real(), alpha[r].imag()});
+             }, 1)) != DD_OK)
+            return st;
+        if ((st = fetch_red(c, 3 * n, red)) != DD_OK) return st;
         for (int r = 0; r < n; ++r) {
             BRhs &b = R[r];
             if (!b.active) continue;
-            b.rn2 = red[r];
+            b.rn2 = red[3 * r];
             b.o.relres = std::sqrt(b.rn2 / b.bn2);
             if (b.o.relres < b.tol) {
                 if ((st = settle_y(r, alpha[r])) != DD_OK) return st;
@@ -240,10 +256,10 @@ dd_status solve_batch32(dd_ctx *c, int n, bool sap, std::vector<BRhs> &R, int ma
         if (nact == 0) break;
         if ((st = precond(BK_R16, BK_MR16)) != DD_OK) return st;
         if ((st = k_dirac_mrhs(c, c->bk[BK_T], c->bk[mr], n, sap ? DD_F16 : DD_F32)) != DD_OK) return st;
-        for (int r = 0; r < n; ++r)
-            if (R[r].active &&
-                (st = reduce_to(c, mkb(dd::BLAS_DOT_NORM, {bf(c, BK_T, r), bf(c, BK_R, r)}, {1, 1}), 3, 3 * r)) != DD_OK)
-                return st;
+        if ((st = vec(dd::BLAS_DOT_NORM, active(), [&](int r) {
+                 return mkb(dd::BLAS_DOT_NORM, {bf(c, BK_T, r), bf(c, BK_R, r)}, {1, 1});
+             }, 3)) != DD_OK)
+            return st;
         if ((st = fetch_red(c, 3 * n, red)) != DD_OK) return st;
         std::vector<cplx> omega(n);
         for (int r = 0; r < n; ++r) {
@@ -256,21 +272,20 @@ dd_status solve_batch32(dd_ctx *c, int n, bool sap, std::vector<BRhs> &R, int ma
                 continue;
             }
             omega[r] = cplx(d[0], d[1]) / d[2];
-            if (sap)
-                st = reduce_to(c, mkb(dd::BLAS_UPDATE2_MM,
-                                      {bf(c, BK_Y, r), bf(c, BK_MP16, r), bf(c, BK_MR16, r), bf(c, BK_R, r),
-                                       bf(c, BK_T, r), bf(c, BK_RT, r)},
-                                      {1, 2, 2, 1, 1, 1},
-                                      {alpha[r].real(), alpha[r].imag(), omega[r].real(), omega[r].imag()}),
-                               3, 3 * r);
-            else
-                st = reduce_to(c, mkb(dd::BLAS_UPDATE2,
-                                      {bf(c, BK_Y, r), bf(c, mr, r), bf(c, BK_R, r), bf(c, BK_T, r), bf(c, BK_RT, r)},
-                                      {1, 1, 1}, {omega[r].real(), omega[r].imag()}),
-                               3, 3 * r);
-            if (st != DD_OK) return st;
         }
+        if ((st = vec(dd::BLAS_UPDATE2_MM, active(), [&](int r) {
+                 return sap ? mkb(dd::BLAS_UPDATE2_MM,
+                                  {bf(c, BK_Y, r), bf(c, BK_MP16, r), bf(c, BK_MR16, r), bf(c, BK_R, r), bf(c, BK_T, r),
+                                   bf(c, BK_RT, r)},
+                                  {1, 2, 2, 1, 1, 1},
+                                  {alpha[r].real(), alpha[r].imag(), omega[r].real(), omega[r].imag()})
+                            : mkb(dd::BLAS_UPDATE2,
+                                  {bf(c, BK_Y, r), bf(c, mr, r), bf(c, BK_R, r), bf(c, BK_T, r), bf(c, BK_RT, r)},
+                                  {1, 1, 1}, {omega[r].real(), omega[r].imag()});
+             }, 3)) != DD_OK)
+            return st;
         if ((st = fetch_red(c, 3 * n, red)) != DD_OK) return st;
+        std::vector<cplx> beta_r(n);
         for (int r = 0; r < n; ++r) {
             BRhs &b = R[r];
             if (!b.active) continue;
@@ -296,14 +311,16 @@ dd_status solve_batch32(dd_ctx *c, int n, bool sap, std::vector<BRhs> &R, int ma
                 continue;
             }
             b.rho0 = rho;
-            if (sap)
-                st = blas(c, mkb(dd::BLAS_PUPDATE_H, {bf(c, BK_P, r), bf(c, BK_R, r), bf(c, BK_Q, r), bf(c, BK_P16, r)},
-                                 {1, 1, 1, 2}, {beta.real(), beta.imag(), omega[r].real(), omega[r].imag()}));
-            else
-                st = blas(c, mkb(dd::BLAS_PUPDATE, {bf(c, BK_P, r), bf(c, BK_R, r), bf(c, BK_Q, r)}, {1, 1, 1},
-                                 {beta.real(), beta.imag(), omega[r].real(), omega[r].imag()}));
-            if (st != DD_OK) return st;
+            beta_r[r] = beta;
         }
+        if ((st = vec(dd::BLAS_PUPDATE_H, active(), [&](int r) {
+                 const std::initializer_list<double> cf = {beta_r[r].real(), beta_r[r].imag(), omega[r].real(),
+                                                           omega[r].imag()};
+                 return sap ? mkb(dd::BLAS_PUPDATE_H, {bf(c, BK_P, r), bf(c, BK_R, r), bf(c, BK_Q, r), bf(c, BK_P16, r)},
+                                  {1, 1, 1, 2}, cf)
+                            : mkb(dd::BLAS_PUPDATE, {bf(c, BK_P, r), bf(c, BK_R, r), bf(c, BK_Q, r)}, {1, 1, 1}, cf);
+             }, 0)) != DD_OK)
+            return st;
         if (c->verbose && (it + 1) % 100 == 0) {
             std::fprintf(stderr, "[ddsolve] batched inner iteration %d: %d right-hand sides still running\n", it + 1, nact);
             std::fflush(stderr);
@@ -321,13 +338,16 @@ dd_status solve_batch32(dd_ctx *c, int n, bool sap, std::vector<BRhs> &R, int ma
 dd_status residual64_batch(dd_ctx *c, int n, double *rn2)
 {
     dd_status st;
+    std::vector<VecJob> jobs;
     for (int r = 0; r < n; ++r) {
         if ((st = k_dirac(c, bf(c, BK_T64, r), bf(c, BK_X64, r), 0, 0, 0, 0)) != DD_OK) return st;
-        if ((st = reduce_to(c, mkb(dd::BLAS_SUB_NORM, {bf(c, BK_R64, r), bf(c, BK_B64, r), bf(c, BK_T64, r)}, {0, 0, 0}), 1,
-                            r)) != DD_OK)
-            return st;
+        jobs.push_back({c, mkb(dd::BLAS_SUB_NORM, {bf(c, BK_R64, r), bf(c, BK_B64, r), bf(c, BK_T64, r)}, {0, 0, 0}), r});
     }
-    return fetch_red(c, n, rn2);
+    HIPCK(c, vec_table(c, c->stream, dd::BLAS_SUB_NORM, jobs, 1, c->red));
+    double red[3 * BATCH_MAX];
+    if ((st = fetch_red(c, 3 * n, red)) != DD_OK) return st;
+    for (int r = 0; r < n; ++r) rn2[r] = red[3 * r];
+    return DD_OK;
 }
 
 
@@ -377,71 +397,43 @@ dd_status multi_launch(dd_multi *m, int t, int pin)
     return DD_OK;
 }
 
-// a reducing vector kernel on lattice k whose nv sums go to that lattice's slots of the
-// multi-lattice result array
-static dd_status multi_reduce(dd_multi *m, int k, dd::BlasArgs a, int nv)
-{
-    dd_ctx *c = m->L[k];
-    dd_status st = blas(c, a);
-    if (st != DD_OK) return lat_fail(m, k, st);
-    MHIPCK(m, dd::launch_finalize(m->stream, c->partials, dd::blas_grid(c->g), nv, m->red_all + 3 * k));
-    return DD_OK;
-}
-
-// bring the first nv results of every lattice's last multi_reduce or multi_blas to the host (one copy,
-// one sync)
+// wait for the first nv results of every lattice's last multi_blas
 dd_status multi_fetch(dd_multi *m, int nv, std::vector<std::array<double, 3>> &out)
 {
     const size_t n = m->L.size();
-    MHIPCK(m, hipMemcpyAsync(m->red_all_host, m->red_all, 3 * n * sizeof(double), hipMemcpyDeviceToHost, m->stream));
     MHIPCK(m, hipStreamSynchronize(m->stream));
     for (size_t k = 0; k < n; ++k)
         for (int v = 0; v < nv; ++v) out[k][v] = m->red_all_host[3 * k + v];
     return DD_OK;
 }
 
-// one vector kernel of the lockstep solver on the lattices ks (fields and coefficients from
-// mk(k)), in table launches of up to MULTI_BLAS_MAX lattices whose partials fit the first
-// lattice's partials array; with nv > 0 each lattice's nv sums are finalised into its slots
-// of the result array (multi_fetch brings them over).  Timed on the first lattice's timers.
+// one vector kernel of the lockstep solver on the lattices ks (fields and coefficients from mk(k)); with
+// nv > 0 each lattice's nv sums go to its slots of the result array (multi_fetch waits for them)
 static dd_status multi_blas(dd_multi *m, int kind, const std::vector<int> &ks,
                             const std::function<dd::BlasArgs(int)> &mk, int nv)
 {
-    dd_ctx *c0 = m->L[0];
-    size_t i = 0;
-    while (i < ks.size()) {
-        dd::MultiBlasTab t{};
-        int slot[dd::MULTI_BLAS_MAX];
-        int total = 0;
-        long long poff = 0;
-        double bytes = 0, flops = 0;
-        for (; i < ks.size() && t.n < dd::MULTI_BLAS_MAX; ++i) {
-            dd_ctx *c = m->L[ks[i]];
-            const int nwg = dd::blas_grid(c->g);
-            const long long need = (long long)nwg * (nv > 0 ? nv : 1);
-            if (t.n > 0 && poff + need > dd::MAX_PARTIALS) break;
-            const dd::BlasArgs a = mk(ks[i]);
-            dd::MultiBlasLat &e = t.e[t.n];
-            e.g = c->g;
-            for (int j = 0; j < 6; ++j) e.v[j] = a.v[j];
-            for (int j = 0; j < 4; ++j) e.c[j] = a.c[j];
-            e.item0 = total;
-            e.nwg = nwg;
-            e.poff = poff;
-            slot[t.n] = ks[i];
-            total += nwg;
-            poff += need;
-            ++t.n;
-            double rw, fl;
-            blas_cost(a, rw, fl);
-            bytes += rw * (double)c->g.V;
-            flops += fl * (double)c->g.V;
-        }
-        hipError_t e = timed(c0, DD_KT_BLAS, bytes, flops,
-                             [&] { return dd::launch_blas_multi(m->stream, kind, t, total, c0->partials); });
-        if (e != hipSuccess) return mfail(m, DD_ERR_HIP, std::string("multi-lattice vector kernel: ") + hipGetErrorString(e));
-        if (nv > 0) MHIPCK(m, dd::launch_finalize_multi(m->stream, t, slot, c0->partials, nv, m->red_all));
+    std::vector<VecJob> jobs;
+    for (int k : ks) jobs.push_back({m->L[k], mk(k), k});
+    MHIPCK(m, vec_table(m->L[0], m->stream, kind, jobs, nv, m->red_all));
+    return DD_OK;
+}
+
+// r = b - D x of the lattices ks (FP64), |r|^2 into rn2
+static dd_status multi_residual64(dd_multi *m, const std::vector<int> &ks, std::vector<double> &rn2)
+{
+    dd_status st;
+    for (int k : ks) {
+        dd_ctx *c = m->L[k];
+        if ((st = k_dirac(c, c->f64[3], c->f64[1], 0, 0, 0, 0)) != DD_OK) return lat_fail(m, k, st);
     }
+    if ((st = multi_blas(m, dd::BLAS_SUB_NORM, ks, [&](int k) {
+             dd_ctx *c = m->L[k];
+             return mkb(dd::BLAS_SUB_NORM, {c->f64[2], c->f64[0], c->f64[3]}, {0, 0, 0});
+         }, 1)) != DD_OK)
+        return st;
+    std::vector<std::array<double, 3>> red(m->L.size());
+    if ((st = multi_fetch(m, 1, red)) != DD_OK) return st;
+    for (int k : ks) rn2[k] = red[k][0];
     return DD_OK;
 }
 
@@ -502,11 +494,12 @@ dd_status solve_multi32(dd_multi *m, std::vector<BRhs> &R, int maxiter)
     };
     int nact = 0;
     std::vector<cplx> alpha(n), omega(n), beta_k(n);
-    for (int k = 0; k < n; ++k) {
-        dd_ctx *c = m->L[k];
-        MHIPCK(m, hipMemsetAsync(F(k, 1), 0, spinor_bytes(c->g, DD_F32), m->stream));
-        if ((st = multi_reduce(m, k, mkb(dd::BLAS_NORM2, {F(k, 0)}, {1}), 1)) != DD_OK) return st;
-    }
+    std::vector<int> all(n);
+    for (int k = 0; k < n; ++k) all[k] = k;
+    if ((st = multi_blas(m, dd::BLAS_START, all, [&](int k) {
+             return mkb(dd::BLAS_START, {F(k, 0), F(k, 2), F(k, 4), F(k, 3), F(k, 10), F(k, 1)}, {1, 1, 1, 1, 2, 1});
+         }, 1)) != DD_OK)
+        return st;
     if ((st = multi_fetch(m, 1, red)) != DD_OK) return st;
     for (int k = 0; k < n; ++k) {
         BRhs &b = R[k];
@@ -518,11 +511,6 @@ dd_status solve_multi32(dd_multi *m, std::vector<BRhs> &R, int maxiter)
         if (!is_fin(red[k][0])) return mfail(m, DD_ERR_NONFINITE, "inner source holds NaN or Inf");
         b.active = red[k][0] > 0.0;
         nact += b.active;
-        if (!b.active) continue;
-        dd_ctx *c = m->L[k];
-        for (int w : {2, 4, 3})
-            if ((st = copy(c, F(k, w), 1, F(k, 0), 1)) != DD_OK) return lat_fail(m, k, st);
-        if ((st = copy(c, F(k, 10), 2, F(k, 0), 1)) != DD_OK) return lat_fail(m, k, st);
     }
     // the FP16 SAP of each lattice reads the FP16 copies of p and r that the fused updates
     // write (as in solve_sap32); y takes alpha Mp + omega Mr in one pass
@@ -748,9 +736,15 @@ dd_status bicgstab_solve_batch(dd_ctx *c, void *x_dev, const void *b_dev, int nr
     for (int r = 0; r < n; ++r) {
         HIPCK(c, dd::launch_pack_spinor(c->g, c->stream, DD_F64, bf(c, BK_B64, r), (const char *)b_dev + r * cb));
         HIPCK(c, dd::launch_pack_spinor(c->g, c->stream, DD_F64, bf(c, BK_X64, r), (const char *)x_dev + r * cb));
-        if ((st = reduce_to(c, mkb(dd::BLAS_NORM2, {bf(c, BK_B64, r)}, {0}), 1, r)) != DD_OK) return st;
     }
-    if ((st = fetch_red(c, n, bn2)) != DD_OK) return st;
+    {
+        std::vector<VecJob> jobs;
+        for (int r = 0; r < n; ++r) jobs.push_back({c, mkb(dd::BLAS_NORM2, {bf(c, BK_B64, r)}, {0}), r});
+        HIPCK(c, vec_table(c, c->stream, dd::BLAS_NORM2, jobs, 1, c->red));
+        double red[3 * BATCH_MAX];
+        if ((st = fetch_red(c, 3 * n, red)) != DD_OK) return st;
+        for (int r = 0; r < n; ++r) bn2[r] = red[3 * r];
+    }
     for (int r = 0; r < n; ++r)
         if (!is_fin(bn2[r])) return fail(c, DD_ERR_NONFINITE, "a source holds NaN or Inf");
     for (int r = 0; r < n; ++r)
@@ -761,6 +755,7 @@ dd_status bicgstab_solve_batch(dd_ctx *c, void *x_dev, const void *b_dev, int nr
     std::vector<int> stall(n, 0);
     std::vector<dd_status> res(n, DD_NOT_CONVERGED);
     for (int r = 0; r < n; ++r) prev[r] = rn2[r];
+    bool back = false;  // a right-hand side's last correction was taken back
     const size_t f32 = spinor_bytes(c->g, DD_F32);
     for (int outer = 0;; ++outer) {
         int running = 0;
@@ -805,6 +800,7 @@ dd_status bicgstab_solve_batch(dd_ctx *c, void *x_dev, const void *b_dev, int nr
                 if ((st = blas(c, mkb(dd::BLAS_AXPBY, {bf(c, BK_Y, r), bf(c, BK_X64, r)}, {1, 0}, {-err[r], 1.0}))) !=
                     DD_OK)
                     return st;
+                back = true;
                 state[r] = 2;
                 res[r] = DD_BREAKDOWN;
                 inf[r].status_detail = is_fin(rn2[r]) ? DETAIL_OUTER_STALL : 4;
@@ -832,8 +828,8 @@ dd_status bicgstab_solve_batch(dd_ctx *c, void *x_dev, const void *b_dev, int nr
             std::fflush(stderr);
         }
     }
-    // true FP64 residuals of the returned solutions
-    if ((st = residual64_batch(c, n, rn2)) != DD_OK) return st;
+    // true FP64 residuals of the returned solutions: those of the last pass, unless one was taken back
+    if (back && (st = residual64_batch(c, n, rn2)) != DD_OK) return st;
     dd_status worst = DD_OK;
     for (int r = 0; r < n; ++r) {
         inf[r].relres_true = bn2[r] > 0 ? std::sqrt(rn2[r] / bn2[r]) : 0.0;
@@ -873,8 +869,8 @@ dd_status dd_multi_create(const dd_params *params, int nlat, void *hip_stream, d
               hipMalloc((void **)&m->desc_dev, 3 * nlat * sizeof(dd::LatDesc)) == hipSuccess &&
               hipHostMalloc((void **)&m->desc_host, 3 * nlat * sizeof(dd::LatDesc), hipHostMallocDefault) == hipSuccess &&
               hipHostMalloc((void **)&m->sap_host, 2 * nlat * sizeof(dd::SapLat), hipHostMallocDefault) == hipSuccess &&
-              hipMalloc((void **)&m->red_all, 3 * nlat * sizeof(double)) == hipSuccess &&
-              hipHostMalloc((void **)&m->red_all_host, 3 * nlat * sizeof(double), hipHostMallocDefault) == hipSuccess;
+              hipHostMalloc((void **)&m->red_all_host, 3 * nlat * sizeof(double), hipHostMallocMapped) == hipSuccess &&
+              hipHostGetDevicePointer((void **)&m->red_all, m->red_all_host, 0) == hipSuccess;
     // the groups of lattices whose SAP half-sweeps share one launch (same block shape and
     // n_sap, packed-FP16 arithmetic)
     int off = 0;
@@ -915,7 +911,6 @@ dd_status dd_multi_destroy(dd_multi *m)
     if (m->desc_dev) (void)hipFree(m->desc_dev);
     if (m->desc_host) (void)hipHostFree(m->desc_host);
     if (m->sap_host) (void)hipHostFree(m->sap_host);
-    if (m->red_all) (void)hipFree(m->red_all);
     if (m->red_all_host) (void)hipHostFree(m->red_all_host);
     delete m;
     return DD_OK;
@@ -1025,12 +1020,25 @@ dd_status bicgstab_solve_multi(dd_multi *m, void *const *x_dev, const void *cons
         dd_ctx *c = m->L[k];
         MHIPCK(m, dd::launch_pack_spinor(c->g, m->stream, DD_F64, c->f64[0], b_dev[k]));
         MHIPCK(m, dd::launch_pack_spinor(c->g, m->stream, DD_F64, c->f64[1], x_dev[k]));
-        if ((st = norm2(c, c->f64[0], 0, &bn2[k])) != DD_OK) return lat_fail(m, k, st);
+    }
+    std::vector<int> all(n);
+    for (int k = 0; k < n; ++k) all[k] = k;
+    if ((st = multi_blas(m, dd::BLAS_NORM2, all, [&](int k) { return mkb(dd::BLAS_NORM2, {m->L[k]->f64[0]}, {0}); }, 1)) !=
+        DD_OK)
+        return st;
+    {
+        std::vector<std::array<double, 3>> red(n);
+        if ((st = multi_fetch(m, 1, red)) != DD_OK) return st;
+        for (int k = 0; k < n; ++k) bn2[k] = red[k][0];
+    }
+    for (int k = 0; k < n; ++k) {
+        dd_ctx *c = m->L[k];
         if (!is_fin(bn2[k])) return mfail(m, DD_ERR_NONFINITE, "a source holds NaN or Inf");
         if (bn2[k] == 0.0) MHIPCK(m, hipMemsetAsync(c->f64[1], 0, spinor_bytes(c->g, DD_F64), m->stream));
-        if ((st = residual64(c, c->f64[2], c->f64[0], c->f64[1], c->f64[3], &rn2[k])) != DD_OK) return lat_fail(m, k, st);
-        prev[k] = rn2[k];
     }
+    if ((st = multi_residual64(m, all, rn2)) != DD_OK) return st;
+    prev = rn2;
+    std::vector<int> back;  // lattices whose last correction was taken back
     for (int outer = 0;; ++outer) {
         int running = 0;
         for (int k = 0; k < n; ++k) {
@@ -1057,6 +1065,7 @@ dd_status bicgstab_solve_multi(dd_multi *m, void *const *x_dev, const void *cons
             R[k].tol = need > c->prm.inner_tol ? (need < 0.1 ? need : 0.1) : c->prm.inner_tol;
         }
         if ((st = solve_multi32(m, R, m->L[0]->prm.inner_maxiter)) != DD_OK) return st;
+        std::vector<int> ks;  // the lattices of this pass
         for (int k = 0; k < n; ++k) {
             if (state[k] != 0) continue;
             dd_ctx *c = m->L[k];
@@ -1064,12 +1073,16 @@ dd_status bicgstab_solve_multi(dd_multi *m, void *const *x_dev, const void *cons
             inf[k].relres_inner_last = R[k].o.relres;
             if ((st = blas(c, mkb(dd::BLAS_AXPBY, {c->f32[1], c->f64[1]}, {1, 0}, {err[k], 1.0}))) != DD_OK)
                 return lat_fail(m, k, st);
-            if ((st = residual64(c, c->f64[2], c->f64[0], c->f64[1], c->f64[3], &rn2[k])) != DD_OK)
-                return lat_fail(m, k, st);
+            ks.push_back(k);
+        }
+        if ((st = multi_residual64(m, ks, rn2)) != DD_OK) return st;
+        for (int k : ks) {
+            dd_ctx *c = m->L[k];
             inf[k].iters_outer = outer + 1;
             if (!is_fin(rn2[k]) || rn2[k] >= prev[k]) {
                 if ((st = blas(c, mkb(dd::BLAS_AXPBY, {c->f32[1], c->f64[1]}, {1, 0}, {-err[k], 1.0}))) != DD_OK)
                     return lat_fail(m, k, st);
+                back.push_back(k);
                 state[k] = 2;
                 res[k] = DD_BREAKDOWN;
                 inf[k].status_detail = is_fin(rn2[k]) ? DETAIL_OUTER_STALL : 4;
@@ -1090,10 +1103,11 @@ dd_status bicgstab_solve_multi(dd_multi *m, void *const *x_dev, const void *cons
             }
         }
     }
+    // true FP64 residuals of the returned solutions: those of the last pass, except where it was taken back
+    if ((st = multi_residual64(m, back, rn2)) != DD_OK) return st;
     dd_status worst = DD_OK;
     for (int k = 0; k < n; ++k) {
         dd_ctx *c = m->L[k];
-        if ((st = residual64(c, c->f64[2], c->f64[0], c->f64[1], c->f64[3], &rn2[k])) != DD_OK) return lat_fail(m, k, st);
         inf[k].relres_true = bn2[k] > 0 ? std::sqrt(rn2[k] / bn2[k]) : 0.0;
         if (res[k] == DD_NOT_CONVERGED && inf[k].relres_true < tol) res[k] = DD_OK;
         if (res[k] > worst) worst = res[k];

@@ -83,8 +83,9 @@ dd_status dd_create(const dd_params *prm, void *hip_stream, dd_ctx **out)
     for (int i = 0; ok && i < N32; ++i) ok = alloc(&c->f32[i], spinor_bytes(g, DD_F32));
     for (int i = 0; ok && i < N16; ++i) ok = alloc(&c->f16[i], spinor_bytes(g, DD_F16));
     ok = ok && alloc((void **)&c->partials, dd::MAX_PARTIALS * sizeof(double)) &&
-         alloc((void **)&c->red, RED_MAX * sizeof(double)) && alloc((void **)&c->flag, 4 * sizeof(int)) &&
-         hipHostMalloc((void **)&c->red_host, RED_MAX * sizeof(double), hipHostMallocDefault) == hipSuccess;
+         alloc((void **)&c->flag, 4 * sizeof(int)) &&
+         hipHostMalloc((void **)&c->red_host, RED_MAX * sizeof(double), hipHostMallocMapped) == hipSuccess &&
+         hipHostGetDevicePointer((void **)&c->red, c->red_host, 0) == hipSuccess;
     if (!ok) {
         (void)hipGetLastError();
         dd_destroy(c);
@@ -103,7 +104,7 @@ dd_status dd_destroy(dd_ctx *c)
     if (!c) return DD_OK;
     (void)hipStreamSynchronize(c->stream);
     void *bufs[] = {c->U64,   c->U32,     c->U16,      c->clov64, c->cinv32, c->cinv16,
-                    c->CPsap, c->faces, c->yforce, c->partials, c->red,    c->flag};
+                    c->CPsap, c->faces, c->yforce, c->partials, c->flag};
     for (void *p : bufs)
         if (p) (void)hipFree(p);
     for (void *p : c->f64)
@@ -262,6 +263,7 @@ static dd_status solve_entry(dd_ctx *c, void *x_dev, const void *b_dev, double t
     if (st != DD_OK) return st;
     if (!is_fin(bn2)) return fail(c, DD_ERR_NONFINITE, "source holds NaN or Inf");
     dd_status res = DD_OK;
+    double rn2_x = -1.0;  // |b - D x|^2 of the x that is returned, if known
     if (mode == DD_SOLVE_F64_PLAIN) {
         HIPCK(c, dd::launch_pack_spinor(c->g, c->stream, DD_F64, x, x_dev, dagger));
         SolveOut o;
@@ -414,13 +416,11 @@ static dd_status solve_entry(dd_ctx *c, void *x_dev, const void *b_dev, double t
         }
         inf.iters_outer = outer;
         inf.precision_level = level;
+        rn2_x = rn2;  // every way out of the loop has the residual of the current x
     }
-    // true FP64 residual of the returned x
-    {
-        double rn2;
-        if ((st = residual64(c, c->f64[2], b, x, c->f64[3], &rn2)) != DD_OK) return st;
-        inf.relres_true = bn2 > 0 ? std::sqrt(rn2 / bn2) : 0.0;
-    }
+    // true FP64 residual of the returned x, where the solver did not leave it
+    if (!(rn2_x >= 0) && (st = residual64(c, c->f64[2], b, x, c->f64[3], &rn2_x)) != DD_OK) return st;
+    inf.relres_true = bn2 > 0 ? std::sqrt(rn2_x / bn2) : 0.0;
     HIPCK(c, dd::launch_unpack_spinor(c->g, c->stream, DD_F64, x_dev, x, dagger));
     HIPCK(c, hipStreamSynchronize(c->stream));
     inf.seconds = std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count();
@@ -493,13 +493,8 @@ static dd_status force_entry(dd_ctx *c, void *out_dev, double *dcsw, const void 
     hipError_t e = timed_launch ? timed(c, DD_KT_FORCE, bytes, flops, [&] { return dd::launch_force(g, c->stream, a); })
                                 : dd::launch_force(g, c->stream, a);
     if (e != hipSuccess) return fail(c, DD_ERR_HIP, std::string("force launch: ") + hipGetErrorString(e));
-    if (dcsw) {
-        HIPCK(c, hipMemcpyAsync(c->red_host, c->red, sizeof(double), hipMemcpyDeviceToHost, c->stream));
-        HIPCK(c, hipStreamSynchronize(c->stream));
-        *dcsw = c->red_host[0];
-    } else {
-        HIPCK(c, hipStreamSynchronize(c->stream));
-    }
+    HIPCK(c, hipStreamSynchronize(c->stream));
+    if (dcsw) *dcsw = c->red_host[0];
     return DD_OK;
 }
 

@@ -229,9 +229,7 @@ __global__ void __launch_bounds__(BLAS_WG, CSW == 2 ? 1 : 2)
             for (int plane = 0; plane < 6; ++plane) plane_y(plane, lam);
         } else {
             int plane = 0;
-#pragma unroll
             for (int mu = 0; mu < 4; ++mu)
-#pragma unroll
                 for (int nu = mu + 1; nu < 4; ++nu, ++plane) {
                     plane_y(plane, lam);
                     Mat3<double> F;

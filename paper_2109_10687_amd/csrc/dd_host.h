@@ -78,6 +78,8 @@ struct dd_ctx {
     // inner solve never touches, the rest are allocated by the first such solve (fv_own, fz_own)
     void *fv[dd::GCR_MAX_NKV + 1] = {}, *fz[dd::GCR_MAX_NKV] = {};
     void *fv_own[dd::GCR_MAX_NKV + 1] = {}, *fz_own[dd::GCR_MAX_NKV] = {};
+    // per-workgroup partial sums, and the finished sums: mapped host memory (red: its device address), so
+    // a reduction's results are there when its stream is
     double *partials = nullptr, *red = nullptr, *red_host = nullptr;
     int *flag = nullptr;
     // kernel timing
@@ -110,7 +112,7 @@ struct dd_multi {
     };
     dd::SapLat *sap_host = nullptr;  // the multi-lattice half-sweep tables (kernel arguments)
     std::vector<SapGroup> sap_groups;
-    double *red_all = nullptr, *red_all_host = nullptr;  // three reduction results per lattice
+    double *red_all = nullptr, *red_all_host = nullptr;  // three reduction results per lattice (mapped host memory)
 };
 
 namespace ddh {
@@ -293,6 +295,15 @@ void *bf(dd_ctx *c, int k, int r);
 // run a reducing vector kernel on right-hand side r and leave its nv sums at red[off..]
 dd_status reduce_to(dd_ctx *c, dd::BlasArgs a, int nv, int off);
 dd_status fetch_red(dd_ctx *c, int n, double *out);
+// one vector kernel on several entries (lattices, or right-hand sides of one), in table launches of up
+// to MULTI_BLAS_MAX entries whose partials fit c0's; with nv > 0 the nv sums of an entry go to
+// out[3 slot ..].  Timed on c0's timers.
+struct VecJob {
+    const dd_ctx *c;
+    dd::BlasArgs a;
+    int slot;
+};
+hipError_t vec_table(dd_ctx *c0, hipStream_t st, int kind, const std::vector<VecJob> &jobs, int nv, double *out);
 // out = A in for n batched fields at input precision pin (DD_F32 or DD_F16), FP32 output,
 // in tiles of up to 12
 dd_status k_dirac_mrhs(dd_ctx *c, void *out, const void *in, int n, int pin);

@@ -916,22 +916,38 @@ template <> struct Elem<2> {  // read only: the scale belongs to the whole site
     }
 };
 
-// sum the per-workgroup partials in a fixed order: out[k] = sum_w partials[w*nv + k]
+// Sum nv values of nwg workgroups' partials (p[w nv + k]) in a fixed order into out[k]: every thread
+// adds its workgroups w = tid, tid + 256, ..., the wavefronts add by shuffles and the four of them
+// in order, up to three values at a time (one pass and one barrier for every reduction of BiCGStab,
+// where a pass with an LDS tree of nine barriers per value took 6.4 us on 16^4).  out may be host
+// memory mapped for the device: the results then need no copy of their own.
+DD_INL void finalize_sum(const double *p, int nwg, int nv, double *out)
+{
+    __shared__ double sh[4][3];
+    for (int k0 = 0; k0 < nv; k0 += 3) {
+        const int m = nv - k0 < 3 ? nv - k0 : 3;
+        double t[3] = {0, 0, 0};
+        for (int w = threadIdx.x; w < nwg; w += 256)
+#pragma unroll
+            for (int k = 0; k < 3; ++k)
+                if (k < m) t[k] += p[(long long)w * nv + k0 + k];
+#pragma unroll
+        for (int k = 0; k < 3; ++k)
+#pragma unroll
+            for (int off = 32; off >= 1; off >>= 1) t[k] += __shfl_xor(t[k], off, 64);
+        if (k0 > 0) wg_barrier();  // the last values are read
+        if ((threadIdx.x & 63) == 0)
+#pragma unroll
+            for (int k = 0; k < 3; ++k) sh[threadIdx.x >> 6][k] = t[k];
+        wg_barrier();
+        if ((int)threadIdx.x < m)
+            out[k0 + threadIdx.x] = ((sh[0][threadIdx.x] + sh[1][threadIdx.x]) + sh[2][threadIdx.x]) + sh[3][threadIdx.x];
+    }
+}
+
 __global__ void __launch_bounds__(256) k_finalize(const double *partials, int nwg, int nv, double *out)
 {
-    __shared__ double sh[256];
-    for (int k = 0; k < nv; ++k) {
-        double t = 0;
-        for (int w = threadIdx.x; w < nwg; w += 256) t += partials[(long long)w * nv + k];
-        sh[threadIdx.x] = t;
-        wg_barrier();
-        for (int h = 128; h >= 1; h >>= 1) {
-            if ((int)threadIdx.x < h) sh[threadIdx.x] += sh[threadIdx.x + h];
-            wg_barrier();
-        }
-        if (threadIdx.x == 0) out[k] = sh[0];
-        wg_barrier();
-    }
+    finalize_sum(partials, nwg, nv, out);
 }
 
 #define GRID_STRIDE(o, N) for (long long o = (long long)blockIdx.x * BLAS_WG + threadIdx.x; o < (N); o += (long long)gridDim.x * BLAS_WG)
@@ -961,12 +977,17 @@ __global__ void __launch_bounds__(BLAS_WG) k_dot(Geom g, SpinorField<PA> a, Spin
     dot_body<PA, PB, NV>(g, a, b, partials, blockIdx.x, gridDim.x);
 }
 
+template <int PA> DD_INL void norm2_body(const Geom &g, SpinorField<PA> a, double *partials, int wid, int nwg)
+{
+    double v[1] = {0};
+    GRID_STRIDE_W(o, 12 * g.V) v[0] += norm2(Elem<PA>::get(a, g, o));
+    wg_reduce_store_at<1>(v, partials, wid);
+}
+
 template <int PA>
 __global__ void __launch_bounds__(BLAS_WG) k_norm2(Geom g, SpinorField<PA> a, double *partials)
 {
-    double v[1] = {0};
-    GRID_STRIDE(o, 12 * g.V) v[0] += norm2(Elem<PA>::get(a, g, o));
-    wg_reduce_store<1>(v, partials);
+    norm2_body<PA>(g, a, partials, blockIdx.x, gridDim.x);
 }
 
 // x += alpha y ; r -= alpha q ; partial |r|^2
@@ -1132,7 +1153,62 @@ __global__ void __launch_bounds__(BLAS_WG) k_pupdate_h(Geom g, SpinorField<1> p,
     pupdate_h_body(g, p, r, q, p16, bre, bim, ore, oim, blockIdx.x, gridDim.x);
 }
 
-// The vector kernels of the lockstep multi-lattice solver, one launch for the lattices of a
+// The start of an FP32 BiCGStab for the source src: r = p = rt = src, p16 = src where p16 is given
+// (FP16 storage), y = 0, partial |src|^2 -- one pass over the source
+DD_INL void start_body(const Geom &g, SpinorField<1> src, SpinorField<1> r, SpinorField<1> p, SpinorField<1> rt,
+                       SpinorField<2> p16, SpinorField<1> y, double *partials, int wid, int nwg)
+{
+    double v[1] = {0};
+    Spinor<float> none;
+    zero(none);
+    SITE_STRIDE_W(i)
+    {
+        const int l = (int)(i >> g.lbvol), s = (int)(i & (g.bvol - 1));
+        Spinor<float> x;
+        src.load(g, l, s, x);
+        r.store(g, l, s, x);
+        p.store(g, l, s, x);
+        rt.store(g, l, s, x);
+        if (p16.p) p16.store(g, l, s, x);
+        y.store(g, l, s, none);
+#pragma unroll
+        for (int a = 0; a < 4; ++a)
+#pragma unroll
+            for (int c = 0; c < 3; ++c) v[0] += norm2(cx<double>{(double)x.v[a][c].re, (double)x.v[a][c].im});
+    }
+    wg_reduce_store_at<1>(v, partials, wid);
+}
+
+__global__ void __launch_bounds__(BLAS_WG) k_start(Geom g, SpinorField<1> src, SpinorField<1> r, SpinorField<1> p,
+                                                   SpinorField<1> rt, SpinorField<2> p16, SpinorField<1> y,
+                                                   double *partials)
+{
+    start_body(g, src, r, p, rt, p16, y, partials, blockIdx.x, gridDim.x);
+}
+
+// r = b - a ; partial |r|^2
+template <int P>
+DD_INL void sub_norm_body(const Geom &g, SpinorField<P> r, SpinorField<P> b, SpinorField<P> a, double *partials, int wid,
+                          int nwg)
+{
+    double v[1] = {0};
+    GRID_STRIDE_W(o, 12 * g.V)
+    {
+        cx<double> d = Elem<P>::get(b, g, o) - Elem<P>::get(a, g, o);
+        Elem<P>::put(r, g, o, d);
+        v[0] += norm2(d);
+    }
+    wg_reduce_store_at<1>(v, partials, wid);
+}
+
+template <int P>
+__global__ void __launch_bounds__(BLAS_WG) k_sub_norm(Geom g, SpinorField<P> r, SpinorField<P> b, SpinorField<P> a,
+                                                      double *partials)
+{
+    sub_norm_body<P>(g, r, b, a, partials, blockIdx.x, gridDim.x);
+}
+
+// The vector kernels of the lockstep solvers (several lattices, several right-hand sides), one launch for the lattices of a
 // table (each with its own fields, coefficients, workgroups and partials)
 template <int KIND>
 __global__ void __launch_bounds__(BLAS_WG) k_blas_multi(MultiBlasTab t, double *partials)
@@ -1143,11 +1219,18 @@ __global__ void __launch_bounds__(BLAS_WG) k_blas_multi(MultiBlasTab t, double *
     const Geom &g = L.g;
     const int wid = (int)blockIdx.x - L.item0, nwg = L.nwg;
     double *pp = partials + L.poff;
+    auto f0 = [&](int i) { return SpinorField<0>{(double2 *)L.v[i]}; };
     auto f1 = [&](int i) { return SpinorField<1>{(float2 *)L.v[i]}; };
     auto f2 = [&](int i) {
         return SpinorField<2>{(__half2 *)L.v[i], (float *)((char *)L.v[i] + 12 * g.V * sizeof(__half2))};
     };
-    if constexpr (KIND == BLAS_DOT)
+    if constexpr (KIND == BLAS_NORM2)
+        norm2_body<0>(g, f0(0), pp, wid, nwg);
+    else if constexpr (KIND == BLAS_SUB_NORM)
+        sub_norm_body<0>(g, f0(0), f0(1), f0(2), pp, wid, nwg);
+    else if constexpr (KIND == BLAS_START)
+        start_body(g, f1(0), f1(1), f1(2), f1(3), f2(4), f1(5), pp, wid, nwg);
+    else if constexpr (KIND == BLAS_DOT)
         dot_body<1, 1, 2>(g, f1(0), f1(1), pp, wid, nwg);
     else if constexpr (KIND == BLAS_DOT_NORM)
         dot_body<1, 1, 3>(g, f1(0), f1(1), pp, wid, nwg);
@@ -1168,21 +1251,8 @@ struct MultiFin {
 
 __global__ void __launch_bounds__(256) k_finalize_multi(MultiFin f, const double *partials, int nv, double *out)
 {
-    __shared__ double sh[256];
     const int k = blockIdx.x;
-    const double *pp = partials + f.poff[k];
-    for (int q = 0; q < nv; ++q) {
-        double t = 0;
-        for (int w = threadIdx.x; w < f.nwg[k]; w += 256) t += pp[(long long)w * nv + q];
-        sh[threadIdx.x] = t;
-        wg_barrier();
-        for (int h = 128; h >= 1; h >>= 1) {
-            if ((int)threadIdx.x < h) sh[threadIdx.x] += sh[threadIdx.x + h];
-            wg_barrier();
-        }
-        if (threadIdx.x == 0) out[3 * f.slot[k] + q] = sh[0];
-        wg_barrier();
-    }
+    finalize_sum(partials + f.poff[k], f.nwg[k], nv, out + 3 * f.slot[k]);
 }
 
 // x += alpha y (complex alpha)
@@ -1209,21 +1279,6 @@ __global__ void __launch_bounds__(BLAS_WG) k_axpby(Geom g, double alpha, SpinorF
         cx<double> yv = beta == 0.0 ? cx<double>{0, 0} : Elem<PY>::get(y, g, o);
         Elem<PY>::put(y, g, o, alpha * Elem<PA>::get(a, g, o) + beta * yv);
     }
-}
-
-// r = b - a ; partial |r|^2
-template <int P>
-__global__ void __launch_bounds__(BLAS_WG) k_sub_norm(Geom g, SpinorField<P> r, SpinorField<P> b, SpinorField<P> a,
-                                                      double *partials)
-{
-    double v[1] = {0};
-    GRID_STRIDE(o, 12 * g.V)
-    {
-        cx<double> d = Elem<P>::get(b, g, o) - Elem<P>::get(a, g, o);
-        Elem<P>::put(r, g, o, d);
-        v[0] += norm2(d);
-    }
-    wg_reduce_store<1>(v, partials);
 }
 
 // per-site conversion into another storage precision (any target, FP16 included)
@@ -1611,6 +1666,9 @@ hipError_t launch_blas_multi(hipStream_t st, int kind, const MultiBlasTab &t, in
     if (t.n <= 0 || t.n > MULTI_BLAS_MAX || total <= 0) return hipErrorInvalidValue;
     const dim3 G(total), B(BLAS_WG);
     switch (kind) {
+    case BLAS_NORM2: hipLaunchKernelGGL(k_blas_multi<BLAS_NORM2>, G, B, 0, st, t, partials); break;
+    case BLAS_SUB_NORM: hipLaunchKernelGGL(k_blas_multi<BLAS_SUB_NORM>, G, B, 0, st, t, partials); break;
+    case BLAS_START: hipLaunchKernelGGL(k_blas_multi<BLAS_START>, G, B, 0, st, t, partials); break;
     case BLAS_DOT: hipLaunchKernelGGL(k_blas_multi<BLAS_DOT>, G, B, 0, st, t, partials); break;
     case BLAS_DOT_NORM: hipLaunchKernelGGL(k_blas_multi<BLAS_DOT_NORM>, G, B, 0, st, t, partials); break;
     case BLAS_UPDATE1_H: hipLaunchKernelGGL(k_blas_multi<BLAS_UPDATE1_H>, G, B, 0, st, t, partials); break;
@@ -1722,6 +1780,11 @@ hipError_t launch_blas(const Geom &g, hipStream_t st, const BlasArgs &a)
             return hipErrorInvalidValue;
         break;
     }
+    case BLAS_START:  // v1 = v2 = v3 = v0 ; v4 = v0 (FP16, if given) ; v5 = 0 ; |v0|^2
+        hipLaunchKernelGGL(k_start, G, B, 0, st, g, sf<1>(a.v[0], g), sf<1>(a.v[1], g), sf<1>(a.v[2], g),
+                           sf<1>(a.v[3], g), a.v[4] ? sf<2>(a.v[4], g) : SpinorField<2>{}, sf<1>(a.v[5], g),
+                           a.partials);
+        break;
     case BLAS_UPDATE1_H:  // r -= c01 q ; |r|^2 ; v2 = r (FP16)
         hipLaunchKernelGGL(k_update1_h, G, B, 0, st, g, sf<1>(a.v[0], g), sf<1>(a.v[1], g), sf<2>(a.v[2], g), a.c[0],
                            a.c[1], a.partials);

@@ -86,6 +86,7 @@ enum BlasKind {
     BLAS_UPDATE2_MM, // FP32 y += c01 v1 + c23 v2 (FP16 v1, v2) ; r -= c23 t ; |r|^2, <rt|r>
     BLAS_PUPDATE_H,  // FP32 p = r + c01 (p - c23 q) ; v3 = p in FP16 storage
     BLAS_CAXPY,      // v0 += c01 v1 (FP32 v0, v1 at precision p1)
+    BLAS_START,      // FP32 v1 = v2 = v3 = v0 ; v4 = v0 in FP16 storage (unless null) ; v5 = 0 ; |v0|^2
 };
 
 struct BlasArgs {
@@ -96,8 +97,8 @@ struct BlasArgs {
     double *partials;
 };
 
-// One launch of a vector kernel over several lattices (the lockstep multi-lattice
-// solver): lattice k of the table runs the kernel's grid-stride loop over its own sites
+// One launch of a vector kernel over several lattices or right-hand sides (the lockstep
+// solvers): entry k of the table runs the kernel's grid-stride loop over its own sites
 // with nwg workgroups, launch workgroups item0 .. item0 + nwg - 1, its fields and
 // coefficients as in BlasArgs, and leaves its partial sums at partials[poff + w nv + q].
 // The table travels by value in the kernel arguments.
@@ -260,8 +261,9 @@ hipError_t launch_gcr_rupdate(const Geom &g, hipStream_t st, void *z, void *r, d
 // y (FP32) += sum_j coef_j p_j, p_j at precision pp (FP16 or FP32)
 hipError_t launch_multi_axpy(const Geom &g, hipStream_t st, const VecSet &ps, int k, int pp, void *y);
 hipError_t launch_finalize(hipStream_t st, const double *partials, int nwg, int nv, double *out);
-// kind in {BLAS_DOT, BLAS_DOT_NORM, BLAS_UPDATE1_H, BLAS_UPDATE2_MM (FP16 M p, M r), BLAS_PUPDATE_H}
-// on the lattices of t (total workgroups: the sum of their nwg)
+// kind in {BLAS_NORM2 and BLAS_SUB_NORM (FP64), BLAS_START (with its FP16 copy), BLAS_DOT, BLAS_DOT_NORM,
+// BLAS_UPDATE1_H, BLAS_UPDATE2_MM (FP16 M p, M r), BLAS_PUPDATE_H} on the entries of t (total
+// workgroups: the sum of their nwg)
 hipError_t launch_blas_multi(hipStream_t st, int kind, const MultiBlasTab &t, int total, double *partials);
 // out[3 slot[k] + q] = the fixed-order sum of lattice k's nv partials, for the lattices of t
 hipError_t launch_finalize_multi(hipStream_t st, const MultiBlasTab &t, const int *slot, const double *partials, int nv,

@@ -303,6 +303,7 @@ void blas_cost(const dd::BlasArgs &a, double &rw, double &fl)
     case dd::BLAS_UPDATE2_MM: rw = 4 * sp_b(1) + 2 * P1 + 2 * sp_b(1); fl = 432; break;  // y, r r/w; Mp, Mr; t, rt
     case dd::BLAS_PUPDATE_H: rw = 4 * sp_b(1) + sp_b(2); fl = 192; break;                 // p r/w, r, q, p16 written
     case dd::BLAS_CAXPY: rw = 2 * sp_b(1) + P1; fl = 96; break;
+    case dd::BLAS_START: rw = 5 * sp_b(1) + (a.v[4] ? sp_b(2) : 0); fl = 48; break;  // src read; r, p, rt, y, p16 written
     }
 }
 
@@ -317,13 +318,50 @@ dd_status blas(dd_ctx *c, dd::BlasArgs a)
     return DD_OK;
 }
 
+hipError_t vec_table(dd_ctx *c0, hipStream_t st, int kind, const std::vector<VecJob> &jobs, int nv, double *out)
+{
+    size_t i = 0;
+    while (i < jobs.size()) {
+        dd::MultiBlasTab t{};
+        int slot[dd::MULTI_BLAS_MAX];
+        int total = 0;
+        long long poff = 0;
+        double bytes = 0, flops = 0;
+        for (; i < jobs.size() && t.n < dd::MULTI_BLAS_MAX; ++i) {
+            const dd_ctx *c = jobs[i].c;
+            const dd::BlasArgs &a = jobs[i].a;
+            const int nwg = dd::blas_grid(c->g);
+            const long long need = (long long)nwg * (nv > 0 ? nv : 1);
+            if (t.n > 0 && poff + need > dd::MAX_PARTIALS) break;
+            dd::MultiBlasLat &e = t.e[t.n];
+            e.g = c->g;
+            for (int j = 0; j < 6; ++j) e.v[j] = a.v[j];
+            for (int j = 0; j < 4; ++j) e.c[j] = a.c[j];
+            e.item0 = total;
+            e.nwg = nwg;
+            e.poff = poff;
+            slot[t.n] = jobs[i].slot;
+            total += nwg;
+            poff += need;
+            ++t.n;
+            double rw, fl;
+            blas_cost(a, rw, fl);
+            bytes += rw * (double)c->g.V;
+            flops += fl * (double)c->g.V;
+        }
+        hipError_t e = timed(c0, DD_KT_BLAS, bytes, flops, [&] { return dd::launch_blas_multi(st, kind, t, total, c0->partials); });
+        if (e == hipSuccess && nv > 0) e = dd::launch_finalize_multi(st, t, slot, c0->partials, nv, out);
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+
 // run a reducing vector kernel and bring its nv sums to the host
 dd_status reduce(dd_ctx *c, dd::BlasArgs a, int nv, double *out)
 {
     dd_status st = blas(c, a);
     if (st != DD_OK) return st;
     HIPCK(c, dd::launch_finalize(c->stream, c->partials, dd::blas_grid(c->g), nv, c->red));
-    HIPCK(c, hipMemcpyAsync(c->red_host, c->red, nv * sizeof(double), hipMemcpyDeviceToHost, c->stream));
     HIPCK(c, hipStreamSynchronize(c->stream));
     for (int k = 0; k < nv; ++k) out[k] = c->red_host[k];
     return DD_OK;
@@ -368,7 +406,6 @@ dd_status residual64(dd_ctx *c, void *r, void *b, void *x, void *tmp, double *rn
 dd_status fetch(dd_ctx *c, int nv, double *out)
 {
     HIPCK(c, dd::launch_finalize(c->stream, c->partials, dd::blas_grid(c->g), nv, c->red));
-    HIPCK(c, hipMemcpyAsync(c->red_host, c->red, nv * sizeof(double), hipMemcpyDeviceToHost, c->stream));
     HIPCK(c, hipStreamSynchronize(c->stream));
     for (int k = 0; k < nv; ++k) out[k] = c->red_host[k];
     return DD_OK;

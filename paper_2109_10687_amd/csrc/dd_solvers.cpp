@@ -120,17 +120,14 @@ dd_status solve_sap32(dd_ctx *c, int prec, void *src, void *y, double tol, int m
     // inputs), and y takes alpha Mp + omega Mr in one pass per iteration
     const bool fused = prec == 2;
     dd_status st;
-    HIPCK(c, hipMemsetAsync(y, 0, spinor_bytes(c->g, DD_F32), c->stream));
     double bn2;
-    if ((st = norm2(c, src, 1, &bn2)) != DD_OK) return st;
+    if ((st = reduce(c, mkb(dd::BLAS_START, {src, r, p, rt, fused ? p16 : nullptr, y}, {1, 1, 1, 1, 2, 1}), 1, &bn2)) !=
+        DD_OK)
+        return st;
     if (!is_fin(bn2)) return fail(c, DD_ERR_NONFINITE, "inner source holds NaN or Inf");
     o.iters = 0;
     o.relres = 0;
     if (bn2 == 0.0) return DD_OK;
-    if ((st = copy(c, r, 1, src, 1)) != DD_OK) return st;
-    if ((st = copy(c, p, 1, src, 1)) != DD_OK) return st;
-    if ((st = copy(c, rt, 1, src, 1)) != DD_OK) return st;
-    if (fused && (st = copy(c, p16, 2, src, 1)) != DD_OK) return st;
     cplx rho0 = bn2;
     double rn2 = bn2;
     Stall stall{c->prm.stall_window};
