@@ -384,7 +384,7 @@ MULTI_SET = [((8, 8, 8, 8), (4, 4, 4, 4)), ((12, 12, 12, 12), (2, 2, 2, 2)), ((1
 
 def multi_bench(dd, args, reps=20):
     """The multi-lattice leg: eight independent lattices (two each of MULTI_SET, own links),
-    A on all of them in one persistent launch against one launch per lattice, and the lockstep
+    A on all of them in one launch against one launch per lattice, and the lockstep
     mixed-precision solve of all eight against eight solves one after another."""
     import torch
     import synth

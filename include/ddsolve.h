@@ -393,8 +393,8 @@ dd_status bicgstab_solve_batch(dd_ctx *ctx, void *x_dev, const void *b_dev, int 
 
 /* A set of independent lattices (sizes, blocks, kappa, c_SW and phases of their
  * own, each with its own gauge field) whose FP32 operator A is applied to all of
- * them in one persistent launch: the work items are (lattice, 256-site chunk)
- * pairs taken from a global counter, so uneven lattices fill the chip together. */
+ * them in one launch (up to 16 lattices each): the workgroups are (lattice,
+ * 256-site chunk) pairs, so uneven lattices fill the chip together. */
 typedef struct dd_multi dd_multi;
 
 /* params: nlat (1..64) parameter sets, each checked as by dd_create (every

@@ -532,7 +532,7 @@ class Solver:
 
 
 class Multi:
-    """Several independent lattices whose FP32 operator runs in one persistent launch
+    """Several independent lattices whose FP32 operator runs in one launch
     (dd_multi_*): load a gauge field per lattice, apply A to all, or solve all in lockstep."""
 
     def __init__(self, params_list, stream=None):

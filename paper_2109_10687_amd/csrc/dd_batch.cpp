@@ -1,6 +1,6 @@
 // dd_batch.cpp -- batched right-hand sides (one launch of the multi-RHS A for
 // all of them, each with its own BiCGStab scalars) and several lattices in one
-// work-queue launch: the internals and their C entry points.
+// launch: the internals and their C entry points.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -364,7 +364,6 @@ dd_status lat_fail(dd_multi *m, int k, dd_status s)
 
 void fill_desc(dd_multi *m, dd::LatDesc *d, const std::vector<const void *> &in, const std::vector<void *> &out)
 {
-    int item = 0;
     for (size_t k = 0; k < m->L.size(); ++k) {
         dd_ctx *c = m->L[k];
         d[k].g = c->g;
@@ -374,8 +373,6 @@ void fill_desc(dd_multi *m, dd::LatDesc *d, const std::vector<const void *> &in,
         d[k].cinv = c->cinv32;
         d[k].phase = c->phase;
         d[k].kappa = c->prm.kappa;
-        d[k].item0 = item;
-        item += (int)((c->g.V + 255) / 256);
     }
 }
 
@@ -391,7 +388,7 @@ dd_status multi_launch(dd_multi *m, int t, int pin)
     }
     dd_ctx *c0 = m->L[0];  // the timers of the first lattice's context hold the multi-lattice launches
     hipError_t e = timed(c0, DD_KT_DIRAC_MULTI, bytes, flops, [&] {
-        return dd::launch_dirac_multi(m->stream, m->desc_dev + t * n, n, m->total, pin, m->counter);
+        return dd::launch_dirac_multi(m->stream, m->desc.data() + t * n, n, pin);
     });
     if (e != hipSuccess) return mfail(m, DD_ERR_HIP, std::string("multi-lattice dirac launch: ") + hipGetErrorString(e));
     return DD_OK;
@@ -445,7 +442,7 @@ static dd_status sap_multi(dd_multi *m, int v)
     dd_ctx *t0 = m->L[0];  // the first lattice's timers hold the multi-lattice launches
     for (const auto &gr : m->sap_groups) {
         dd_ctx *c0 = m->L[gr.lat[0]];
-        const dd::SapLat *tab = m->sap_host + (size_t)v * m->L.size() + gr.off;
+        const dd::SapLat *tab = m->sap_tab.data() + (size_t)v * m->L.size() + gr.off;
         dd_status st = sap_schedule(c0->prm.n_sap, true, false, [&](int colour, int flags) -> dd_status {
             double bytes = 0, flops = 0;
             for (int k : gr.lat) {
@@ -455,7 +452,7 @@ static dd_status sap_multi(dd_multi *m, int v)
                 flops += f;
             }
             hipError_t e = timed(t0, DD_KT_SAP, bytes, flops, [&] {
-                return dd::launch_sap_half_pk_multi(c0->g, m->stream, tab, (int)gr.lat.size(), colour, flags);
+                return dd::launch_sap_half_pk_multi(m->stream, tab, (int)gr.lat.size(), colour, flags);
             });
             if (e != hipSuccess)
                 return mfail(m, DD_ERR_HIP, std::string("multi-lattice sap launch: ") + hipGetErrorString(e));
@@ -863,16 +860,13 @@ dd_status dd_multi_create(const dd_params *params, int nlat, void *hip_stream, d
             return st;
         }
         m->L.push_back(c);
-        m->total += (int)((c->g.V + 255) / 256);
     }
-    bool ok = hipMalloc((void **)&m->counter, sizeof(int)) == hipSuccess &&
-              hipMalloc((void **)&m->desc_dev, 3 * nlat * sizeof(dd::LatDesc)) == hipSuccess &&
-              hipHostMalloc((void **)&m->desc_host, 3 * nlat * sizeof(dd::LatDesc), hipHostMallocDefault) == hipSuccess &&
-              hipHostMalloc((void **)&m->sap_host, 2 * nlat * sizeof(dd::SapLat), hipHostMallocDefault) == hipSuccess &&
-              hipHostMalloc((void **)&m->red_all_host, 3 * nlat * sizeof(double), hipHostMallocMapped) == hipSuccess &&
+    bool ok = hipHostMalloc((void **)&m->red_all_host, 3 * nlat * sizeof(double), hipHostMallocMapped) == hipSuccess &&
               hipHostGetDevicePointer((void **)&m->red_all, m->red_all_host, 0) == hipSuccess;
-    // the groups of lattices whose SAP half-sweeps share one launch (same block shape and
-    // n_sap, packed-FP16 arithmetic)
+    m->desc.resize(3 * nlat);
+    m->sap_tab.resize(2 * nlat);
+    // the groups of lattices whose SAP half-sweeps share one launch (same n_sap, block shapes that go
+    // together, packed-FP16 arithmetic)
     int off = 0;
     for (int k = 0; k < nlat; ++k) {
         const dd_ctx *c = m->L[k];
@@ -880,14 +874,13 @@ dd_status dd_multi_create(const dd_params *params, int nlat, void *hip_stream, d
         dd_multi::SapGroup *grp = nullptr;
         for (auto &gr : m->sap_groups) {
             const dd_ctx *c0 = m->L[gr.lat[0]];
-            if (c0->prm.n_sap == c->prm.n_sap && std::equal(c0->g.b, c0->g.b + 4, c->g.b)) grp = &gr;
+            if (c0->prm.n_sap == c->prm.n_sap && dd::sap_multi_together(c0->g, c->g)) grp = &gr;
         }
         if (!grp) {
             m->sap_groups.emplace_back();
             grp = &m->sap_groups.back();
         }
         grp->lat.push_back(k);
-        grp->items += dd::sap_multi_items(c->g);
     }
     for (auto &gr : m->sap_groups) {
         gr.off = off;
@@ -907,10 +900,6 @@ dd_status dd_multi_destroy(dd_multi *m)
     if (!m) return DD_OK;
     if (!m->L.empty()) (void)hipStreamSynchronize(m->stream);  // no device call when nothing was created
     for (dd_ctx *c : m->L) dd_destroy(c);
-    if (m->counter) (void)hipFree(m->counter);
-    if (m->desc_dev) (void)hipFree(m->desc_dev);
-    if (m->desc_host) (void)hipHostFree(m->desc_host);
-    if (m->sap_host) (void)hipHostFree(m->sap_host);
     if (m->red_all_host) (void)hipHostFree(m->red_all_host);
     delete m;
     return DD_OK;
@@ -953,12 +942,11 @@ dd_status dirac_apply_multi(dd_multi *m, void *const *out, const void *const *in
         vout[k] = c->f32[8];
         MHIPCK(m, dd::launch_pack_spinor(c->g, m->stream, DD_F32, c->f32[7], in[k]));
     }
-    fill_desc(m, m->desc_host, vin, vout);
-    MHIPCK(m, hipMemcpyAsync(m->desc_dev, m->desc_host, n * sizeof(dd::LatDesc), hipMemcpyHostToDevice, m->stream));
+    fill_desc(m, m->desc.data(), vin, vout);
     if ((st = multi_launch(m, 0, 1)) != DD_OK) return st;
     for (int k = 0; k < n; ++k)
         MHIPCK(m, dd::launch_unpack_spinor(m->L[k]->g, m->stream, DD_F32, out[k], m->L[k]->f32[8]));
-    MHIPCK(m, hipStreamSynchronize(m->stream));  // the staging table is reused by the next call
+    MHIPCK(m, hipStreamSynchronize(m->stream));
     return DD_OK;
 }
 
@@ -984,14 +972,11 @@ dd_status bicgstab_solve_multi(dd_multi *m, void *const *x_dev, const void *cons
             i2[k] = c->f16[3];
             o2[k] = c->f32[6];
         }
-        fill_desc(m, m->desc_host + n, i1, o1);
-        fill_desc(m, m->desc_host + 2 * n, i2, o2);
-        MHIPCK(m, hipMemcpyAsync(m->desc_dev + n, m->desc_host + n, 2 * n * sizeof(dd::LatDesc), hipMemcpyHostToDevice,
-                                 m->stream));
+        fill_desc(m, m->desc.data() + n, i1, o1);
+        fill_desc(m, m->desc.data() + 2 * n, i2, o2);
         // the shared SAP launches: p16 -> M p and r16 -> M r, the SAP work vector
         for (int v = 0; v < 2; ++v)
             for (const auto &gr : m->sap_groups) {
-                int item0 = 0;
                 for (size_t q = 0; q < gr.lat.size(); ++q) {
                     dd_ctx *c = m->L[gr.lat[q]];
                     dd::SapArgs a{};
@@ -1005,11 +990,9 @@ dd_status bicgstab_solve_multi(dd_multi *m, void *const *x_dev, const void *cons
                     a.kappa = c->prm.kappa;
                     a.phase = c->phase;
                     a.faces = c->faces;
-                    m->sap_host[v * n + gr.off + q] = dd::sap_lat(c->g, a, item0);
-                    item0 += dd::sap_multi_items(c->g);
+                    m->sap_tab[v * n + gr.off + q] = dd::sap_lat(c->g, a);
                 }
             }
-        MHIPCK(m, hipStreamSynchronize(m->stream));
     }
     std::vector<dd_solve_info> inf(n);
     std::vector<BRhs> R(n);

@@ -98,19 +98,15 @@ struct dd_multi {
     std::vector<dd_ctx *> L;
     hipStream_t stream = nullptr;
     std::string err;
-    int *counter = nullptr;                      // work-queue head of the multi-lattice launch
-    dd::LatDesc *desc_dev = nullptr;             // three descriptor tables: the caller's apply, A Mp, A Mr
-    dd::LatDesc *desc_host = nullptr;            // pinned staging for the caller's apply
-    int total = 0;                               // work items (256-site chunks) over all lattices
-    // the multi-lattice packed-FP16 SAP: lattices with the same block shape and n_sap (and
-    // packed-FP16 arithmetic) share one launch per half-sweep; two tables of nlat entries (the
+    std::vector<dd::LatDesc> desc;  // three descriptor tables: the caller's apply, A Mp, A Mr
+    // the multi-lattice packed-FP16 SAP: lattices with the same n_sap (and packed-FP16 arithmetic)
+    // whose block shapes allow it (sap_multi_together) share one launch per half-sweep; two tables of nlat entries (the
     // SAP of p and of r in the inner solve), each group's lattices consecutive in them
     struct SapGroup {
         std::vector<int> lat;  // lattice indices
-        int items = 0;         // work items of a launch
         int off = 0;           // first table entry
     };
-    dd::SapLat *sap_host = nullptr;  // the multi-lattice half-sweep tables (kernel arguments)
+    std::vector<dd::SapLat> sap_tab;  // the multi-lattice half-sweep tables (kernel arguments)
     std::vector<SapGroup> sap_groups;
     double *red_all = nullptr, *red_all_host = nullptr;  // three reduction results per lattice (mapped host memory)
 };

@@ -143,8 +143,13 @@ struct LatDesc {
     double kappa;
     int item0;  // first work item (256-site chunk) of this lattice
 };
+constexpr int LAT_TAB_MAX = 16;
+struct LatTab {
+    LatDesc e[LAT_TAB_MAX];
+    int n;
+};
 
-// one lattice of a multi-lattice packed-FP16 half-sweep (4^4 blocks, one right-hand side)
+// one lattice of a multi-lattice packed-FP16 half-sweep (one right-hand side)
 struct SapLat {
     Geom g;
     SpinorField<2> b, s, x;  // source, work vector, output (FP16 storage)
@@ -229,13 +234,12 @@ size_t sap_pk_lds_bytes(const Geom &g);
 hipError_t launch_sap_prep(const Geom &g, hipStream_t st, const void *cinv16, void *cpsap);
 size_t sap_face_bytes(const Geom &g);
 hipError_t launch_sap_half_pk(const Geom &g, hipStream_t st, const SapArgs &a, int colour, int flags);
-// the table entry of one lattice for the multi-lattice half-sweep, the work items of one
-// lattice in it, and that launch: the nlat lattices of the table (host memory; it travels in
-// the kernel arguments, SAP_MULTI_MAX lattices per launch) share the block shape of g
-SapLat sap_lat(const Geom &g, const SapArgs &a, int item0);
-int sap_multi_items(const Geom &g);
-hipError_t launch_sap_half_pk_multi(const Geom &g, hipStream_t st, const SapLat *lat, int nlat, int colour,
-                                    int flags);
+// the table entry of one lattice for the multi-lattice half-sweep; whether two lattices can share its
+// launches (one block shape, or 4^4 and 2^4 blocks); and that launch: the nlat lattices of the table
+// (host memory; it travels in the kernel arguments, SAP_MULTI_MAX lattices per launch)
+SapLat sap_lat(const Geom &g, const SapArgs &a);
+bool sap_multi_together(const Geom &a, const Geom &b);
+hipError_t launch_sap_half_pk_multi(hipStream_t st, const SapLat *lat, int nlat, int colour, int flags);
 int blas_grid(const Geom &g);
 // grid of a grid-stride loop over the sites (one thread per site, at most BLAS_MAX_WG workgroups)
 int blas_grid_sites(const Geom &g);
@@ -269,9 +273,9 @@ hipError_t launch_blas_multi(hipStream_t st, int kind, const MultiBlasTab &t, in
 hipError_t launch_finalize_multi(hipStream_t st, const MultiBlasTab &t, const int *slot, const double *partials, int nv,
                                  double *out);
 
-// A on several lattices in one persistent launch (work queue over (lattice, chunk)
-// items, desc_dev in device memory, counter: one device int, cleared here)
-hipError_t launch_dirac_multi(hipStream_t st, const LatDesc *desc_dev, int nlat, int total, int pin, int *counter);
+// A on the nlat lattices of desc (host memory; LAT_TAB_MAX lattices per launch, in the kernel
+// arguments) at input precision pin
+hipError_t launch_dirac_multi(hipStream_t st, const LatDesc *desc, int nlat, int pin);
 
 // multi right-hand-side A on the matrix cores; variant in [0, mrhs_variant_count())
 int mrhs_variant_count();
