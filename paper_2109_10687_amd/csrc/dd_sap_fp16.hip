@@ -16,7 +16,7 @@
 // the block) travels between half-sweeps as face hop terms: each half-sweep leaves,
 // at the faces of its blocks, the projected half spinors of its result (multiplied
 // by its own link for the hops that run backwards into the neighbour), straight
-// from LDS in packed FP16, and the next half-sweep of the other colour reads them
+// from registers in packed FP16, and the next half-sweep of the other colour reads them
 // instead of its neighbours' whole spinors and links.  x itself is written only by
 // the last two half-sweeps (the preconditioner's output).  With h = H_{c c'} x_{c'}
 // the updated source x0 = s_c + kappa C_inv h takes one clover product (it is the
@@ -448,8 +448,20 @@ DD_INL void recon_mix(int mu, bool fwd, const PC (&k)[3], float f, Spinor<float>
     }
 }
 
-// LDS: the Jacobi iterate as 3 x uint4 per site (one colour: u.re, u.im, l.re, l.im), and a zero
-// spinor as site bvol
+// LDS of a block, planes of (bvol + 1) entries, one per site and a zero as entry bvol:
+//   uint4 planes 0 .. 2: the Jacobi iterate, one colour each (u.re, u.im, l.re, l.im);
+//   uint4 planes 3 + mu: colours 0 and 1 of the site's backward hop term in direction mu,
+//     U_mu(s)^dagger (1 + gamma_mu) x(s), pair form, and after them uint2 planes mu: its colour 2.
+// A site forms the terms of its own links, which stay in registers: a forward hop takes the
+// neighbour's iterate, a backward hop the neighbour's finished term.  That is 432 bytes of LDS
+// traffic per site and Jacobi step; with the links in LDS and every hop formed by its receiver
+// it was 720 (and 96 instead of 33 LDS reads and writes), 49 KB instead of 37 KB for a 4^4 block,
+// and the face terms were formed anew from LDS.  Half-sweeps: 32^3x64 146 -> 142 us, 16^4
+// 19.4 -> 18.5, 2^4 blocks on 12x16x16x24 19.7 -> 16.6, 2x4x4x2 blocks on 8x16^3 21.1 -> 17.4.
+// Small lattices are bound by latency (a step's 600 packed instructions and its LDS round trip on
+// one wavefront per SIMD, 1.6 us), large ones by the packed instructions (3 wavefronts per SIMD).
+DD_HDI int sap_lds_planes() { return 9; }  // in units of one uint4 plane
+
 DD_INL void lds_put(uint4 *xs, int bvol, int s, const SpH &p)
 {
 #pragma unroll
@@ -475,23 +487,37 @@ DD_INL void lds_get(const uint4 *xs, int bvol, int s, SpH &p)
     }
 }
 
-// staged links: U_mu(s) entry (a, b) as one half2 (re, im) at [(mu*9 + a*3 + b)][s]
-DD_INL void lds_link(const h2 *ul, int bvol, int s, int mu, h2 (&U)[3][3])
+// a site's backward hop term of direction mu: U_mu^dagger (1 + gamma_mu) x
+DD_INL void back_term(int mu, const h2 (&U)[3][3], const SpH &x, PC (&k)[3])
 {
-#pragma unroll
-    for (int a = 0; a < 3; ++a)
-#pragma unroll
-        for (int b = 0; b < 3; ++b) U[a][b] = ul[(mu * 9 + a * 3 + b) * bvol + s];
+    PC h[3];
+    proj_pair(mu, -1, x, h);
+    mat_pair(U, true, h, k);
 }
 
-// acc = H_in x in pair form (hops inside the block, Dirichlet at its faces); bvol is
-// the block volume (a compile-time constant where the kernel is specialised for it).
+DD_INL void lds_put_term(uint4 *xs, int bvol, int s, int mu, const PC (&k)[3])
+{
+    xs[(3 + mu) * (bvol + 1) + s] = make_uint4(bits_of(k[0].re), bits_of(k[0].im), bits_of(k[1].re), bits_of(k[1].im));
+    reinterpret_cast<uint2 *>(xs + 7 * (bvol + 1))[mu * (bvol + 1) + s] = make_uint2(bits_of(k[2].re), bits_of(k[2].im));
+}
+
+DD_INL void lds_get_term(const uint4 *xs, int bvol, int s, int mu, PC (&k)[3])
+{
+    const uint4 v = xs[(3 + mu) * (bvol + 1) + s];
+    const uint2 w = reinterpret_cast<const uint2 *>(xs + 7 * (bvol + 1))[mu * (bvol + 1) + s];
+    k[0] = PC{as_h2(v.x), as_h2(v.y)};
+    k[1] = PC{as_h2(v.z), as_h2(v.w)};
+    k[2] = PC{as_h2(w.x), as_h2(w.y)};
+}
+
+// acc = H_in x in pair form (hops inside the block, Dirichlet at its faces), from the iterate and the
+// backward hop terms in LDS and the site's own links U; bvol is the block volume (a compile-time
+// constant where the kernel is specialised for it).
 // nb[2 mu + side]: the site of the hop from +mu (side 0) or -mu (side 1), bvol (the zero
-// spinor) where that leaves the block: no branch splits the LDS reads of one hop from the
+// entry) where that leaves the block: no branch splits the LDS reads of one hop from the
 // arithmetic of the one before it.  Where a wavefront is a t slice (B = 4) the t hops branch.
 template <int B>
-DD_INL void inblock_pair(const uint4 *xs, const h2 *ul, const Geom &g, int bvol, const Site &st, const int (&nb)[8],
-                         SpH &acc)
+DD_INL void inblock_pair(const uint4 *xs, const h2 (&U)[4][3][3], int bvol, const int (&nb)[8], SpH &acc)
 {
     zero(acc);
 #pragma unroll
@@ -500,11 +526,15 @@ DD_INL void inblock_pair(const uint4 *xs, const h2 *ul, const Geom &g, int bvol,
         for (int side = 0; side < 2; ++side) {
             const int m = nb[2 * mu + side];
             if (B == 4 && mu == 3 && __builtin_amdgcn_readfirstlane(m) == bvol) continue;
-            SpH p;
-            lds_get(xs, bvol, m, p);
-            h2 U[3][3];
-            lds_link(ul, bvol, side == 0 ? st.s : (m < bvol ? m : st.s), mu, U);
-            hop_pair(mu, side == 0 ? 1 : -1, U, p, acc);
+            if (side == 0) {
+                SpH p;
+                lds_get(xs, bvol, m, p);
+                hop_pair(mu, 1, U[mu], p, acc);
+            } else {
+                PC k[3];
+                lds_get_term(xs, bvol, m, mu, k);
+                recon_pair(mu, -1, k, acc);
+            }
         }
     }
 }
@@ -523,6 +553,19 @@ DD_INL int face_offset(const Geom &g, int mu, int side)
     return o + side * (g.bvol >> log2b(g, mu));
 }
 
+// number of a face site of direction mu by its other three in-block coordinates
+DD_INL int face_site(const Geom &g, const Site &st, int mu)
+{
+    int kk = 0, w8 = 0;
+#pragma unroll
+    for (int nu = 0; nu < 4; ++nu) {
+        if (nu == mu) continue;
+        kk += st.c[nu] << w8;
+        w8 += log2b(g, nu);
+    }
+    return kk;
+}
+
 // Face hop terms.  A half-sweep that is followed by one of the other colour leaves, for
 // every site m of each of its block's faces, the part of that site's hop into the
 // neighbouring block that it can form from its own data (pair form, relative to the
@@ -534,31 +577,38 @@ DD_INL int face_offset(const Geom &g, int mu, int side)
 //     which multiplies it in; the term is the projection alone.
 // kk numbers the face's sites by their other three in-block coordinates in order, so a
 // face site and the site across the face share it.
-template <int MU, int SIDE>
-DD_INL void face_out(const Geom &g, int l, int kk, int p, int P, const uint4 *xs, const h2 *ul, int bvol, h2 *ft)
+// A site lies on at most one face per direction (extents are at least 2), so one masked pass per
+// direction stores both sides.  `term` is the site's backward hop term of direction mu.
+DD_INL void face_out(const Geom &g, const Site &st, int mu, int P, const SpH &x, const PC (&term)[3], h2 *ft)
 {
-    int m = (SIDE == 0 ? g.b[MU] - 1 : 0) << g.sh[MU];
-#pragma unroll
-    for (int nu = 0; nu < 4; ++nu) {
-        if (nu == MU) continue;
-        m += (kk & (g.b[nu] - 1)) << g.sh[nu];
-        kk >>= log2b(g, nu);
-    }
-    SpH xp;
-    lds_get(xs, bvol, m, xp);
+    const int c = st.c[mu];
+    const bool fwd = c == g.b[mu] - 1;
+    if (!fwd && c != 0) return;
     PC k[3];
-    if (SIDE == 0) {
-        PC h[3];
-        h2 U[3][3];
-        proj_pair(MU, -1, xp, h);
-        lds_link(ul, bvol, m, MU, U);
-        mat_pair(U, true, h, k);
-    } else {
-        proj_pair(MU, +1, xp, k);
-    }
-    uint2 *dst = reinterpret_cast<uint2 *>(ft) + (long long)l * 3 * P + p;
 #pragma unroll
-    for (int c = 0; c < 3; ++c) dst[c * P] = make_uint2(bits_of(k[c].re), bits_of(k[c].im));
+    for (int q = 0; q < 3; ++q) k[q] = term[q];
+    if (!fwd) proj_pair(mu, +1, x, k);
+    const int slot = face_site(g, st, mu) + (fwd ? face_offset(g, mu, 0) : face_offset(g, mu, 1));
+    uint2 *dst = reinterpret_cast<uint2 *>(ft) + (long long)st.l * 3 * P + slot;
+#pragma unroll
+    for (int q = 0; q < 3; ++q) dst[q * P] = make_uint2(bits_of(k[q].re), bits_of(k[q].im));
+}
+
+// the site's iterate and backward hop terms to LDS (LDS), and its face terms to ft (faces)
+template <int B, bool LDS>
+DD_INL void put_iterate(uint4 *xs, const Geom &g, int bvol, const Site &st, const h2 (&U)[4][3][3], const SpH &x,
+                        bool faces, int P, h2 *ft)
+{
+    if (LDS) lds_put(xs, bvol, st.s, x);
+#pragma unroll
+    for (int mu = 0; mu < 4; ++mu) {
+        // (B = 4: nobody takes the terms of the wavefront that is the block's last t slice)
+        if (B == 4 && mu == 3 && !faces && __builtin_amdgcn_readfirstlane(st.c[3]) == 3) continue;
+        PC k[3];
+        back_term(mu, U[mu], x, k);
+        if (LDS) lds_put_term(xs, bvol, st.s, mu, k);
+        if (faces) face_out(g, st, mu, P, x, k, ft);
+    }
 }
 
 // the face term at slot `slot` of block l and the scale of that block
@@ -591,12 +641,32 @@ DD_INL SpinorField<2> rhs_field(const SpinorField<2> &f, long long off)
 // k_sap_half<2>, except that the cross-block term comes from the face hop terms of the
 // previous half-sweep (faces: the terms, then one scale per block) and that x is written
 // only by the tails of Alg. 1 (a middle half-sweep's x is only ever read through those
-// terms).  FACES_OUT leaves this half-sweep's terms for the next one.  B > 0 (4 or 2) fixes the block shape to B^4 at compile time: the block extents, in-block strides and the
-// block volume become constants, so every LDS offset of the sweeps is an immediate instead
+// terms).  FACES_OUT leaves this half-sweep's terms for the next one.  B > 0 (4 or 2) fixes
+// the block shape to B^4 at compile time: the block extents, in-block strides and the block volume become constants, so every LDS offset of the sweeps is an immediate instead
 // of a register and the face index arithmetic folds; B = 0 takes the shape from the geometry.
 // blocks per workgroup of the packed-FP16 half-sweep: blocks of fewer than 64 sites share
 // one wavefront (a block volume is a power of two, at least 16)
 DD_HDI int sap_blocks_per_wg(int bvol) { return bvol < 64 ? 64 / bvol : 1; }
+
+// Hides from the compiler that the links are the same in every Jacobi step: it would otherwise form
+// the broadcasts of their parts (operand modifiers of the packed instructions) once, before the
+// loop, and hold them in registers (256 VGPRs and 82 AGPRs for the kernel, instead of 168).
+DD_INL void renew(h2 (&U)[4][3][3], ClovPair &C)
+{
+#pragma unroll
+    for (int b = 0; b < 2; ++b)
+#pragma unroll
+        for (int c = 0; c < 3; ++c)
+            asm volatile(""
+                         : "+v"(C.Ad[b][c]), "+v"(C.Au[b][c].re), "+v"(C.Au[b][c].im), "+v"(C.Bd[b][c]),
+                           "+v"(C.Bu[b][c].re), "+v"(C.Bu[b][c].im));
+#pragma unroll
+    for (int mu = 0; mu < 4; ++mu)
+#pragma unroll
+        for (int a = 0; a < 3; ++a)
+#pragma unroll
+            for (int b = 0; b < 3; ++b) asm volatile("" : "+v"(U[mu][a][b]));
+}
 
 // barrier between the writers and readers of a block's LDS; WAVE: they are one wavefront, whose LDS
 // accesses stay in order by themselves
@@ -625,8 +695,7 @@ DD_INL void sap_half_pk_body(Geom gin, int w, int colour, int flags, SpinorField
     const int bpw = WAVE ? 16 : sap_blocks_per_wg(bvol);
     const int q = bpw > 1 ? (int)(threadIdx.x >> g.lbvol) : 0;
     const int tid = bpw > 1 ? (int)(threadIdx.x & (bvol - 1)) : (int)threadIdx.x;  // site in the block
-    uint4 *xs = smem_pk + (size_t)q * (12 * bvol + 3);      // 3 x (bvol + 1) uint4
-    h2 *ul = reinterpret_cast<h2 *>(xs + 3 * (bvol + 1));   // 36 x bvol half2
+    uint4 *xs = smem_pk + (size_t)q * sap_lds_planes() * (bvol + 1);
     __shared__ float wmax[4];
     const int P = face_offset(g, 3, 1) + (bvol >> log2b(g, 3));  // face sites of a block
     wg_skew();
@@ -641,26 +710,18 @@ DD_INL void sap_half_pk_body(Geom gin, int w, int colour, int flags, SpinorField
     for (int mu = 0; mu < 4; ++mu) st.c[mu] = (st.s >> g.sh[mu]) & (g.b[mu] - 1);
     block_coords(g, st.l, st.B);
 
-    // stage the block's links in LDS as full 3x3 FP16 matrices (row 2 rebuilt from the two stored
-    // rows) and load its C_inv pair coefficients from the SAP-ready copy; all loads first, then row 2 and the LDS stores: where the pointers come from a table
-    // (the multi-lattice kernel) the loads are flat, and an LDS store right after each would wait
-    // for it
+    // the site's links, to stay in registers as full 3x3 FP16 matrices (row 2 rebuilt from the two
+    // stored rows), and its C_inv pair coefficients from the SAP-ready copy; all loads first
+    h2 lk[4][3][3];
     ClovPair CP;
-    {
-        h2 lk[4][3][3];
 #pragma unroll
-        for (int mu = 0; mu < 4; ++mu) link_rows(u16, g, st.l, st.s, mu, lk[mu]);
-        clov_pairs_get(cpsap, g, st.l, st.s, CP);
+    for (int mu = 0; mu < 4; ++mu) link_rows(u16, g, st.l, st.s, mu, lk[mu]);
+    clov_pairs_get(cpsap, g, st.l, st.s, CP);
 #pragma unroll
-        for (int mu = 0; mu < 4; ++mu) {
-            link_row2(lk[mu]);
-#pragma unroll
-            for (int a = 0; a < 3; ++a)
-#pragma unroll
-                for (int b = 0; b < 3; ++b) ul[(mu * 9 + a * 3 + b) * bvol + st.s] = lk[mu][a][b];
-        }
-    }
-    if (tid < 3) xs[tid * (bvol + 1) + bvol] = make_uint4(0, 0, 0, 0);  // read after the first barrier
+    for (int mu = 0; mu < 4; ++mu) link_row2(lk[mu]);
+    // the zero entries, read after the first barrier (a block has at least 16 threads)
+    if (tid < 7) xs[tid * (bvol + 1) + bvol] = make_uint4(0, 0, 0, 0);
+    if (tid < 4) reinterpret_cast<uint2 *>(xs + 7 * (bvol + 1))[tid * (bvol + 1) + bvol] = make_uint2(0, 0);
     int nb[8];
 #pragma unroll
     for (int mu = 0; mu < 4; ++mu) {
@@ -685,6 +746,7 @@ DD_INL void sap_half_pk_body(Geom gin, int w, int colour, int flags, SpinorField
     Spinor<float> hc;
     zero(hc);
     if (pre) {
+        renew(lk, CP);
         PC tk[4][3];
         float tsc[4];
 #pragma unroll
@@ -692,13 +754,7 @@ DD_INL void sap_half_pk_body(Geom gin, int w, int colour, int flags, SpinorField
             const int c = st.c[mu];
             const bool fwd = c == g.b[mu] - 1;
             if (!fwd && c != 0) continue;
-            int kk = 0, w8 = 0;
-#pragma unroll
-            for (int nu = 0; nu < 4; ++nu) {
-                if (nu == mu) continue;
-                kk += st.c[nu] << w8;
-                w8 += log2b(g, nu);
-            }
+            const int kk = face_site(g, st, mu);
             // forward hop from block l + mu, whose -mu face holds the projection; backward hop from
             // block l - mu, whose +mu face holds U^dagger times the projection
             const int dB = fwd ? (st.B[mu] == g.NB[mu] - 1 ? 1 - g.NB[mu] : 1) : (st.B[mu] == 0 ? g.NB[mu] - 1 : -1);
@@ -712,9 +768,7 @@ DD_INL void sap_half_pk_body(Geom gin, int w, int colour, int flags, SpinorField
             if (!fwd && c != 0) continue;
             if (fwd) {
                 PC k[3];
-                h2 U[3][3];
-                lds_link(ul, bvol, st.s, mu, U);  // this site's own link, staged by this thread
-                mat_pair(U, false, tk[mu], k);
+                mat_pair(lk[mu], false, tk[mu], k);
 #pragma unroll
                 for (int q3 = 0; q3 < 3; ++q3) tk[mu][q3] = k[q3];
             }
@@ -734,7 +788,7 @@ DD_INL void sap_half_pk_body(Geom gin, int w, int colour, int flags, SpinorField
     const int wv = bvol < 64 ? bvol : 64;  // lanes of one block in one wavefront
     for (int o2 = wv / 2; o2 >= 1; o2 >>= 1) m = fmaxf(m, __shfl_xor(m, o2, wv));
     if (bvol >= 64 && (threadIdx.x & 63) == 0) wmax[threadIdx.x >> 6] = m;
-    sap_barrier<WAVE>();  // also: every link is staged
+    sap_barrier<WAVE>();
     if (bvol >= 64) {  // smaller blocks have their maximum from the shuffles
         m = 0.f;
         for (int k = 0; k < bvol / 64; ++k) m = fmaxf(m, wmax[k]);
@@ -758,10 +812,12 @@ DD_INL void sap_half_pk_body(Geom gin, int w, int colour, int flags, SpinorField
     }
     x = x0;
     for (int j = 0; j < n_jac; ++j) {
+        renew(lk, CP);
         if (j > 0) sap_barrier<WAVE>();  // the readers of the last iterate are done
-        lds_put(xs, bvol, st.s, x);
+        put_iterate<B, true>(xs, g, bvol, st, lk, x, false, P, ft);
         sap_barrier<WAVE>();
-        inblock_pair<B>(xs, ul, g, bvol, st, nb, acc);
+        renew(lk, CP);
+        inblock_pair<B>(xs, lk, bvol, nb, acc);
         clover_pair(CP, acc, t);
 #pragma unroll
         for (int c = 0; c < 3; ++c) {
@@ -770,12 +826,15 @@ DD_INL void sap_half_pk_body(Geom gin, int w, int colour, int flags, SpinorField
         }
     }
     const float inv = m;  // undo the normalisation
+    const bool faces = (flags & SAP_FACES_OUT) != 0;
     if (!(flags & SAP_TAIL)) {
         // s_c <- (s_c + kappa C_inv h) + b_c - x_c + kappa C_inv H_in x_c, in FP32
         sap_barrier<WAVE>();
-        lds_put(xs, bvol, st.s, x);
+        renew(lk, CP);
+        put_iterate<B, true>(xs, g, bvol, st, lk, x, faces, P, ft);
         sap_barrier<WAVE>();
-        inblock_pair<B>(xs, ul, g, bvol, st, nb, acc);
+        renew(lk, CP);
+        inblock_pair<B>(xs, lk, bvol, nb, acc);
         clover_pair(CP, acc, t);
         SpH braw;
         const float sb = load_pair(bsrc, g, st.l, st.s, braw);
@@ -786,50 +845,14 @@ DD_INL void sap_half_pk_body(Geom gin, int w, int colour, int flags, SpinorField
         Spinor<float> xf;
         from_pair(x, inv, xf);
         xw.store(g, st.l, st.s, xf);
-        if (flags & SAP_FACES_OUT) {
-            sap_barrier<WAVE>();
-            lds_put(xs, bvol, st.s, x);
-        }
+        renew(lk, CP);
+        if (faces) put_iterate<B, false>(xs, g, bvol, st, lk, x, true, P, ft);
     }
-    if (flags & SAP_FACES_OUT) {
-        // this block's face terms from x in LDS (put there by the s update, or just above),
-        // spread evenly over the workgroup
-        sap_barrier<WAVE>();
-        const bool equal_faces = g.b[0] == g.b[1] && g.b[1] == g.b[2] && g.b[2] == g.b[3];
-        const int lnf = g.lbvol - log2b(g, 0);  // log2 of the sites per face
-        for (int p = tid; p < P; p += bvol) {
-            int q = 0, base = 0;
-            if (equal_faces) {  // hypercubic block: face q holds sites q * nf ... q * nf + nf - 1
-                q = p >> lnf;
-                base = q << lnf;
-            } else {
-#pragma unroll
-                for (int qq = 0; qq < 7; ++qq) {
-                    const int n = bvol >> log2b(g, qq >> 1);
-                    if (q == qq && p >= base + n) {
-                        base += n;
-                        q = qq + 1;
-                    }
-                }
-            }
-            const int kk = p - base;
-            switch (q) {  // faces in order +x, -x, +y, -y, +z, -z, +t, -t
-            case 0: face_out<0, 0>(g, st.l, kk, p, P, xs, ul, bvol, ft); break;
-            case 1: face_out<0, 1>(g, st.l, kk, p, P, xs, ul, bvol, ft); break;
-            case 2: face_out<1, 0>(g, st.l, kk, p, P, xs, ul, bvol, ft); break;
-            case 3: face_out<1, 1>(g, st.l, kk, p, P, xs, ul, bvol, ft); break;
-            case 4: face_out<2, 0>(g, st.l, kk, p, P, xs, ul, bvol, ft); break;
-            case 5: face_out<2, 1>(g, st.l, kk, p, P, xs, ul, bvol, ft); break;
-            case 6: face_out<3, 0>(g, st.l, kk, p, P, xs, ul, bvol, ft); break;
-            default: face_out<3, 1>(g, st.l, kk, p, P, xs, ul, bvol, ft); break;
-            }
-        }
-        if (tid == 0) fs[st.l] = inv;
-    }
+    if (faces && tid == 0) fs[st.l] = inv;
 }
 
 template <int B>
-__global__ void __launch_bounds__(256, B == 0 ? 2 : 1) k_sap_half_pk(Geom gin, int colour, int flags, SpinorField<2> bsrc,
+__global__ void __launch_bounds__(256, 3) k_sap_half_pk(Geom gin, int colour, int flags, SpinorField<2> bsrc,
                                                      SpinorField<2> sw, SpinorField<2> xw, const __half2 *u16,
                                                      const __half2 *cpsap, Phase4 ph, float kappa, int n_jac, h2 *ft,
                                                      SapRhs rhs)
@@ -855,7 +878,7 @@ __global__ void __launch_bounds__(256, B == 0 ? 2 : 1) k_sap_half_pk(Geom gin, i
 // (from a table in device memory every access would be a flat one).  Two launches, one per block
 // shape, ran one after the other: 44.0 + 16.4 us per half-sweep on the set of eight lattices.
 template <int B>
-__global__ void __launch_bounds__(256, B == 0 ? 2 : 3) k_sap_half_pk_multi(SapLatTab t, int colour, int flags)
+__global__ void __launch_bounds__(256, 3) k_sap_half_pk_multi(SapLatTab t, int colour, int flags)
 {
     const int w = xcd_remap(blockIdx.x, gridDim.x);
     int k = 0;
@@ -884,8 +907,7 @@ size_t sap_face_bytes(const Geom &g)
 
 size_t sap_pk_lds_bytes(const Geom &g)
 {
-    // the Jacobi iterate with its zero spinor, and the staged links
-    return (size_t)g.bvol * (3 * sizeof(uint4) + 36 * sizeof(__half2)) + 3 * sizeof(uint4);
+    return (size_t)sap_lds_planes() * (g.bvol + 1) * sizeof(uint4);
 }
 
 hipError_t launch_sap_half_pk(const Geom &g, hipStream_t st, const SapArgs &a, int colour, int flags)
