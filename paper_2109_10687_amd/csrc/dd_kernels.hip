@@ -463,7 +463,7 @@ __global__ void __launch_bounds__(256) k_dirac_ts(Geom gin, SpinorField<POUT> ou
 }
 
 // the sums of a spinor are complete here, and volatile statements that follow come after them
-DD_INL void settle(Spinor<double> &s)
+template <typename R> DD_INL void settle(Spinor<R> &s)
 {
 #pragma unroll
     for (int a = 0; a < 4; ++a)
@@ -657,87 +657,187 @@ __global__ void __launch_bounds__(256) k_dirac_multi(LatTab t)
 
 // ============================================================ SAP half-sweep
 
-// where the SAP kernel reads the block's links from: the FP16 copy (rows 0 and
-// 1, 24 half2 per site, 24 KB for a 4^4 block) is staged in LDS as is and the
-// third row is rebuilt at each use (staging full 3x3 matrices measured slower:
-// the extra LDS reads cost more than the rebuild); FP32 links are read from
-// global memory through the caches, which keeps that workgroup's LDS at 24 KB
-template <int P> struct SapLinks;
-template <> struct SapLinks<1> {
-    static constexpr int E = 0;  // nothing staged
-    using T = float2;
-    LinkField<1> U;
-    DD_INL void stage(T *, const Geom &, int, int) const {}
-    DD_INL void load(const T *, const Geom &g, int l, int s, int mu, Mat3<float> &W) const { U.load(g, l, s, mu, W); }
+// rows 0 and 1 of a link (row 2 is rebuilt where the matrix is used: 24 registers less for the four
+// links a site keeps)
+struct LinkRows {
+    float re[2][3], im[2][3];
 };
-template <> struct SapLinks<2> {
-    static constexpr int E = 24;
-    using T = __half2;
-    const __half2 *p;
-    DD_INL void stage(T *lds, const Geom &g, int l, int s) const
-    {
-        const uint2 *v = link16_site(p, g, l, s, 0);
-        for (int k = 0; k < E / 2; ++k) {
-            const uint2 t = v[k << g.lbvol];
-            lds[2 * k * g.bvol + s] = *reinterpret_cast<const __half2 *>(&t.x);
-            lds[(2 * k + 1) * g.bvol + s] = *reinterpret_cast<const __half2 *>(&t.y);
+
+DD_INL void full_link(const LinkRows &r, Mat3<float> &U)
+{
+#pragma unroll
+    for (int a = 0; a < 2; ++a)
+#pragma unroll
+        for (int b = 0; b < 3; ++b) U.m[a][b] = {r.re[a][b], r.im[a][b]};
+    su3_row3(U);
+}
+
+template <int P> DD_INL void load_rows(const LinkField<P> &U, const Geom &g, int l, int s, int mu, LinkRows &r)
+{
+    Mat3<float> W;
+    U.load(g, l, s, mu, W);
+#pragma unroll
+    for (int a = 0; a < 2; ++a)
+#pragma unroll
+        for (int b = 0; b < 3; ++b) {
+            r.re[a][b] = W.m[a][b].re;
+            r.im[a][b] = W.m[a][b].im;
+        }
+}
+
+// hides from the compiler that the links are the same in every Jacobi step: it would otherwise
+// rebuild their third rows once and hold them
+DD_INL void renew(LinkRows (&U)[4])
+{
+#pragma unroll
+    for (int mu = 0; mu < 4; ++mu)
+#pragma unroll
+        for (int a = 0; a < 2; ++a)
+#pragma unroll
+            for (int b = 0; b < 3; ++b) asm volatile("" : "+v"(U[mu].re[a][b]), "+v"(U[mu].im[a][b]));
+}
+
+// LDS of the FP32 half-sweep, planes of (bvol + 1) 16-byte entries, one per site and a zero as entry
+// bvol: 3 hh + c, the iterate's spins 2 hh, 2 hh + 1 of colour c; 6 + 3 mu + c, colour c of the
+// site's backward hop term of direction mu, U_mu^dagger (1 + gamma_mu) x.
+constexpr int SAP_PLANES = 18;
+
+DD_INL float4 pack2(const cx<float> &a, const cx<float> &b) { return make_float4(a.re, a.im, b.re, b.im); }
+
+// the site's iterate and backward hop terms to LDS.  A site forms the terms of its own links, which
+// stay in registers: a forward hop takes the neighbour's iterate, a backward hop the neighbour's
+// finished term.
+template <int B>
+DD_INL void put_iterate(float4 *xs, int bvol, const Site &st, const LinkRows (&U)[4], const Spinor<float> &x)
+{
+    const int n = bvol + 1;
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+        xs[c * n + st.s] = pack2(x.v[0][c], x.v[1][c]);
+        xs[(3 + c) * n + st.s] = pack2(x.v[2][c], x.v[3][c]);
+    }
+#pragma unroll
+    for (int mu = 0; mu < 4; ++mu) {
+        // (B = 4: nobody takes the terms of the wavefront that is the block's last t slice)
+        if (B == 4 && mu == 3 && __builtin_amdgcn_readfirstlane(st.c[3]) == 3) continue;
+        Mat3<float> W;
+        Half<float> h, k;
+        full_link(U[mu], W);
+        project(mu, -1, x, h);
+        mat_half(W, true, h, k);
+#pragma unroll
+        for (int c = 0; c < 3; ++c) xs[(6 + 3 * mu + c) * n + st.s] = pack2(k.v[0][c], k.v[1][c]);
+    }
+}
+
+DD_INL void get_iterate(const float4 *xs, int bvol, int s, Spinor<float> &x)
+{
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+        const float4 u = xs[c * (bvol + 1) + s], l = xs[(3 + c) * (bvol + 1) + s];
+        x.v[0][c] = {u.x, u.y};
+        x.v[1][c] = {u.z, u.w};
+        x.v[2][c] = {l.x, l.y};
+        x.v[3][c] = {l.z, l.w};
+    }
+}
+
+// acc = H_in x: the hops that stay inside the block (Dirichlet at the block faces), from LDS and
+// the site's own links; in-block hops never cross the lattice edge, so they carry no boundary phase.
+// nb[2 mu + side]: the site of the hop from +mu (side 0) or -mu (side 1), bvol (the zero entry)
+// where that leaves the block.  Where a wavefront is a t slice (B = 4) the t hops branch.
+template <int B>
+DD_INL void inblock_hops(const float4 *xs, int bvol, const int (&nb)[8], const LinkRows (&U)[4], Spinor<float> &acc)
+{
+    const int n = bvol + 1;
+    zero(acc);
+#pragma unroll
+    for (int mu = 0; mu < 4; ++mu) {
+#pragma unroll
+        for (int side = 0; side < 2; ++side) {
+            const int m = nb[2 * mu + side];
+            if (B == 4 && mu == 3 && __builtin_amdgcn_readfirstlane(m) == bvol) continue;
+            if (side == 0) {
+                Spinor<float> psi;
+                get_iterate(xs, bvol, m, psi);
+                Mat3<float> W;
+                full_link(U[mu], W);
+                hop(mu, 1, W, psi, false, cx<float>{1.f, 0.f}, acc);
+                settle(acc);
+            } else {
+                Half<float> k;
+#pragma unroll
+                for (int c = 0; c < 3; ++c) {
+                    const float4 t = xs[(6 + 3 * mu + c) * n + m];
+                    k.v[0][c] = {t.x, t.y};
+                    k.v[1][c] = {t.z, t.w};
+                }
+                reconstruct(mu, -1, k, acc);
+            }
         }
     }
-    DD_INL void load(const T *lds, const Geom &g, int, int s, int mu, Mat3<float> &U) const
-    {
+}
+
+// acc += H_{c c'} x_{c'} at this site: the hops that come from the neighbouring blocks.  A site
+// lies on at most one face per direction (extents are at least 2), so one masked pass per
+// direction takes both sides: forward U = this site's link, backward the neighbour's, daggered.
+template <int P>
+DD_INL void cross_hops(const Geom &g, const Site &st, const SpinorField<P> &xw, const LinkField<P> &U,
+                       const LinkRows (&lk)[4], const Phase4 &ph, Spinor<float> &acc)
+{
+#pragma unroll
+    for (int mu = 0; mu < 4; ++mu) {
+        const int c = st.c[mu];
+        const bool fwd = c == g.b[mu] - 1;
+        if (!fwd && c != 0) continue;
+        bool wrap, inblk;
+        const long long j = neighbour(g, st, mu, fwd ? 1 : -1, wrap, inblk);
+        const int lj = (int)(j >> g.lbvol), sj = (int)(j & (g.bvol - 1));
+        Spinor<float> psi;
+        xw.load(g, lj, sj, psi);
+        LinkRows n, r;
+        load_rows(U, g, lj, sj, mu, n);
 #pragma unroll
         for (int a = 0; a < 2; ++a)
 #pragma unroll
             for (int b = 0; b < 3; ++b) {
-                float2 t = __half22float2(lds[(mu * 6 + a * 3 + b) * g.bvol + s]);
-                U.m[a][b] = {t.x, t.y};
+                r.re[a][b] = fwd ? lk[mu].re[a][b] : n.re[a][b];
+                r.im[a][b] = fwd ? lk[mu].im[a][b] : n.im[a][b];
             }
-        su3_row3(U);
-    }
-};
-
-DD_INL void lds_store_spinor(float2 *xs, int bvol, int s, const Spinor<float> &x)
-{
+        Mat3<float> W, V;
+        full_link(r, W);
 #pragma unroll
-    for (int a = 0; a < 4; ++a)
+        for (int a = 0; a < 3; ++a)
 #pragma unroll
-        for (int c = 0; c < 3; ++c) xs[(a * 3 + c) * bvol + s] = make_float2(x.v[a][c].re, x.v[a][c].im);
-}
-
-DD_INL void lds_load_spinor(const float2 *xs, int bvol, int s, Spinor<float> &x)
-{
+            for (int b = 0; b < 3; ++b)
+                V.m[a][b] = {fwd ? W.m[a][b].re : W.m[b][a].re, fwd ? W.m[a][b].im : -W.m[b][a].im};
+        Half<float> h, k;
+        if (mu < 3) {
+            project(mu, fwd ? 1 : -1, psi, h);
+        } else {
 #pragma unroll
-    for (int a = 0; a < 4; ++a)
+            for (int a = 0; a < 2; ++a)
 #pragma unroll
-        for (int c = 0; c < 3; ++c) {
-            float2 t = xs[(a * 3 + c) * bvol + s];
-            x.v[a][c] = {t.x, t.y};
+                for (int q = 0; q < 3; ++q)
+                    h.v[a][q] = {2.f * (fwd ? psi.v[2 + a][q].re : psi.v[a][q].re),
+                                 2.f * (fwd ? psi.v[2 + a][q].im : psi.v[a][q].im)};
         }
-}
-
-// acc = H_in x: the hops that stay inside the block (Dirichlet at the block
-// faces), neighbours from LDS; in-block hops never cross the lattice edge, so
-// they carry no boundary phase
-template <int P>
-DD_INL void inblock_hops(const float2 *xs, const SapLinks<P> &lk, const typename SapLinks<P>::T *ul, const Geom &g,
-                         const Site &st, Spinor<float> &acc)
-{
-    zero(acc);
-    const int bvol = g.bvol;
+        mat_half(V, false, h, k);
+        if (wrap) {
+            const cx<float> phase = {(float)ph.re[mu], (float)(fwd ? ph.im[mu] : -ph.im[mu])};
 #pragma unroll
-    for (int mu = 0; mu < 4; ++mu) {
-        const int stride = 1 << g.sh[mu];
+            for (int a = 0; a < 2; ++a)
 #pragma unroll
-        for (int dir = 1; dir >= -1; dir -= 2) {
-            int c = st.c[mu] + dir;
-            if (c < 0 || c >= g.b[mu]) continue;
-            int m = st.s + dir * stride;
-            Spinor<float> psi;
-            lds_load_spinor(xs, bvol, m, psi);
-            Mat3<float> W;
-            lk.load(ul, g, st.l, dir > 0 ? st.s : m, mu, W);
-            hop(mu, dir, W, psi, false, cx<float>{1.f, 0.f}, acc);
+                for (int q = 0; q < 3; ++q) k.v[a][q] = k.v[a][q] * phase;
         }
+        if (mu < 3) {
+            reconstruct(mu, fwd ? 1 : -1, k, acc);
+        } else if (fwd) {
+            reconstruct(3, 1, k, acc);
+        } else {
+            reconstruct(3, -1, k, acc);
+        }
+        settle(acc);
     }
 }
 
@@ -750,18 +850,21 @@ DD_INL void inblock_hops(const float2 *xs, const SapLinks<P> &lk, const typename
 // cross-block term A_{c c'} x_{c'} (the odd tail, whose neighbours already hold the final even
 // x), and a CROSS_ONLY launch on the even blocks then adds A_{c c'} x_{c'} of the final odd x.  One
 // workgroup per block, one thread per site; blockDim.x == block volume.
+// Bound by FP32 arithmetic and its latencies (some 1480 instructions per Jacobi step and site at two
+// wavefronts per SIMD, 74 KB of LDS for a 4^4 block).  A site multiplies only by its own links: with
+// every hop formed by its receiver, each step read eight links per site through the caches (FP32
+// storage) and the cross-block hops took a pass per face.  SAP (10 half-sweeps, 4 Jacobi steps) in
+// FP32 on 16x16x24x32 and 32^4: 464 -> 441 us and 2.04 -> 1.85 ms; 2^4 blocks on 12^4 481 -> 261 us;
+// FP16 storage on 16x16x24x32 488 -> 400 us.
 template <int P, int B>
-__global__ void __launch_bounds__(256) k_sap_half(Geom gin, int colour, int flags, SpinorField<P> bsrc,
-                                                  SpinorField<P> sw, SpinorField<P> xw, SapLinks<P> lk,
-                                                  LinkField<P> U, CloverField<P> Ci, Phase4 ph, float kappa,
+__global__ void __launch_bounds__(256, 2) k_sap_half(Geom gin, int colour, int flags, SpinorField<P> bsrc,
+                                                  SpinorField<P> sw, SpinorField<P> xw, LinkField<P> U,
+                                                  CloverField<P> Ci, Phase4 ph, float kappa,
                                                   int n_jac, SpinorField<P> axw)
 {
     const Geom g = fixed_shape<B>(gin);
-    using LT = typename SapLinks<P>::T;
-    extern __shared__ float4 smem_raw[];
+    extern __shared__ float4 xs[];
     const int bvol = g.bvol;
-    float2 *xs = reinterpret_cast<float2 *>(smem_raw);
-    LT *ul = reinterpret_cast<LT *>(xs + 12 * bvol);
     wg_skew();
 
     const int w = xcd_remap(blockIdx.x, gridDim.x);
@@ -773,7 +876,16 @@ __global__ void __launch_bounds__(256) k_sap_half(Geom gin, int colour, int flag
     block_coords(g, st.l, st.B);
 
     const bool cross_only = (flags & SAP_CROSS_ONLY) != 0;
-    if (!cross_only) lk.stage(ul, g, st.l, st.s);
+    LinkRows lk[4];
+#pragma unroll
+    for (int mu = 0; mu < 4; ++mu) load_rows(U, g, st.l, st.s, mu, lk[mu]);
+    for (int p = st.s; p < SAP_PLANES; p += bvol) xs[p * (bvol + 1) + bvol] = make_float4(0.f, 0.f, 0.f, 0.f);
+    int nb[8];
+#pragma unroll
+    for (int mu = 0; mu < 4; ++mu) {
+        nb[2 * mu] = st.c[mu] + 1 < g.b[mu] ? st.s + (1 << g.sh[mu]) : bvol;
+        nb[2 * mu + 1] = st.c[mu] > 0 ? st.s - (1 << g.sh[mu]) : bvol;
+    }
 
     Clov<float> cl;
     Ci.load(g, st.l, st.s, cl);
@@ -785,31 +897,10 @@ __global__ void __launch_bounds__(256) k_sap_half(Geom gin, int colour, int flag
             sw.load(g, st.l, st.s, src);
     }
 
-    // acc += H_{c c'} x_{c'} at this site: the hops that come from the neighbouring blocks
-    auto cross_hops = [&](Spinor<float> &acc) {
-        for (int mu = 0; mu < 4; ++mu) {
-            for (int dir = 1; dir >= -1; dir -= 2) {
-                int c = st.c[mu] + dir;
-                if (c >= 0 && c < g.b[mu]) continue;
-                bool wrap, inblk;
-                long long j = neighbour(g, st, mu, dir, wrap, inblk);
-                int lj = (int)(j >> g.lbvol), sj = (int)(j & (bvol - 1));
-                Spinor<float> psi;
-                xw.load(g, lj, sj, psi);
-                Mat3<float> W;
-                if (dir > 0)
-                    U.load(g, st.l, st.s, mu, W);
-                else
-                    U.load(g, lj, sj, mu, W);
-                cx<float> phase = {(float)ph.re[mu], (float)(dir > 0 ? ph.im[mu] : -ph.im[mu])};
-                hop(mu, dir, W, psi, wrap, phase, acc);
-            }
-        }
-    };
     Spinor<float> acc, t;
     if ((flags & SAP_PRE) || cross_only) {
         zero(acc);
-        cross_hops(acc);
+        cross_hops(g, st, xw, U, lk, ph, acc);
         clover_mul(cl, acc, t);
         if (cross_only) {  // ax_c += A_{c c'} x_{c'} = -kappa C_inv H_{c c'} x_{c'}
             Spinor<float> q;
@@ -829,10 +920,12 @@ __global__ void __launch_bounds__(256) k_sap_half(Geom gin, int colour, int flag
 
     Spinor<float> x = src;
     for (int j = 0; j < n_jac; ++j) {
-        wg_barrier();  // previous readers of xs are done (and links staged)
-        lds_store_spinor(xs, bvol, st.s, x);
+        renew(lk);
+        if (j > 0) wg_barrier();  // previous readers of xs are done
+        put_iterate<B>(xs, bvol, st, lk, x);
         wg_barrier();
-        inblock_hops<P>(xs, lk, ul, g, st, acc);
+        renew(lk);
+        inblock_hops<B>(xs, bvol, nb, lk, acc);
         clover_mul(cl, acc, t);
 #pragma unroll
         for (int a = 0; a < 4; ++a)
@@ -840,10 +933,12 @@ __global__ void __launch_bounds__(256) k_sap_half(Geom gin, int colour, int flag
             for (int c = 0; c < 3; ++c) x.v[a][c] = src.v[a][c] + kappa * t.v[a][c];
     }
     if (!(flags & SAP_TAIL)) {
+        renew(lk);
         wg_barrier();
-        lds_store_spinor(xs, bvol, st.s, x);
+        put_iterate<B>(xs, bvol, st, lk, x);
         wg_barrier();
-        inblock_hops<P>(xs, lk, ul, g, st, acc);
+        renew(lk);
+        inblock_hops<B>(xs, bvol, nb, lk, acc);
         clover_mul(cl, acc, t);
         Spinor<float> b;
         bsrc.load(g, st.l, st.s, b);
@@ -858,12 +953,15 @@ __global__ void __launch_bounds__(256) k_sap_half(Geom gin, int colour, int flag
         // in-block hops of the final x, and with AMSAP_PRE the hops from the other colour's final
         // x, the same ones this launch's prologue read (formed again here rather than kept
         // through the sweeps), all under one C_inv product as in the Dirac apply
+        renew(lk);
         wg_barrier();
-        lds_store_spinor(xs, bvol, st.s, x);
+        put_iterate<B>(xs, bvol, st, lk, x);
         wg_barrier();
-        inblock_hops<P>(xs, lk, ul, g, st, acc);
-        if (flags & SAP_AMSAP_PRE) cross_hops(acc);
+        renew(lk);
+        inblock_hops<B>(xs, bvol, nb, lk, acc);
+        if (flags & SAP_AMSAP_PRE) cross_hops(g, st, xw, U, lk, ph, acc);
         clover_mul(cl, acc, t);
+        get_iterate(xs, bvol, st.s, x);  // (from LDS: 24 registers less during the hops)
         Spinor<float> q;
 #pragma unroll
         for (int a = 0; a < 4; ++a)
@@ -1619,27 +1717,21 @@ hipError_t launch_dirac_multi(hipStream_t st, const LatDesc *desc, int nlat, int
     return hipSuccess;
 }
 
-size_t sap_lds_bytes(const Geom &g, int prec)
-{
-    size_t link = prec == 1 ? 0 : SapLinks<2>::E * sizeof(__half2);
-    return (size_t)g.bvol * (12 * sizeof(float2) + link);
-}
+size_t sap_lds_bytes(const Geom &g) { return (size_t)SAP_PLANES * (g.bvol + 1) * sizeof(float4); }
 
 hipError_t launch_sap_half(const Geom &g, hipStream_t st, const SapArgs &a, int colour, int flags)
 {
     if ((flags & (SAP_AMSAP | SAP_CROSS_ONLY)) && !a.ax) return hipErrorInvalidValue;
     const int nwg = g.nblk / 2;
-    const size_t lds = sap_lds_bytes(g, a.prec);
+    const size_t lds = sap_lds_bytes(g);
     const bool cube4 = g.b[0] == 4 && g.b[1] == 4 && g.b[2] == 4 && g.b[3] == 4;
     if (a.prec == 1) {
         hipLaunchKernelGGL((cube4 ? k_sap_half<1, 4> : k_sap_half<1, 0>), dim3(nwg), dim3(g.bvol), lds, st, g, colour, flags, sf<1>((void *)a.b, g),
-                           sf<1>(a.s, g), sf<1>(a.x, g), SapLinks<1>{LinkField<1>{(const float2 *)a.links}},
-                           LinkField<1>{(const float2 *)a.links}, CloverField<1>{(const float2 *)a.cinv}, a.phase,
+                           sf<1>(a.s, g), sf<1>(a.x, g), LinkField<1>{(const float2 *)a.links}, CloverField<1>{(const float2 *)a.cinv}, a.phase,
                            (float)a.kappa, a.n_jac, sf<1>(a.ax, g));
     } else if (a.prec == 2) {
         hipLaunchKernelGGL((cube4 ? k_sap_half<2, 4> : k_sap_half<2, 0>), dim3(nwg), dim3(g.bvol), lds, st, g, colour, flags, sf<2>((void *)a.b, g),
-                           sf<2>(a.s, g), sf<2>(a.x, g), SapLinks<2>{(const __half2 *)a.links},
-                           LinkField<2>{(const __half2 *)a.links}, CloverField<2>{(const __half2 *)a.cinv}, a.phase,
+                           sf<2>(a.s, g), sf<2>(a.x, g), LinkField<2>{(const __half2 *)a.links}, CloverField<2>{(const __half2 *)a.cinv}, a.phase,
                            (float)a.kappa, a.n_jac, sf<2>(a.ax, g));
     } else {
         return hipErrorInvalidValue;

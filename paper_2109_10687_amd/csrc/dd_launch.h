@@ -224,7 +224,7 @@ hipError_t launch_dirac(const Geom &g, hipStream_t st, const DiracArgs &a);
 // out = D in (op 0) or D^dagger in (op 2) on canonical spinors, FP64 links and clover blocks
 hipError_t launch_dirac_can(const Geom &g, hipStream_t st, void *out, const void *in, const void *u64,
                             const void *clov64, int op, double kappa, const Phase4 &ph);
-size_t sap_lds_bytes(const Geom &g, int prec);
+size_t sap_lds_bytes(const Geom &g);
 hipError_t launch_sap_half(const Geom &g, hipStream_t st, const SapArgs &a, int colour, int flags);
 // the same half-sweep with FP16 storage and packed FP16 block-local arithmetic; the cross-block
 // term travels between half-sweeps as face hop terms (sap_face_bytes per lattice)
