@@ -300,6 +300,18 @@ struct VecJob {
     int slot;
 };
 hipError_t vec_table(dd_ctx *c0, hipStream_t st, int kind, const std::vector<VecJob> &jobs, int nv, double *out);
+
+// r = b - D x (FP64) of every job, |r|^2 to out[3 slot]: launches of up to RESID_MAX entries (all of
+// one lattice where `shared`) whose partials fit c0's, on stream st.  A lattice whose partials alone
+// do not fit is refused (resid_fits).
+struct ResidJob {
+    dd_ctx *c;
+    const void *x, *b;
+    void *r;
+    int slot;
+};
+bool resid_fits(const dd::Geom &g);
+hipError_t resid_table(dd_ctx *c0, hipStream_t st, const std::vector<ResidJob> &jobs, bool shared, double *out);
 // out = A in for n batched fields at input precision pin (DD_F32 or DD_F16), FP32 output,
 // in tiles of up to 12
 dd_status k_dirac_mrhs(dd_ctx *c, void *out, const void *in, int n, int pin);

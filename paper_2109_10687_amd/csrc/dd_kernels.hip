@@ -214,15 +214,54 @@ template <int PG> struct Acc<0, PG> { using T = double; };
 template <> struct Acc<1, 0> { using T = double; };
 template <> struct Acc<2, 0> { using T = double; };
 
+// the sums of a spinor are complete here, and volatile statements that follow come after them
+template <typename R> DD_INL void settle(Spinor<R> &s)
+{
+#pragma unroll
+    for (int a = 0; a < 4; ++a)
+        asm volatile("" : "+v"(s.v[a][0].re), "+v"(s.v[a][0].im), "+v"(s.v[a][1].re), "+v"(s.v[a][1].im),
+                     "+v"(s.v[a][2].re), "+v"(s.v[a][2].im));
+}
+
+// The chiral components v = (u_+, u_-) times the FP64 clover blocks of site sb of block l, block by block:
+// the second block's loads stay behind the first product, and both behind the hops' sums
+// acc (together they take more registers than there are)
+DD_INL void clover_blocks(const double2 *clov, const Geom &g, int l, int sb, Spinor<double> &acc, cx<double> (&v)[2][6],
+                          cx<double> (&r)[2][6])
+{
+#pragma unroll
+    for (int b = 0; b < 2; ++b) {
+        settle(acc);
+        if (b == 1)
+            asm volatile("" : "+v"(l), "+v"(sb) : "v"(r[0][0].re), "v"(r[0][1].re), "v"(r[0][2].re), "v"(r[0][3].re),
+                         "v"(r[0][4].re), "v"(r[0][5].re), "v"(r[0][0].im), "v"(r[0][1].im), "v"(r[0][2].im),
+                         "v"(r[0][3].im), "v"(r[0][4].im), "v"(r[0][5].im));
+        else
+            asm volatile("" : "+v"(l), "+v"(sb));
+        double d[6];
+        cx<double> h[15];
+#pragma unroll
+        for (int j = 0; j < 3; ++j) {
+            const double2 q = ld_stream(&clov[elem(g, l, sb, 36, b * 18 + j)]);
+            d[2 * j] = q.x;
+            d[2 * j + 1] = q.y;
+        }
+#pragma unroll
+        for (int j = 0; j < 15; ++j) {
+            const double2 q = ld_stream(&clov[elem(g, l, sb, 36, b * 18 + 3 + j)]);
+            h[j] = {q.x, q.y};
+        }
+        herm6(d, h, v[b], r[b]);
+    }
+}
+
 // out = op(in) on the full lattice, one thread per site; op 0 = D, 1 = A, 2 = D^dagger
-// out(i) = op(in)(i) for one site i
-template <int PIN, int POUT, int PG, int OP>
-DD_INL void dirac_site(const Geom &g, const SpinorField<POUT> &out, const SpinorField<PIN> &in, const LinkField<PG> &U,
-                       const CloverField<PG> &C, const Phase4 &ph, double kappa, long long i)
+// o = op(in)(i) for one site i, decoded in st
+template <int PIN, int PG, int OP>
+DD_INL void dirac_value(const Geom &g, const SpinorField<PIN> &in, const LinkField<PG> &U, const CloverField<PG> &C,
+                        const Phase4 &ph, double kappa, const Site &st, Spinor<typename Acc<PIN, PG>::T> &o)
 {
     using R = typename Acc<PIN, PG>::T;
-    Site st;
-    decode(g, i, st);
     Spinor<R> acc;
     zero(acc);
 #pragma unroll
@@ -242,14 +281,38 @@ DD_INL void dirac_site(const Geom &g, const SpinorField<POUT> &out, const Spinor
                 U.load(g, lj, sj, mu, W);
             cx<R> phase = {R(ph.re[mu]), R(dir > 0 ? ph.im[mu] : -ph.im[mu])};
             hop(mu, dir, W, psi, wrap, phase, acc);
+            // (FP64: the loads of every hop at once take more registers than there are: 256 and 74, one
+            // wavefront per SIMD, against 220 and two)
+            if (PG == 0) settle(acc);
         }
     }
-    Spinor<R> x, t, o;
+    Spinor<R> x, t;
     in.load(g, st.l, st.s, x);
     if (OP == 2) gamma5(x);
+    const R k = R(kappa);
+    if constexpr (PG == 0) {
+        cx<double> v[2][6], r[2][6];
+#pragma unroll
+        for (int a = 0; a < 2; ++a)
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                v[0][a * 3 + c] = x.v[a][c] + x.v[a + 2][c];
+                v[1][a * 3 + c] = x.v[a][c] - x.v[a + 2][c];
+            }
+        clover_blocks(C.p, g, st.l, st.s, acc, v, r);
+#pragma unroll
+        for (int a = 0; a < 2; ++a)
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                const int q = a * 3 + c;
+                o.v[a][c] = (r[0][q] + r[1][q]) - kappa * acc.v[a][c];
+                o.v[a + 2][c] = (r[0][q] - r[1][q]) - kappa * acc.v[a + 2][c];
+            }
+        if (OP == 2) gamma5(o);
+        return;
+    }
     Clov<R> cl;
     C.load(g, st.l, st.s, cl);
-    const R k = R(kappa);
     if (OP == 1) {
         clover_mul(cl, acc, t);
 #pragma unroll
@@ -264,6 +327,16 @@ DD_INL void dirac_site(const Geom &g, const SpinorField<POUT> &out, const Spinor
             for (int c = 0; c < 3; ++c) o.v[a][c] = t.v[a][c] - k * acc.v[a][c];
         if (OP == 2) gamma5(o);
     }
+}
+
+template <int PIN, int POUT, int PG, int OP>
+DD_INL void dirac_site(const Geom &g, const SpinorField<POUT> &out, const SpinorField<PIN> &in, const LinkField<PG> &U,
+                       const CloverField<PG> &C, const Phase4 &ph, double kappa, long long i)
+{
+    Site st;
+    decode(g, i, st);
+    Spinor<typename Acc<PIN, PG>::T> o;
+    dirac_value<PIN, PG, OP>(g, in, U, C, ph, kappa, st, o);
     out.store(g, st.l, st.s, o, true);
 }
 
@@ -462,15 +535,6 @@ __global__ void __launch_bounds__(256) k_dirac_ts(Geom gin, SpinorField<POUT> ou
     }
 }
 
-// the sums of a spinor are complete here, and volatile statements that follow come after them
-template <typename R> DD_INL void settle(Spinor<R> &s)
-{
-#pragma unroll
-    for (int a = 0; a < 4; ++a)
-        asm volatile("" : "+v"(s.v[a][0].re), "+v"(s.v[a][0].im), "+v"(s.v[a][1].re), "+v"(s.v[a][1].im),
-                     "+v"(s.v[a][2].re), "+v"(s.v[a][2].im));
-}
-
 // ---- D and D^dagger on canonical spinors (FP64), no pack and unpack passes
 // A workgroup takes a 4^3 x TT tile of the lattice (every extent is a multiple of 4), one site per
 // thread.  The canonical layout keeps a site's 12 components together (192 bytes), so the tile is
@@ -587,30 +651,7 @@ __global__ void __launch_bounds__(64 * TT, 2) k_dirac_can(Geom gin, double2 *out
                 v[1][a * 3 + c] = x.v[a][c] - x.v[a + 2][c];
             }
     }
-#pragma unroll
-    for (int b = 0; b < 2; ++b) {
-        settle(acc);
-        if (b == 1)
-            asm volatile("" : "+v"(l), "+v"(sb) : "v"(r[0][0].re), "v"(r[0][1].re), "v"(r[0][2].re), "v"(r[0][3].re),
-                         "v"(r[0][4].re), "v"(r[0][5].re), "v"(r[0][0].im), "v"(r[0][1].im), "v"(r[0][2].im),
-                         "v"(r[0][3].im), "v"(r[0][4].im), "v"(r[0][5].im));
-        else
-            asm volatile("" : "+v"(l), "+v"(sb));
-        double d[6];
-        cx<double> h[15];
-#pragma unroll
-        for (int j = 0; j < 3; ++j) {
-            const double2 q = ld_stream(&clov[elem(g, l, sb, 36, b * 18 + j)]);
-            d[2 * j] = q.x;
-            d[2 * j + 1] = q.y;
-        }
-#pragma unroll
-        for (int j = 0; j < 15; ++j) {
-            const double2 q = ld_stream(&clov[elem(g, l, sb, 36, b * 18 + 3 + j)]);
-            h[j] = {q.x, q.y};
-        }
-        herm6(d, h, v[b], r[b]);
-    }
+    clover_blocks(clov, g, l, sb, acc, v, r);
     wg_barrier();
 #pragma unroll
     for (int c = 0; c < 3; ++c)
@@ -1302,6 +1343,47 @@ __global__ void __launch_bounds__(BLAS_WG) k_sub_norm(Geom g, SpinorField<P> r, 
     sub_norm_body<P>(g, r, b, a, partials, blockIdx.x, gridDim.x);
 }
 
+// r = b - D x in FP64 and the partial sums of |r|^2, for the entries of a table in one launch: one
+// field, several lattices, or several right-hand sides of one lattice (t.shared), whose workgroups for a
+// chunk of 256 sites then follow one another, so its links and clover blocks (300 KB, three quarters
+// of what a right-hand side reads) come from the L2 after the first.  D x itself is never stored.
+// HBM-bound (1728 bytes per site): with a launch of D (t-streamed where that pays) and a pass of
+// b - D x each, against this: 12 right-hand sides on 16^3x32 662 and 455 us, 16^4 alone 31 and 26,
+// 32^3x64 932 and 856 us, 64^3x128 14.7 and 13.6 ms.
+__global__ void __launch_bounds__(BLAS_WG, 2) k_resid64(ResidTab t, double *partials)
+{
+    const int w = xcd_remap(blockIdx.x, gridDim.x);
+    int k = 0, chunk;
+    if (t.shared) {
+        chunk = w / t.n;
+        k = w - chunk * t.n;
+    } else {
+        while (k + 1 < t.n && w >= t.e[k + 1].item0) ++k;
+        chunk = w - t.e[k].item0;
+    }
+    const ResidLat &L = t.e[k];
+    const Geom &g = L.g;
+    const long long i = (long long)chunk * BLAS_WG + threadIdx.x;
+    double v[1] = {0};
+    if (i < g.V) {
+        Site st;
+        decode(g, i, st);
+        Spinor<double> o, b;
+        dirac_value<0, 0, 0>(g, SpinorField<0>{(double2 *)L.x}, LinkField<0>{(const double2 *)L.u},
+                             CloverField<0>{(const double2 *)L.clov}, L.phase, L.kappa, st, o);
+        SpinorField<0>{(double2 *)L.b}.load(g, st.l, st.s, b);
+#pragma unroll
+        for (int a = 0; a < 4; ++a)
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                o.v[a][c] = b.v[a][c] - o.v[a][c];
+                v[0] += norm2(o.v[a][c]);
+            }
+        SpinorField<0>{(double2 *)L.r}.store(g, st.l, st.s, o);
+    }
+    wg_reduce_store_at<1>(v, partials + L.poff, chunk);
+}
+
 // The vector kernels of the lockstep solvers (several lattices, several right-hand sides), one launch for the lattices of a
 // table (each with its own fields, coefficients, workgroups and partials)
 template <int KIND>
@@ -1772,6 +1854,15 @@ hipError_t launch_blas_multi(hipStream_t st, int kind, const MultiBlasTab &t, in
     case BLAS_PUPDATE_H: hipLaunchKernelGGL(k_blas_multi<BLAS_PUPDATE_H>, G, B, 0, st, t, partials); break;
     default: return hipErrorInvalidValue;
     }
+    return hipGetLastError();
+}
+
+int resid_grid(const Geom &g) { return grid_sites(g.V, BLAS_WG); }
+
+hipError_t launch_resid64(hipStream_t st, const ResidTab &t, int total, double *partials)
+{
+    if (t.n <= 0 || t.n > RESID_MAX || total <= 0) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(k_resid64, dim3(total), dim3(BLAS_WG), 0, st, t, partials);
     return hipGetLastError();
 }
 

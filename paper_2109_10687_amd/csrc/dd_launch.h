@@ -149,6 +149,25 @@ struct LatTab {
     int n;
 };
 
+// one entry of a launch of FP64 residuals r = b - D x: fields in the FP64 internal layout
+struct ResidLat {
+    Geom g;
+    const void *x, *b;
+    void *r;
+    const void *u, *clov;  // FP64 links and clover blocks
+    Phase4 phase;
+    double kappa;
+    int item0, nwg;  // first work item (256-site chunk) of this entry and their number
+    long long poff;  // its partial sums, nwg of them
+};
+constexpr int RESID_MAX = 14;
+struct ResidTab {
+    ResidLat e[RESID_MAX];
+    int n;
+    int shared;  // the entries are fields of one lattice
+};
+static_assert(sizeof(ResidTab) <= 4000, "the table travels in the kernel arguments");
+
 // one lattice of a multi-lattice packed-FP16 half-sweep (one right-hand side)
 struct SapLat {
     Geom g;
@@ -244,6 +263,10 @@ int blas_grid(const Geom &g);
 // grid of a grid-stride loop over the sites (one thread per site, at most BLAS_MAX_WG workgroups)
 int blas_grid_sites(const Geom &g);
 hipError_t launch_blas(const Geom &g, hipStream_t st, const BlasArgs &a);
+
+// the residuals of a table (total: the work items of all entries); resid_grid: those of one lattice
+int resid_grid(const Geom &g);
+hipError_t launch_resid64(hipStream_t st, const ResidTab &t, int total, double *partials);
 
 // ---- flexible GCR: k directions p_j (FP16 storage) with images z_j (FP32)
 struct VecSet {

@@ -318,6 +318,52 @@ dd_status blas(dd_ctx *c, dd::BlasArgs a)
     return DD_OK;
 }
 
+bool resid_fits(const dd::Geom &g) { return dd::resid_grid(g) <= dd::MAX_PARTIALS; }
+
+hipError_t resid_table(dd_ctx *c0, hipStream_t st, const std::vector<ResidJob> &jobs, bool shared, double *out)
+{
+    size_t i = 0;
+    while (i < jobs.size()) {
+        dd::ResidTab t{};
+        dd::MultiBlasTab f{};  // where the partials are, for the finalizing launch
+        int slot[dd::MULTI_BLAS_MAX];
+        int total = 0;
+        double bytes = 0, flops = 0;
+        t.shared = shared;
+        for (; i < jobs.size() && t.n < dd::RESID_MAX && t.n < dd::MULTI_BLAS_MAX; ++i) {
+            const ResidJob &j = jobs[i];
+            const int nwg = dd::resid_grid(j.c->g);
+            if (nwg > dd::MAX_PARTIALS) return hipErrorInvalidValue;
+            if (total + nwg > dd::MAX_PARTIALS) break;
+            dd::ResidLat &e = t.e[t.n];
+            e.g = j.c->g;
+            e.x = j.x;
+            e.b = j.b;
+            e.r = j.r;
+            e.u = j.c->U64;
+            e.clov = j.c->clov64;
+            e.phase = j.c->phase;
+            e.kappa = j.c->prm.kappa;
+            e.item0 = total;
+            e.nwg = nwg;
+            e.poff = total;
+            f.e[t.n].poff = total;
+            f.e[t.n].nwg = nwg;
+            slot[t.n] = j.slot;
+            total += nwg;
+            ++t.n;
+            const double V = (double)j.c->g.V;
+            bytes += V * (3 * sp_b(0) + 4 * lk_b(0) + cl_b(0));
+            flops += V * (hops_in(j.c->g) + hops_out(j.c->g) + CLOVF + 72);
+        }
+        f.n = t.n;
+        hipError_t e = timed(c0, DD_KT_DIRAC_F64, bytes, flops, [&] { return dd::launch_resid64(st, t, total, c0->partials); });
+        if (e == hipSuccess) e = dd::launch_finalize_multi(st, f, slot, c0->partials, 1, out);
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+
 hipError_t vec_table(dd_ctx *c0, hipStream_t st, int kind, const std::vector<VecJob> &jobs, int nv, double *out)
 {
     size_t i = 0;
@@ -397,6 +443,12 @@ dd_status copy(dd_ctx *c, void *dst, int pd, void *src, int ps)
 dd_status residual64(dd_ctx *c, void *r, void *b, void *x, void *tmp, double *rn2)
 {
     Range range("ddsolve: FP64 residual");
+    if (resid_fits(c->g)) {
+        HIPCK(c, resid_table(c, c->stream, {{c, x, b, r, 0}}, false, c->red));
+        HIPCK(c, hipStreamSynchronize(c->stream));
+        *rn2 = c->red_host[0];
+        return DD_OK;
+    }
     dd_status st = k_dirac(c, tmp, x, 0, 0, 0, 0);
     if (st != DD_OK) return st;
     return reduce(c, mkb(dd::BLAS_SUB_NORM, {r, b, tmp}, {0, 0, 0}), 1, rn2);

@@ -225,3 +225,36 @@ def test_solve_multi_more_lattices_than_one_table_holds():
         res = np.linalg.norm(orc.D(x.cpu().numpy()) - b.numpy()) / np.linalg.norm(b.numpy())
         assert res < 1e-10, (k, res)
     m.close()
+
+
+@pytest.mark.parametrize("dims, block", [((8, 8, 8, 8), (4, 4, 4, 4)), ((4, 4, 12, 8), (2, 2, 2, 2)),
+                                         ((16, 8, 8, 16), (8, 4, 4, 2)), ((16, 16, 24, 16), (4, 4, 4, 4))])
+def test_residual_of_single_batch_and_multi(dims, block):
+    """|b - D x| / |b| as the single, batched (16 right-hand sides: more than one launch of the
+    residual's table) and multi-lattice solvers report it, after one pass from a given x, against
+    b - D x formed from the operator's own output.  Both round D x alike to within some 1e-15 of |b|,
+    and the passes stop at 1e-5 or so, above 1e-8: 1e-6 relative."""
+    p = dd.Params(dims=dims, kappa=0.12, csw=1.3, block=block, phases=(1, np.exp(0.3j), 1, -1),
+                  inner_tol=1e-4)
+    U = synth.su3_links(dims, 0.3, 351, device="cuda")
+    s = dd.Solver(p, U)
+    bs = synth.gaussian_spinor(dims, 352, device="cuda", batch=16)
+    x0 = 0.5 * bs.conj().contiguous()
+
+    def check(x, b, info):
+        want = ((b - s.apply(x)).norm() / b.norm()).item()
+        assert want > 1e-8 and abs(info["relres_true"] / want - 1) < 1e-6, (info, want)
+
+    x, info = s.solve(bs[0], tol=1e-12, maxiter=1, x0=x0[0])
+    check(x, bs[0], info)
+    xs, infos = s.solve_batch(bs, tol=1e-12, maxiter=1, x0=x0)
+    for r in range(16):
+        check(xs[r], bs[r], infos[r])
+    m = dd.Multi([p, p, p])
+    for k in range(3):
+        m.load_gauge(k, U)
+    xs, infos = m.solve([bs[k] for k in range(3)], tol=1e-12, maxiter=1, x0=[x0[k] for k in range(3)])
+    for k in range(3):
+        check(xs[k], bs[k], infos[k])
+    m.close()
+    s.close()
