@@ -255,6 +255,29 @@ DD_INL void clover_blocks(const double2 *clov, const Geom &g, int l, int sb, Spi
     }
 }
 
+// o = (1 + C) x - kappa acc
+DD_INL void clover_value(const double2 *clov, const Geom &g, int l, int s, double kappa, const Spinor<double> &x,
+                         Spinor<double> &acc, Spinor<double> &o)
+{
+    cx<double> v[2][6], r[2][6];
+#pragma unroll
+    for (int a = 0; a < 2; ++a)
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            v[0][a * 3 + c] = x.v[a][c] + x.v[a + 2][c];
+            v[1][a * 3 + c] = x.v[a][c] - x.v[a + 2][c];
+        }
+    clover_blocks(clov, g, l, s, acc, v, r);
+#pragma unroll
+    for (int a = 0; a < 2; ++a)
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            const int q = a * 3 + c;
+            o.v[a][c] = (r[0][q] + r[1][q]) - kappa * acc.v[a][c];
+            o.v[a + 2][c] = (r[0][q] - r[1][q]) - kappa * acc.v[a + 2][c];
+        }
+}
+
 // out = op(in) on the full lattice, one thread per site; op 0 = D, 1 = A, 2 = D^dagger
 // o = op(in)(i) for one site i, decoded in st
 template <int PIN, int PG, int OP>
@@ -291,23 +314,7 @@ DD_INL void dirac_value(const Geom &g, const SpinorField<PIN> &in, const LinkFie
     if (OP == 2) gamma5(x);
     const R k = R(kappa);
     if constexpr (PG == 0) {
-        cx<double> v[2][6], r[2][6];
-#pragma unroll
-        for (int a = 0; a < 2; ++a)
-#pragma unroll
-            for (int c = 0; c < 3; ++c) {
-                v[0][a * 3 + c] = x.v[a][c] + x.v[a + 2][c];
-                v[1][a * 3 + c] = x.v[a][c] - x.v[a + 2][c];
-            }
-        clover_blocks(C.p, g, st.l, st.s, acc, v, r);
-#pragma unroll
-        for (int a = 0; a < 2; ++a)
-#pragma unroll
-            for (int c = 0; c < 3; ++c) {
-                const int q = a * 3 + c;
-                o.v[a][c] = (r[0][q] + r[1][q]) - kappa * acc.v[a][c];
-                o.v[a + 2][c] = (r[0][q] - r[1][q]) - kappa * acc.v[a + 2][c];
-            }
+        clover_value(C.p, g, st.l, st.s, kappa, x, acc, o);
         if (OP == 2) gamma5(o);
         return;
     }
@@ -377,6 +384,10 @@ __global__ void __launch_bounds__(256) k_dirac(Geom gin, SpinorField<POUT> out, 
 // lose.
 // The hop order and arithmetic are those of dirac_site; results agree to FP32 (FP64) rounding,
 // not bit for bit, since the compiler fuses multiply-adds differently in the two kernels.
+// In FP64 the sums are settled after each hop and the clover blocks taken one after the other: 226
+// registers, two wavefronts per SIMD; 256 and 100 before, one per SIMD (FP64 D on 48^3x96 3.68 ->
+// 3.44 ms, on 64^3x128 11.2 -> 10.7).  OP = 3 (FP64) is the residual r = b - D x with the partial sums of
+// |r|^2, one per workgroup.
 template <int P> struct StoreT;
 template <> struct StoreT<0> { using T = double2; static constexpr int N = 12; };
 template <> struct StoreT<1> { using T = float2; static constexpr int N = 12; };
@@ -411,7 +422,8 @@ template <int P, typename R> DD_INL void raw_to(const RawSp<P> &r, Spinor<R> &x)
 
 template <int PIN, int POUT, int PG, int OP>
 __global__ void __launch_bounds__(256) k_dirac_ts(Geom gin, SpinorField<POUT> out, SpinorField<PIN> in, LinkField<PG> U,
-                                                  CloverField<PG> C, Phase4 ph, double kappa, int ns)
+                                                  CloverField<PG> C, Phase4 ph, double kappa, int ns,
+                                                  const double2 *b64, double *partials)
 {
     using R = typename Acc<PIN, PG>::T;
     using T = typename StoreT<PIN>::T;
@@ -443,6 +455,7 @@ __global__ void __launch_bounds__(256) k_dirac_ts(Geom gin, SpinorField<POUT> ou
             return nullptr;
     };
     const int bt0 = seg * ns;
+    double v[1] = {0};
     for (int k = 0; k < ns; ++k) {
         // the site is decoded afresh in every step, from a thread index the compiler cannot
         // follow across steps: otherwise it keeps every hop's addresses from one step to the
@@ -492,6 +505,7 @@ __global__ void __launch_bounds__(256) k_dirac_ts(Geom gin, SpinorField<POUT> ou
                     U.load(g, lj, sj, mu, W);
                 cx<R> phase = {R(ph.re[mu]), R(dir > 0 ? ph.im[mu] : -ph.im[mu])};
                 hop(mu, dir, W, psi, wrap, phase, acc);
+                if (PG == 0) settle(acc);
             }
         }
         Spinor<R> x, t, o;
@@ -501,22 +515,29 @@ __global__ void __launch_bounds__(256) k_dirac_ts(Geom gin, SpinorField<POUT> ou
             raw_to<PIN>(r, x);
         }
         if (OP == 2) gamma5(x);
-        Clov<R> cl;
-        C.load(g, st.l, sl, cl);
         const R kr = R(kappa);
-        if (OP == 1) {
+        if constexpr (PG == 0) {
+            clover_value(C.p, g, st.l, sl, kappa, x, acc, o);
+            if (OP == 2) gamma5(o);
+            if (OP == 3) {
+                Spinor<double> b;
+                SpinorField<0>{(double2 *)b64}.load(g, st.l, sl, b);
+#pragma unroll
+                for (int a = 0; a < 4; ++a)
+#pragma unroll
+                    for (int c = 0; c < 3; ++c) {
+                        o.v[a][c] = b.v[a][c] - o.v[a][c];
+                        v[0] += norm2(o.v[a][c]);
+                    }
+            }
+        } else if (OP == 1) {
+            Clov<R> cl;
+            C.load(g, st.l, sl, cl);
             clover_mul(cl, acc, t);
 #pragma unroll
             for (int a = 0; a < 4; ++a)
 #pragma unroll
                 for (int c = 0; c < 3; ++c) o.v[a][c] = x.v[a][c] - kr * t.v[a][c];
-        } else {
-            clover_mul(cl, x, t);
-#pragma unroll
-            for (int a = 0; a < 4; ++a)
-#pragma unroll
-                for (int c = 0; c < 3; ++c) o.v[a][c] = t.v[a][c] - kr * acc.v[a][c];
-            if (OP == 2) gamma5(o);
         }
         out.store(g, st.l, sl, o, true);
         // the next block's backward t hop term from this block's top slice
@@ -533,6 +554,7 @@ __global__ void __launch_bounds__(256) k_dirac_ts(Geom gin, SpinorField<POUT> ou
         }
         wg_barrier();
     }
+    if (OP == 3) wg_reduce_store_at<1>(v, partials, blockIdx.x);
 }
 
 // ---- D and D^dagger on canonical spinors (FP64), no pack and unpack passes
@@ -1347,9 +1369,10 @@ __global__ void __launch_bounds__(BLAS_WG) k_sub_norm(Geom g, SpinorField<P> r, 
 // field, several lattices, or several right-hand sides of one lattice (t.shared), whose workgroups for a
 // chunk of 256 sites then follow one another, so its links and clover blocks (300 KB, three quarters
 // of what a right-hand side reads) come from the L2 after the first.  D x itself is never stored.
-// HBM-bound (1728 bytes per site): with a launch of D (t-streamed where that pays) and a pass of
-// b - D x each, against this: 12 right-hand sides on 16^3x32 662 and 455 us, 16^4 alone 31 and 26,
-// 32^3x64 932 and 856 us, 64^3x128 14.7 and 13.6 ms.
+// HBM-bound (1728 bytes per site): with a launch of D and a pass of b - D x each, 12 right-hand sides
+// on 16^3x32 took 662 us, with this 455; 16^4 alone 31 and 26.  A single large lattice of 4^4 blocks
+// takes the t-streamed k_dirac_ts with OP = 3 instead (32^3x64 768 us, this 856, the two passes 932;
+// 64^3x128 11.5-12.2 ms, 13.5 and 14.7).
 __global__ void __launch_bounds__(BLAS_WG, 2) k_resid64(ResidTab t, double *partials)
 {
     const int w = xcd_remap(blockIdx.x, gridDim.x);
@@ -1722,7 +1745,7 @@ static void dirac_launch(const Geom &g, hipStream_t st, const DiracArgs &a, bool
     if constexpr (PG != 2) {
         if (ns > 1) {
             hipLaunchKernelGGL((k_dirac_ts<PIN, POUT, PG, OP>), dim3(g.nblk / ns), dim3(256), 0, st, g, out, in, U, C,
-                               a.phase, a.kappa, ns);
+                               a.phase, a.kappa, ns, nullptr, nullptr);
             return;
         }
     }
@@ -1858,6 +1881,24 @@ hipError_t launch_blas_multi(hipStream_t st, int kind, const MultiBlasTab &t, in
 }
 
 int resid_grid(const Geom &g) { return grid_sites(g.V, BLAS_WG); }
+
+int resid_stream_grid(const Geom &g)
+{
+    const bool cube4 = g.b[0] == 4 && g.b[1] == 4 && g.b[2] == 4 && g.b[3] == 4;
+    const int ns = cube4 ? dirac_stream_len(g) : 0;
+    return ns > 1 ? g.nblk / ns : 0;
+}
+
+hipError_t launch_resid64_stream(hipStream_t st, const ResidLat &L, double *partials)
+{
+    const int nwg = resid_stream_grid(L.g);
+    if (nwg <= 0) return hipErrorInvalidValue;
+    hipLaunchKernelGGL((k_dirac_ts<0, 0, 0, 3>), dim3(nwg), dim3(256), 0, st, L.g, SpinorField<0>{(double2 *)L.r},
+                       SpinorField<0>{(double2 *)L.x}, LinkField<0>{(const double2 *)L.u},
+                       CloverField<0>{(const double2 *)L.clov}, L.phase, L.kappa, L.g.nblk / nwg, (const double2 *)L.b,
+                       partials);
+    return hipGetLastError();
+}
 
 hipError_t launch_resid64(hipStream_t st, const ResidTab &t, int total, double *partials)
 {

@@ -267,6 +267,9 @@ hipError_t launch_blas(const Geom &g, hipStream_t st, const BlasArgs &a);
 // the residuals of a table (total: the work items of all entries); resid_grid: those of one lattice
 int resid_grid(const Geom &g);
 hipError_t launch_resid64(hipStream_t st, const ResidTab &t, int total, double *partials);
+// one lattice's residual by the t-streamed kernel where that serves it: its workgroups (and partials), or 0
+int resid_stream_grid(const Geom &g);
+hipError_t launch_resid64_stream(hipStream_t st, const ResidLat &L, double *partials);
 
 // ---- flexible GCR: k directions p_j (FP16 storage) with images z_j (FP32)
 struct VecSet {

@@ -318,6 +318,27 @@ dd_status blas(dd_ctx *c, dd::BlasArgs a)
     return DD_OK;
 }
 
+static dd::ResidLat resid_lat(const ResidJob &j)
+{
+    dd::ResidLat e{};
+    e.g = j.c->g;
+    e.x = j.x;
+    e.b = j.b;
+    e.r = j.r;
+    e.u = j.c->U64;
+    e.clov = j.c->clov64;
+    e.phase = j.c->phase;
+    e.kappa = j.c->prm.kappa;
+    return e;
+}
+
+static void resid_cost(const dd::Geom &g, double &bytes, double &flops)
+{
+    const double V = (double)g.V;
+    bytes += V * (3 * sp_b(0) + 4 * lk_b(0) + cl_b(0));
+    flops += V * (hops_in(g) + hops_out(g) + CLOVF + 72);
+}
+
 bool resid_fits(const dd::Geom &g) { return dd::resid_grid(g) <= dd::MAX_PARTIALS; }
 
 hipError_t resid_table(dd_ctx *c0, hipStream_t st, const std::vector<ResidJob> &jobs, bool shared, double *out)
@@ -336,14 +357,7 @@ hipError_t resid_table(dd_ctx *c0, hipStream_t st, const std::vector<ResidJob> &
             if (nwg > dd::MAX_PARTIALS) return hipErrorInvalidValue;
             if (total + nwg > dd::MAX_PARTIALS) break;
             dd::ResidLat &e = t.e[t.n];
-            e.g = j.c->g;
-            e.x = j.x;
-            e.b = j.b;
-            e.r = j.r;
-            e.u = j.c->U64;
-            e.clov = j.c->clov64;
-            e.phase = j.c->phase;
-            e.kappa = j.c->prm.kappa;
+            e = resid_lat(j);
             e.item0 = total;
             e.nwg = nwg;
             e.poff = total;
@@ -352,9 +366,7 @@ hipError_t resid_table(dd_ctx *c0, hipStream_t st, const std::vector<ResidJob> &
             slot[t.n] = j.slot;
             total += nwg;
             ++t.n;
-            const double V = (double)j.c->g.V;
-            bytes += V * (3 * sp_b(0) + 4 * lk_b(0) + cl_b(0));
-            flops += V * (hops_in(j.c->g) + hops_out(j.c->g) + CLOVF + 72);
+            resid_cost(j.c->g, bytes, flops);
         }
         f.n = t.n;
         hipError_t e = timed(c0, DD_KT_DIRAC_F64, bytes, flops, [&] { return dd::launch_resid64(st, t, total, c0->partials); });
@@ -443,8 +455,18 @@ dd_status copy(dd_ctx *c, void *dst, int pd, void *src, int ps)
 dd_status residual64(dd_ctx *c, void *r, void *b, void *x, void *tmp, double *rn2)
 {
     Range range("ddsolve: FP64 residual");
-    if (resid_fits(c->g)) {
-        HIPCK(c, resid_table(c, c->stream, {{c, x, b, r, 0}}, false, c->red));
+    const int nts = dd::resid_stream_grid(c->g);
+    if (nts > 0 ? nts <= dd::MAX_PARTIALS : resid_fits(c->g)) {
+        const ResidJob job = {c, x, b, r, 0};
+        if (nts > 0) {
+            double bytes = 0, flops = 0;
+            resid_cost(c->g, bytes, flops);
+            HIPCK(c, timed(c, DD_KT_DIRAC_F64, bytes, flops,
+                           [&] { return dd::launch_resid64_stream(c->stream, resid_lat(job), c->partials); }));
+            HIPCK(c, dd::launch_finalize(c->stream, c->partials, nts, 1, c->red));
+        } else {
+            HIPCK(c, resid_table(c, c->stream, {job}, false, c->red));
+        }
         HIPCK(c, hipStreamSynchronize(c->stream));
         *rn2 = c->red_host[0];
         return DD_OK;

@@ -228,11 +228,13 @@ def test_solve_multi_more_lattices_than_one_table_holds():
 
 
 @pytest.mark.parametrize("dims, block", [((8, 8, 8, 8), (4, 4, 4, 4)), ((4, 4, 12, 8), (2, 2, 2, 2)),
-                                         ((16, 8, 8, 16), (8, 4, 4, 2)), ((16, 16, 24, 16), (4, 4, 4, 4))])
+                                         ((16, 8, 8, 16), (8, 4, 4, 2)), ((16, 16, 24, 16), (4, 4, 4, 4)),
+                                         ((16, 32, 32, 32), (4, 4, 4, 4))])
 def test_residual_of_single_batch_and_multi(dims, block):
     """|b - D x| / |b| as the single, batched (16 right-hand sides: more than one launch of the
     residual's table) and multi-lattice solvers report it, after one pass from a given x, against
-    b - D x formed from the operator's own output.  Both round D x alike to within some 1e-15 of |b|,
+    b - D x formed from the operator's own output (the last lattice is large enough for the single
+    solver's t-streamed kernel).  Both round D x alike to within some 1e-15 of |b|,
     and the passes stop at 1e-5 or so, above 1e-8: 1e-6 relative."""
     p = dd.Params(dims=dims, kappa=0.12, csw=1.3, block=block, phases=(1, np.exp(0.3j), 1, -1),
                   inner_tol=1e-4)
