@@ -41,7 +41,7 @@ def class_kernels(block):
     With 4^4 blocks the FP64, FP32 and FP16-input Dirac applies run the t-streamed kernel
     (k_dirac_ts), the all-FP16 apply and the packed-FP16 SAP half-sweep their 4^4
     specialisations (template argument 4); other block shapes run the generic kernels (0).  (The FP64
-    class also holds the solvers' residuals b - D x: k_dirac_ts<0, 0, 0, 3> and k_resid64.)"""
+    class also holds the solvers' residuals b - D x: k_dirac_ts<0, 0, 0, 3> and k_resid64<.>.)"""
     if tuple(block) == (4, 4, 4, 4):
         return {"dirac_f64": "k_dirac_ts<0, 0, 0, 0>", "dirac_f32": "k_dirac_ts<1, 1, 1, 1>",
                 "dirac_f16in": "k_dirac_ts<2, 1, 1, 1>", "dirac_f16": "k_dirac<2, 2, 2, 1, 4>",

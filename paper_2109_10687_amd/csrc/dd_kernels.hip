@@ -279,12 +279,19 @@ DD_INL void clover_value(const double2 *clov, const Geom &g, int l, int s, doubl
 }
 
 // out = op(in) on the full lattice, one thread per site; op 0 = D, 1 = A, 2 = D^dagger
-// o = op(in)(i) for one site i, decoded in st
-template <int PIN, int PG, int OP>
-DD_INL void dirac_value(const Geom &g, const SpinorField<PIN> &in, const LinkField<PG> &U, const CloverField<PG> &C,
-                        const Phase4 &ph, double kappa, const Site &st, Spinor<typename Acc<PIN, PG>::T> &o)
+// out(i) = op(in)(i) for one site i (out: a field, or ResidOut).  SETTLE (FP64): the sums are settled
+// after each hop and the clover blocks taken one after the other, 222 registers and two wavefronts per
+// SIMD; without it the loads run further ahead in 256 + 74 to 104, one wavefront per SIMD.  Which is
+// faster depends on where the loads come from: FP64 D on 16^3x32 and 24^4 takes 43 and 121 us without,
+// 53 and 139 with; residuals of eight lattices in one launch 202 and 231; 12 right-hand sides of
+// 16^3x32, whose links and clover blocks are in the L2, 481 and 455.
+template <int PIN, int PG, int OP, bool SETTLE = false, typename Out>
+DD_INL void dirac_site(const Geom &g, const Out &out, const SpinorField<PIN> &in, const LinkField<PG> &U,
+                       const CloverField<PG> &C, const Phase4 &ph, double kappa, long long i)
 {
     using R = typename Acc<PIN, PG>::T;
+    Site st;
+    decode(g, i, st);
     Spinor<R> acc;
     zero(acc);
 #pragma unroll
@@ -304,22 +311,21 @@ DD_INL void dirac_value(const Geom &g, const SpinorField<PIN> &in, const LinkFie
                 U.load(g, lj, sj, mu, W);
             cx<R> phase = {R(ph.re[mu]), R(dir > 0 ? ph.im[mu] : -ph.im[mu])};
             hop(mu, dir, W, psi, wrap, phase, acc);
-            // (FP64: the loads of every hop at once take more registers than there are: 256 and 74, one
-            // wavefront per SIMD, against 220 and two)
-            if (PG == 0) settle(acc);
+            if constexpr (SETTLE) settle(acc);
         }
     }
-    Spinor<R> x, t;
+    Spinor<R> x, t, o;
     in.load(g, st.l, st.s, x);
     if (OP == 2) gamma5(x);
-    const R k = R(kappa);
-    if constexpr (PG == 0) {
+    if constexpr (SETTLE) {
         clover_value(C.p, g, st.l, st.s, kappa, x, acc, o);
         if (OP == 2) gamma5(o);
+        out.store(g, st.l, st.s, o, true);
         return;
     }
     Clov<R> cl;
     C.load(g, st.l, st.s, cl);
+    const R k = R(kappa);
     if (OP == 1) {
         clover_mul(cl, acc, t);
 #pragma unroll
@@ -334,16 +340,6 @@ DD_INL void dirac_value(const Geom &g, const SpinorField<PIN> &in, const LinkFie
             for (int c = 0; c < 3; ++c) o.v[a][c] = t.v[a][c] - k * acc.v[a][c];
         if (OP == 2) gamma5(o);
     }
-}
-
-template <int PIN, int POUT, int PG, int OP>
-DD_INL void dirac_site(const Geom &g, const SpinorField<POUT> &out, const SpinorField<PIN> &in, const LinkField<PG> &U,
-                       const CloverField<PG> &C, const Phase4 &ph, double kappa, long long i)
-{
-    Site st;
-    decode(g, i, st);
-    Spinor<typename Acc<PIN, PG>::T> o;
-    dirac_value<PIN, PG, OP>(g, in, U, C, ph, kappa, st, o);
     out.store(g, st.l, st.s, o, true);
 }
 
@@ -356,7 +352,7 @@ __global__ void __launch_bounds__(256) k_dirac(Geom gin, SpinorField<POUT> out, 
     const int w = xcd_remap(blockIdx.x, gridDim.x);
     const long long i = (long long)w * 256 + threadIdx.x;
     if (i >= g.V) return;
-    dirac_site<PIN, POUT, PG, OP>(g, out, in, U, C, ph, kappa, i);
+    dirac_site<PIN, PG, OP>(g, out, in, U, C, ph, kappa, i);
 }
 
 // ---- the same operator streamed along t (4^4 blocks)
@@ -713,9 +709,9 @@ __global__ void __launch_bounds__(256) k_dirac_multi(LatTab t)
     const LinkField<1> U{(const float2 *)d.u};
     const CloverField<1> C{(const float2 *)d.cinv};
     if (d.g.b[0] == 4 && d.g.b[1] == 4 && d.g.b[2] == 4 && d.g.b[3] == 4)
-        dirac_site<PIN, 1, 1, 1>(fixed_shape<4>(d.g), out, in, U, C, d.phase, d.kappa, i);
+        dirac_site<PIN, 1, 1>(fixed_shape<4>(d.g), out, in, U, C, d.phase, d.kappa, i);
     else
-        dirac_site<PIN, 1, 1, 1>(d.g, out, in, U, C, d.phase, d.kappa, i);
+        dirac_site<PIN, 1, 1>(d.g, out, in, U, C, d.phase, d.kappa, i);
 }
 
 // ============================================================ SAP half-sweep
@@ -1365,19 +1361,40 @@ __global__ void __launch_bounds__(BLAS_WG) k_sub_norm(Geom g, SpinorField<P> r, 
     sub_norm_body<P>(g, r, b, a, partials, blockIdx.x, gridDim.x);
 }
 
+// takes D x of a site: r = b - D x there, |r|^2 added to sum
+struct ResidOut {
+    const double2 *b;
+    double2 *r;
+    double &sum;
+    DD_INL void store(const Geom &g, int l, int s, const Spinor<double> &dx, bool) const
+    {
+        Spinor<double> o;
+        SpinorField<0>{const_cast<double2 *>(b)}.load(g, l, s, o);
+#pragma unroll
+        for (int a = 0; a < 4; ++a)
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                o.v[a][c] = o.v[a][c] - dx.v[a][c];
+                sum += norm2(o.v[a][c]);
+            }
+        SpinorField<0>{r}.store(g, l, s, o);
+    }
+};
+
 // r = b - D x in FP64 and the partial sums of |r|^2, for the entries of a table in one launch: one
-// field, several lattices, or several right-hand sides of one lattice (t.shared), whose workgroups for a
+// field, several lattices, or several right-hand sides of one lattice (SHARED), whose workgroups for a
 // chunk of 256 sites then follow one another, so its links and clover blocks (300 KB, three quarters
 // of what a right-hand side reads) come from the L2 after the first.  D x itself is never stored.
 // HBM-bound (1728 bytes per site): with a launch of D and a pass of b - D x each, 12 right-hand sides
-// on 16^3x32 took 662 us, with this 455; 16^4 alone 31 and 26.  A single large lattice of 4^4 blocks
-// takes the t-streamed k_dirac_ts with OP = 3 instead (32^3x64 768 us, this 856, the two passes 932;
-// 64^3x128 11.5-12.2 ms, 13.5 and 14.7).
-__global__ void __launch_bounds__(BLAS_WG, 2) k_resid64(ResidTab t, double *partials)
+// on 16^3x32 took 662 us, with this 456; 16^4 alone 31 and 25; eight lattices 260 and 202.  A single
+// large lattice of 4^4 blocks takes the t-streamed k_dirac_ts with OP = 3 instead (32^3x64 768 us, this
+// 856, the two passes 932; 64^3x128 11.5-12.2 ms, 13.5 and 14.7).
+template <bool SHARED>
+__global__ void __launch_bounds__(BLAS_WG) k_resid64(ResidTab t, double *partials)
 {
     const int w = xcd_remap(blockIdx.x, gridDim.x);
     int k = 0, chunk;
-    if (t.shared) {
+    if constexpr (SHARED) {
         chunk = w / t.n;
         k = w - chunk * t.n;
     } else {
@@ -1389,20 +1406,9 @@ __global__ void __launch_bounds__(BLAS_WG, 2) k_resid64(ResidTab t, double *part
     const long long i = (long long)chunk * BLAS_WG + threadIdx.x;
     double v[1] = {0};
     if (i < g.V) {
-        Site st;
-        decode(g, i, st);
-        Spinor<double> o, b;
-        dirac_value<0, 0, 0>(g, SpinorField<0>{(double2 *)L.x}, LinkField<0>{(const double2 *)L.u},
-                             CloverField<0>{(const double2 *)L.clov}, L.phase, L.kappa, st, o);
-        SpinorField<0>{(double2 *)L.b}.load(g, st.l, st.s, b);
-#pragma unroll
-        for (int a = 0; a < 4; ++a)
-#pragma unroll
-            for (int c = 0; c < 3; ++c) {
-                o.v[a][c] = b.v[a][c] - o.v[a][c];
-                v[0] += norm2(o.v[a][c]);
-            }
-        SpinorField<0>{(double2 *)L.r}.store(g, st.l, st.s, o);
+        dirac_site<0, 0, 0, SHARED>(g, ResidOut{(const double2 *)L.b, (double2 *)L.r, v[0]}, SpinorField<0>{(double2 *)L.x},
+                                    LinkField<0>{(const double2 *)L.u}, CloverField<0>{(const double2 *)L.clov}, L.phase,
+                                    L.kappa, i);
     }
     wg_reduce_store_at<1>(v, partials + L.poff, chunk);
 }
@@ -1903,7 +1909,7 @@ hipError_t launch_resid64_stream(hipStream_t st, const ResidLat &L, double *part
 hipError_t launch_resid64(hipStream_t st, const ResidTab &t, int total, double *partials)
 {
     if (t.n <= 0 || t.n > RESID_MAX || total <= 0) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_resid64, dim3(total), dim3(BLAS_WG), 0, st, t, partials);
+    hipLaunchKernelGGL((t.shared ? k_resid64<true> : k_resid64<false>), dim3(total), dim3(BLAS_WG), 0, st, t, partials);
     return hipGetLastError();
 }
 
