@@ -368,9 +368,11 @@ DD_INL void dirac_site(const Geom &g, const Out &out, const SpinorField<PIN> &in
 // B > 0: the block shape is B^4, known at compile time (strides and block volume fold)
 // FP32 inputs (PIN = 1) are compiled for two wavefronts per SIMD, not three: the loads run further ahead
 // (135 registers for 129; FP32 A on 24x16^3 19.6 -> 19.4 us, 16^3x32 21.8 -> 21.5).  FP16 inputs lose by it
-// (24^4 43.9 -> 45.7 us), and four wavefronts per SIMD cost both 3-7 %.
+// (24^4 43.9 -> 45.7 us), and four wavefronts per SIMD cost both 3-7 % with 4^4 blocks; with other shapes
+// the compiler would run FP16 inputs at four, three is faster on large lattices (28^2x20x40 of 2^4 blocks
+// 101.5 -> 96.7 us, 12x20x28x36 39.3 -> 40.0).
 template <int PIN, int POUT, int PG, int OP, int B>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, PIN == 1 ? 2 : 8))) k_dirac(Geom gin, SpinorField<POUT> out, SpinorField<PIN> in, LinkField<PG> U,
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, PIN == 1 ? 2 : B == 0 ? 3 : 8))) k_dirac(Geom gin, SpinorField<POUT> out, SpinorField<PIN> in, LinkField<PG> U,
                                                CloverField<PG> C, Phase4 ph, double kappa)
 {
     const Geom g = fixed_shape<B>(gin);
