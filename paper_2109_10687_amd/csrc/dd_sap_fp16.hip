@@ -861,8 +861,8 @@ __global__ void __launch_bounds__(256, 3) k_sap_half_pk(Geom gin, int colour, in
     // A workgroup that is alone on its CU takes some 8 us to start, stage its block and finish, and
     // 1.7 us per Jacobi step, so a workgroup that took the right-hand sides in turn left small
     // lattices bound by that latency: 12 of them on 16^3x32 (256 blocks per colour) took 189.5 us per
-    // half-sweep, now 114; on 8^4 190 and 22.  On 32^4, where sharing the staged links and C_inv
-    // between right-hand sides is worth most, the two forms are level.
+    // half-sweep, with this launch 114 (93 in the present form of the sweeps); on 8^4 190 and 22.  On 32^4,
+    // where sharing the block's links and C_inv between right-hand sides is worth most, the two are level.
     const int item = xcd_remap(blockIdx.x, gridDim.x), w = item / rhs.n;
     const long long ridx = rhs.idx[item - w * rhs.n], off = ridx * rhs.sp_stride;
     sap_half_pk_body<B>(gin, w, colour, flags, rhs_field(bsrc, off), rhs_field(sw, off), rhs_field(xw, off), u16, cpsap,
