@@ -413,11 +413,13 @@ DD_INL void combine_pair(const SpH &a, float fa, const SpH &b, float fb, const S
 }
 
 // acc += f (1 - s gamma_mu) rebuilt from the pair-form half spinor k (s = 1 where fwd, else -1),
-// accumulated in FP32 straight from the FP16 parts (mixed-precision FMAs)
+// accumulated in FP32 straight from the FP16 parts.  The fused multiply-adds are written out: fwd
+// differs between the lanes of a wavefront, and where the compiler turns that branch into selects
+// it would round the product first.
 DD_INL void recon_mix(int mu, bool fwd, const PC (&k)[3], float f, Spinor<float> &acc)
 {
     const float fs = fwd ? f : -f;
-    auto add = [](cx<float> &a, float fr, float fi) { a = {a.re + fr, a.im + fi}; };
+    auto add = [](cx<float> &a, float fr, float r, float fi, float i) { a = {fma_(fr, r, a.re), fma_(fi, i, a.im)}; };
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
         const float r0 = __low2float(k[c].re), r1 = __high2float(k[c].re);
@@ -425,25 +427,25 @@ DD_INL void recon_mix(int mu, bool fwd, const PC (&k)[3], float f, Spinor<float>
         if (mu == 3) {  // twice the pair (the factor 2 of 1 - s gamma_4, see proj_pair)
             const float g2 = 2.f * f;
             if (fwd) {
-                add(acc.v[2][c], g2 * r0, g2 * i0);
-                add(acc.v[3][c], g2 * r1, g2 * i1);
+                add(acc.v[2][c], g2, r0, g2, i0);
+                add(acc.v[3][c], g2, r1, g2, i1);
             } else {
-                add(acc.v[0][c], g2 * r0, g2 * i0);
-                add(acc.v[1][c], g2 * r1, g2 * i1);
+                add(acc.v[0][c], g2, r0, g2, i0);
+                add(acc.v[1][c], g2, r1, g2, i1);
             }
             continue;
         }
-        add(acc.v[0][c], f * r0, f * i0);
-        add(acc.v[1][c], f * r1, f * i1);
+        add(acc.v[0][c], f, r0, f, i0);
+        add(acc.v[1][c], f, r1, f, i1);
         if (mu == 0) {  // (acc2, acc3) += s i (k1, k0)
-            add(acc.v[2][c], -fs * i1, fs * r1);
-            add(acc.v[3][c], -fs * i0, fs * r0);
+            add(acc.v[2][c], -fs, i1, fs, r1);
+            add(acc.v[3][c], -fs, i0, fs, r0);
         } else if (mu == 1) {  // (acc2, acc3) += s (k1, -k0)
-            add(acc.v[2][c], fs * r1, fs * i1);
-            add(acc.v[3][c], -fs * r0, -fs * i0);
+            add(acc.v[2][c], fs, r1, fs, i1);
+            add(acc.v[3][c], -fs, r0, -fs, i0);
         } else {  // (acc2, acc3) += s i (k0, -k1)
-            add(acc.v[2][c], -fs * i0, fs * r0);
-            add(acc.v[3][c], fs * i1, -fs * r1);
+            add(acc.v[2][c], -fs, i0, fs, r0);
+            add(acc.v[3][c], fs, i1, -fs, r1);
         }
     }
 }
