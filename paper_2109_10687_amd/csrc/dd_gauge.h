@@ -27,8 +27,8 @@ DD_INL void mul3(const Mat3<double> &A, const Mat3<double> &B, Mat3<double> &C)
 {
     for (int i = 0; i < 3; ++i)
         for (int j = 0; j < 3; ++j) {
-            cx<double> s = A.m[i][0] * B.m[0][j];
-            for (int k = 1; k < 3; ++k) s = cmac(s, A.m[i][k], B.m[k][j]);
+            cx<double> s = {0, 0};
+            for (int k = 0; k < 3; ++k) s = s + A.m[i][k] * B.m[k][j];
             C.m[i][j] = s;
         }
 }

@@ -263,3 +263,26 @@ def test_sap_fp16_after_gauge_reload(name):
     assert rel_l2(got, want) < 3e-3
     assert rel_l2(first, want) > 1e-1  # the two fields give different preconditioners
     s.close()
+
+
+# relative L2 distances to the oracle of a build that rounds every product before it is added (the link
+# products and the rows of the clover blocks): what shorter chains of fused multiply-adds must not exceed
+ROUNDING = [((16, 16, 16, 16), (4, 4, 4, 4), 6.143e-8, 1.372e-7, 2.084e-16),
+            ((16, 8, 8, 12), (8, 2, 4, 2), 6.161e-8, 1.334e-7, 2.084e-16),
+            ((12, 4, 8, 8), (2, 2, 2, 2), 6.145e-8, 1.267e-7, 2.093e-16)]
+
+
+@pytest.mark.parametrize("dims, block, bar_a, bar_sap, bar_d", ROUNDING)
+def test_rounding_errors_have_not_grown(dims, block, bar_a, bar_sap, bar_d):
+    """FP32 A, FP32 SAP and FP64 D against the oracle: no further from it than the bars above."""
+    phases = (np.exp(0.3j), np.exp(-0.5j), np.exp(1.1j), -np.exp(0.2j))
+    par = dict(dims=dims, kappa=0.125, csw=1.5, block=block, phases=phases, n_sap=2, n_jac=4)
+    U, x = synth.su3_links(dims, 0.3, 171), synth.gaussian_spinor(dims, 172)
+    orc = O.Oracle(O.Params(**par), U.numpy())
+    s = dd.Solver(dd.Params(**par), U.cuda())
+    xg = x.cuda()
+    a = rel_l2(s.apply(xg, op=dd.DD_OP_A, prec=dd.DD_F32).cpu().numpy(), orc.A(x.numpy()))
+    sap = rel_l2(s.precondition(xg, prec=dd.DD_F32).cpu().numpy(), orc.sap(x.numpy()))
+    d = rel_l2(s.apply(xg, op=dd.DD_OP_D, prec=dd.DD_F64).cpu().numpy(), orc.D(x.numpy()))
+    s.close()
+    assert a <= bar_a and sap <= bar_sap and d <= bar_d, (a, sap, d)
