@@ -203,10 +203,12 @@ dd_status dd_destroy(dd_ctx *ctx);
 dd_status dd_load_gauge(dd_ctx *ctx, const void *U_dev);
 
 /* out = op(in) for canonical spinor fields (device, caller-owned, 24 doubles
- * per site; in and out must not overlap).  The field is packed into the
- * internal layout at precision prec, the operator is applied at that precision
- * (FP16: per-site-scaled FP16 storage, 12-real links and FP16 C_inv, FP32
- * arithmetic), and the result is unpacked to complex double.  DD_OP_D and
+ * per site).  At DD_F64 one kernel goes straight from in to out.  Otherwise the
+ * field is packed into the internal layout at precision prec, the operator is
+ * applied at that precision (FP16: per-site-scaled FP16 storage, 12-real links
+ * and FP16 C_inv, FP32 arithmetic), and the result is unpacked to complex
+ * double.  in and out should not overlap: where they do, the input is copied
+ * first, which at DD_F64 takes the packed way as well.  DD_OP_D and
  * DD_OP_DDAG are available at DD_F64, DD_OP_A at DD_F32 and DD_F16; other
  * combinations return DD_ERR_ARG.  Asynchronous. */
 dd_status dirac_apply(dd_ctx *ctx, void *out_dev, const void *in_dev, dd_prec prec, dd_op op);

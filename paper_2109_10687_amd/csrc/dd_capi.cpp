@@ -10,6 +10,7 @@
 
 #include <chrono>
 #include <cmath>
+#include <cstdint>
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
@@ -202,7 +203,10 @@ dd_status dirac_apply(dd_ctx *c, void *out, const void *in, dd_prec prec, dd_op 
     if (!c || !out || !in) return fail(c, DD_ERR_ARG, "null argument");
     dd_status st = check_op(c, prec, op);
     if (st != DD_OK) return st;
-    if (prec == DD_F64) return k_dirac_can(c, out, in, op);
+    // FP64: one kernel straight on the caller's fields, whose workgroups read sites that others write; fields
+    // that overlap (out == in among them) go through the internal layout, which copies the input first
+    const uintptr_t o = (uintptr_t)out, i = (uintptr_t)in, bytes = (uintptr_t)spinor_bytes(c->g, DD_F64);
+    if (prec == DD_F64 && (o < i ? i - o : o - i) >= bytes) return k_dirac_can(c, out, in, op);
     void *ti = c->f64[5], *to = c->f64[6];
     HIPCK(c, dd::launch_pack_spinor(c->g, c->stream, prec, ti, in));
     if ((st = k_dirac(c, to, ti, prec, prec, prec, op)) != DD_OK) return st;
