@@ -984,8 +984,7 @@ hipError_t launch_sap_half_pk_multi(hipStream_t st, const SapLat *lat, int nlat,
     if (nlat <= 0) return hipSuccess;
     const Geom &g = lat[0].g;
     const bool cubes = cube(g, 4) || cube(g, 2);
-    const int bpw = sap_blocks_per_wg(g.bvol);
-    const int threads = cubes ? 256 : g.bvol * bpw;
+    const int threads = cubes ? 256 : g.bvol * sap_blocks_per_wg(g.bvol);
     for (int k0 = 0; k0 < nlat; k0 += SAP_MULTI_MAX) {  // up to SAP_MULTI_MAX lattices per launch
         SapLatTab t{};
         int items = 0;
@@ -996,7 +995,7 @@ hipError_t launch_sap_half_pk_multi(hipStream_t st, const SapLat *lat, int nlat,
             if (!sap_multi_together(g, e.g)) return hipErrorInvalidValue;
             e.item0 = items;
             items += sap_multi_items(e.g);
-            const size_t need = sap_pk_lds_bytes(e.g) * (cube(e.g, 2) ? 16 : bpw);
+            const size_t need = sap_pk_lds_bytes(e.g) * (cube(e.g, 2) ? 16 : sap_blocks_per_wg(e.g.bvol));
             if (need > lds) lds = need;
         }
         hipLaunchKernelGGL((cubes ? k_sap_half_pk_multi<4> : k_sap_half_pk_multi<0>), dim3(items), dim3(threads), lds, st, t,
