@@ -598,6 +598,7 @@ __global__ void __launch_bounds__(64 * TT, 2) k_dirac_can(Geom gin, double2 *out
     const Geom g = fixed_shape<(CUBE4 ? 4 : 0)>(gin);
     constexpr int N = 64 * TT, SS = 13;  // sites of a tile; double2 per staged site (13: no bank conflicts)
     __shared__ double2 tile[N * SS];
+    wg_skew();
     const int tid = threadIdx.x;
     // tile coordinates (x fastest)
     const unsigned nx = (unsigned)g.L[0] >> 2, ny = (unsigned)g.L[1] >> 2, nz = (unsigned)g.L[2] >> 2;
@@ -1104,6 +1105,7 @@ template <> struct Elem<2> {  // read only: the scale belongs to the whole site
 DD_INL void finalize_sum(const double *p, int nwg, int nv, double *out)
 {
     __shared__ double sh[4][3];
+    wg_skew();
     for (int k0 = 0; k0 < nv; k0 += 3) {
         const int m = nv - k0 < 3 ? nv - k0 : 3;
         double t[3] = {0, 0, 0};
@@ -1566,6 +1568,7 @@ template <> DD_INL void sf_load<2>(void *p, const Geom &g, int l, int s, Spinor<
 template <int NV> DD_INL void wg_reduce_store_dyn(double (&v)[NV], int nv, double *partials)
 {
     __shared__ double red[NV][BLAS_WG / 64];
+    wg_skew();
 #pragma unroll
     for (int q = 0; q < NV; ++q) {
         if (q >= nv) break;

@@ -208,6 +208,7 @@ struct ForceArgs {
 template <int NV> DD_INL void wg_reduce_store_at(double (&v)[NV], double *partials, long long wid)
 {
     __shared__ double red[NV][BLAS_WG / 64];
+    wg_skew();
 #pragma unroll
     for (int k = 0; k < NV; ++k)
 #pragma unroll

@@ -366,6 +366,7 @@ __global__ void __launch_bounds__(256) k_dirac_rhs_res(Geom gin, MrhsArgs a)
     constexpr int NE = ResT<PIN>::N;
     __shared__ T tile[NE][256];       // the right-hand side in turn, as stored
     __shared__ float tsc[PIN == 2 ? 256 : 1];
+    wg_skew();
     const int w = xcd_remap(blockIdx.x, gridDim.x);
     const int s = threadIdx.x;
     Site st;
