@@ -44,10 +44,10 @@ def class_kernels(block):
     class also holds the solvers' residuals b - D x: k_dirac_ts<0, 0, 0, 3> and k_resid64<.>.)"""
     if tuple(block) == (4, 4, 4, 4):
         return {"dirac_f64": "k_dirac_ts<0, 0, 0, 0>", "dirac_f32": "k_dirac_ts<1, 1, 1, 1>",
-                "dirac_f16in": "k_dirac_ts<2, 1, 1, 1>", "dirac_f16": "k_dirac<2, 2, 2, 1, 4>",
+                "dirac_f16in": "k_dirac_ts<2, 1, 1, 1>", "dirac_f16": "k_dirac<2, 2, 2, 1, 4, 0>",
                 "sap": "k_sap_half<2>", "sap_pk": "k_sap_half_pk<4>", "blas": "vector kernels"}
-    return {"dirac_f64": "k_dirac<0, 0, 0, 0, 0>", "dirac_f32": "k_dirac<1, 1, 1, 1, 0>",
-            "dirac_f16in": "k_dirac<2, 1, 1, 1, 0>", "dirac_f16": "k_dirac<2, 2, 2, 1, 0>",
+    return {"dirac_f64": "k_dirac<0, 0, 0, 0, 0, 0>", "dirac_f32": "k_dirac<1, 1, 1, 1, 0, %d>" % (2 if block[0] == 2 else 0),
+            "dirac_f16in": "k_dirac<2, 1, 1, 1, 0, 3>", "dirac_f16": "k_dirac<2, 2, 2, 1, 0, 0>",
             "sap": "k_sap_half<2>", "sap_pk": "k_sap_half_pk<0>", "blas": "vector kernels"}
 
 

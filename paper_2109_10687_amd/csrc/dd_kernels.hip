@@ -365,15 +365,13 @@ DD_INL void dirac_site(const Geom &g, const Out &out, const SpinorField<PIN> &in
     out.store(g, st.l, st.s, o, true);
 }
 
-// B > 0: the block shape is B^4, known at compile time (strides and block volume fold)
-// FP32 inputs (PIN = 1) are compiled for two wavefronts per SIMD, not three: the loads run further ahead
-// (135 registers for 129; FP32 A on 24x16^3 19.6 -> 19.4 us, 16^3x32 21.8 -> 21.5).  FP16 inputs lose by it
-// (24^4 43.9 -> 45.7 us), and four wavefronts per SIMD cost both 3-7 % with 4^4 blocks; with other shapes
-// the compiler would run FP16 inputs at four, three is faster on large lattices (28^2x20x40 of 2^4 blocks
-// 101.5 -> 96.7 us, 12x20x28x36 39.3 -> 40.0).
-template <int PIN, int POUT, int PG, int OP, int B>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, PIN == 1 ? 2 : B == 0 ? 3 : 8))) k_dirac(Geom gin, SpinorField<POUT> out, SpinorField<PIN> in, LinkField<PG> U,
-                                               CloverField<PG> C, Phase4 ph, double kappa)
+// B > 0: the block shape is B^4, known at compile time (strides and block volume fold).  WV: the most
+// wavefronts per SIMD it is compiled for (0: the compiler's choice); fewer leave registers for loads
+// that run further ahead.
+template <int PIN, int POUT, int PG, int OP, int B, int WV>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, WV > 0 ? WV : 8)))
+    k_dirac(Geom gin, SpinorField<POUT> out, SpinorField<PIN> in, LinkField<PG> U, CloverField<PG> C, Phase4 ph,
+            double kappa)
 {
     const Geom g = fixed_shape<B>(gin);
     const int w = xcd_remap(blockIdx.x, gridDim.x);
@@ -1785,12 +1783,18 @@ static void dirac_launch(const Geom &g, hipStream_t st, const DiracArgs &a, bool
             return;
         }
     }
-    const dim3 grid(grid_sites(g.V, 256));
-    if (cube4)
-        hipLaunchKernelGGL((k_dirac<PIN, POUT, PG, OP, (PG != 0 ? 4 : 0)>), grid, dim3(256), 0, st, g, out, in, U, C,
-                           a.phase, a.kappa);
-    else
-        hipLaunchKernelGGL((k_dirac<PIN, POUT, PG, OP, 0>), grid, dim3(256), 0, st, g, out, in, U, C, a.phase, a.kappa);
+    // Wavefronts per SIMD.  FP32 A: two, not three, with 4^4 blocks (16^4 12.1 -> 11.9 us, 16^3x32 20.9 -> 20.6,
+    // 24^4 52.8 -> 52.3) and with blocks of x extent 2, whose neighbours lie in the most lines (2^4 blocks on
+    // 28^2x20x40 138 -> 121 us, on 12x20x28x36 51 -> 46; 2x4x2x2 on 24^4 54.9 -> 52.5); with longer extents
+    // two win on some lattices and lose on others (8x4x4x2 on 16^4 12.6 -> 12.0, 4x4x4x2 on 16^2x24x32
+    // 30.2 -> 31.7), so the compiler's three stay.  FP16-input A of shapes other than 4^4: three, not four (2^4
+    // on 28^2x20x40 100.4 -> 95.1 us, 2x4x2x2 on 24^4 44.4 -> 43.0; at most 1.5 % the other way, 12x20x28x36
+    // 38.4 -> 38.9).  The all-FP16 operator and FP64 take what the compiler chooses.
+    constexpr int W4 = PIN == 1 ? 2 : 0, WX2 = PIN == 1 ? 2 : PIN == 2 && POUT == 1 ? 3 : 0, W = PIN == 1 ? 0 : WX2;
+    auto kern = cube4         ? k_dirac<PIN, POUT, PG, OP, (PG != 0 ? 4 : 0), W4>
+                : g.b[0] == 2 ? k_dirac<PIN, POUT, PG, OP, 0, WX2>
+                              : k_dirac<PIN, POUT, PG, OP, 0, W>;
+    hipLaunchKernelGGL(kern, dim3(grid_sites(g.V, 256)), dim3(256), 0, st, g, out, in, U, C, a.phase, a.kappa);
 }
 
 hipError_t launch_dirac(const Geom &g, hipStream_t st, const DiracArgs &a)
