@@ -386,7 +386,7 @@ const char *dd_batch_variant_name(int variant);
  * inner_tol and inner_maxiter of the params apply to each inner solve.
  * info (may be NULL) receives nrhs records.  Returns the worst status over
  * the right-hand sides (DD_OK < DD_NOT_CONVERGED < DD_BREAKDOWN).  The first
- * call allocates the batch work fields (about 1.8 KB per site and right-hand
+ * call allocates the batch work fields (about 1.7 KB per site and right-hand
  * side), kept until dd_destroy.  Synchronises the stream. */
 dd_status bicgstab_solve_batch(dd_ctx *ctx, void *x_dev, const void *b_dev, int nrhs, double tol, int maxiter,
                                dd_batch_inner inner, dd_solve_info *info);

@@ -338,18 +338,9 @@ dd_status solve_batch32(dd_ctx *c, int n, bool sap, std::vector<BRhs> &R, int ma
 dd_status residual64_batch(dd_ctx *c, int n, double *rn2)
 {
     dd_status st;
-    if (resid_fits(c->g)) {
-        std::vector<ResidJob> jobs;
-        for (int r = 0; r < n; ++r) jobs.push_back({c, bf(c, BK_X64, r), bf(c, BK_B64, r), bf(c, BK_R64, r), r});
-        HIPCK(c, resid_table(c, c->stream, jobs, true, c->red));
-    } else {
-        std::vector<VecJob> jobs;
-        for (int r = 0; r < n; ++r) {
-            if ((st = k_dirac(c, bf(c, BK_T64, r), bf(c, BK_X64, r), 0, 0, 0, 0)) != DD_OK) return st;
-            jobs.push_back({c, mkb(dd::BLAS_SUB_NORM, {bf(c, BK_R64, r), bf(c, BK_B64, r), bf(c, BK_T64, r)}, {0, 0, 0}), r});
-        }
-        HIPCK(c, vec_table(c, c->stream, dd::BLAS_SUB_NORM, jobs, 1, c->red));
-    }
+    std::vector<ResidJob> jobs;
+    for (int r = 0; r < n; ++r) jobs.push_back({c, bf(c, BK_X64, r), bf(c, BK_B64, r), bf(c, BK_R64, r), r});
+    HIPCK(c, resid_table(c, c->stream, jobs, true, c->red));
     double red[3 * BATCH_MAX];
     if ((st = fetch_red(c, 3 * n, red)) != DD_OK) return st;
     for (int r = 0; r < n; ++r) rn2[r] = red[3 * r];
@@ -425,26 +416,12 @@ static dd_status multi_blas(dd_multi *m, int kind, const std::vector<int> &ks,
 static dd_status multi_residual64(dd_multi *m, const std::vector<int> &ks, std::vector<double> &rn2)
 {
     dd_status st;
-    bool fits = true;
-    for (int k : ks) fits = fits && resid_fits(m->L[k]->g);
-    if (fits) {
-        std::vector<ResidJob> jobs;
-        for (int k : ks) {
-            dd_ctx *c = m->L[k];
-            jobs.push_back({c, c->f64[1], c->f64[0], c->f64[2], k});
-        }
-        MHIPCK(m, resid_table(m->L[0], m->stream, jobs, false, m->red_all));
-    } else {
-        for (int k : ks) {
-            dd_ctx *c = m->L[k];
-            if ((st = k_dirac(c, c->f64[3], c->f64[1], 0, 0, 0, 0)) != DD_OK) return lat_fail(m, k, st);
-        }
-        if ((st = multi_blas(m, dd::BLAS_SUB_NORM, ks, [&](int k) {
-                 dd_ctx *c = m->L[k];
-                 return mkb(dd::BLAS_SUB_NORM, {c->f64[2], c->f64[0], c->f64[3]}, {0, 0, 0});
-             }, 1)) != DD_OK)
-            return st;
+    std::vector<ResidJob> jobs;
+    for (int k : ks) {
+        dd_ctx *c = m->L[k];
+        jobs.push_back({c, c->f64[1], c->f64[0], c->f64[2], k});
     }
+    MHIPCK(m, resid_table(m->L[0], m->stream, jobs, false, m->red_all));
     std::vector<std::array<double, 3>> red(m->L.size());
     if ((st = multi_fetch(m, 1, red)) != DD_OK) return st;
     for (int k : ks) rn2[k] = red[k][0];

@@ -83,7 +83,7 @@ dd_status dd_create(const dd_params *prm, void *hip_stream, dd_ctx **out)
     for (int i = 0; ok && i < N64; ++i) ok = alloc(&c->f64[i], spinor_bytes(g, DD_F64));
     for (int i = 0; ok && i < N32; ++i) ok = alloc(&c->f32[i], spinor_bytes(g, DD_F32));
     for (int i = 0; ok && i < N16; ++i) ok = alloc(&c->f16[i], spinor_bytes(g, DD_F16));
-    ok = ok && alloc((void **)&c->partials, dd::MAX_PARTIALS * sizeof(double)) &&
+    ok = ok && alloc((void **)&c->partials, partials_held(g) * sizeof(double)) &&
          alloc((void **)&c->flag, 4 * sizeof(int)) &&
          hipHostMalloc((void **)&c->red_host, RED_MAX * sizeof(double), hipHostMallocMapped) == hipSuccess &&
          hipHostGetDevicePointer((void **)&c->red, c->red_host, 0) == hipSuccess;
@@ -303,10 +303,10 @@ static dd_status solve_entry(dd_ctx *c, void *x_dev, const void *b_dev, double t
         // Alg. 4: x += err * P_DP(A_SP^{-1} R_SP(C_inv r / err)), r = b - D x in FP64
         if (mode == DD_SOLVE_MIXED_GCR && (st = ensure_gcr(c)) != DD_OK) return st;
         HIPCK(c, dd::launch_pack_spinor(c->g, c->stream, DD_F64, x, x_dev, dagger));
-        void *r = c->f64[2], *tmp = c->f64[3];
+        void *r = c->f64[2];
         void *src = c->f32[0], *y = c->f32[1];
         double rn2;
-        if ((st = residual64(c, r, b, x, tmp, &rn2)) != DD_OK) return st;
+        if ((st = residual64(c, r, b, x, &rn2)) != DD_OK) return st;
         if (bn2 > 0) c->hist_outer.push_back(std::sqrt(rn2 / bn2));
         double prev = rn2;
         int stall = 0, outer = 0;
@@ -348,7 +348,7 @@ static dd_status solve_entry(dd_ctx *c, void *x_dev, const void *b_dev, double t
                 inf.iters_inner_total += o.iters;
                 inf.relres_inner_last = o.relres;
                 const double before = rn2;
-                if ((st = residual64(c, r, b, x, tmp, &rn2)) != DD_OK) return st;
+                if ((st = residual64(c, r, b, x, &rn2)) != DD_OK) return st;
                 c->hist_outer.push_back(std::sqrt(rn2 / bn2));
                 if (sp == DD_BREAKDOWN && !restarted && rn2 <= 1e-2 * before) {
                     restarted = true;  // broke down after a 10x gain: restart once from the new x
@@ -376,13 +376,13 @@ static dd_status solve_entry(dd_ctx *c, void *x_dev, const void *b_dev, double t
             inf.iters_inner_total += o.iters;
             inf.relres_inner_last = o.relres;
             if ((st = blas(c, mkb(dd::BLAS_AXPBY, {y, x}, {1, 0}, {err, 1.0}))) != DD_OK) return st;
-            if ((st = residual64(c, r, b, x, tmp, &rn2)) != DD_OK) return st;
+            if ((st = residual64(c, r, b, x, &rn2)) != DD_OK) return st;
             ++outer;
             if (!is_fin(rn2) || rn2 >= prev) {
                 // the correction made the true residual worse (inner solve failed):
                 // take it back, so x stays the best iterate
                 if ((st = blas(c, mkb(dd::BLAS_AXPBY, {y, x}, {1, 0}, {-err, 1.0}))) != DD_OK) return st;
-                if ((st = residual64(c, r, b, x, tmp, &rn2)) != DD_OK) return st;
+                if ((st = residual64(c, r, b, x, &rn2)) != DD_OK) return st;
                 if (give_up(is_fin(rn2) ? DETAIL_OUTER_STALL : 4)) break;
                 continue;
             }
@@ -423,7 +423,7 @@ static dd_status solve_entry(dd_ctx *c, void *x_dev, const void *b_dev, double t
         rn2_x = rn2;  // every way out of the loop has the residual of the current x
     }
     // true FP64 residual of the returned x, where the solver did not leave it
-    if (!(rn2_x >= 0) && (st = residual64(c, c->f64[2], b, x, c->f64[3], &rn2_x)) != DD_OK) return st;
+    if (!(rn2_x >= 0) && (st = residual64(c, c->f64[2], b, x, &rn2_x)) != DD_OK) return st;
     inf.relres_true = bn2 > 0 ? std::sqrt(rn2_x / bn2) : 0.0;
     HIPCK(c, dd::launch_unpack_spinor(c->g, c->stream, DD_F64, x_dev, x, dagger));
     HIPCK(c, hipStreamSynchronize(c->stream));

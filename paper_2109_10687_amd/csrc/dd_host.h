@@ -223,7 +223,9 @@ dd::BlasArgs mkb(int kind, std::initializer_list<void *> v, std::initializer_lis
 dd_status norm2(dd_ctx *c, void *v, int prec, double *out);
 dd_status copy(dd_ctx *c, void *dst, int pd, void *src, int ps);
 // r = b - D x (FP64) ; returns |r|^2
-dd_status residual64(dd_ctx *c, void *r, void *b, void *x, void *tmp, double *rn2);
+dd_status residual64(dd_ctx *c, void *r, void *b, void *x, double *rn2);
+// partial sums that a context of geometry g holds: those of every reduction, one per 256 sites for residuals
+int partials_held(const dd::Geom &g);
 // bring nv finalized sums of `partials` to the host
 dd_status fetch(dd_ctx *c, int nv, double *out);
 // the operator / precision pairs the apply entry points accept, and a loaded gauge field
@@ -280,10 +282,10 @@ dd_status solve_fgmres64(dd_ctx *c, void *x, void *b, double bn2, double tol, in
 // ---- dd_batch.cpp: batched right-hand sides and several lattices
 
 // kinds of per-RHS fields in the batch buffers (each kind: nrhs fields one after another)
-enum { BK_B64, BK_X64, BK_R64, BK_T64, BK_SRC, BK_Y, BK_R, BK_RT, BK_P, BK_Q, BK_T, BK_IN, BK_OUT,
+enum { BK_B64, BK_X64, BK_R64, BK_SRC, BK_Y, BK_R, BK_RT, BK_P, BK_Q, BK_T, BK_IN, BK_OUT,
        BK_R16, BK_P16, BK_MP16, BK_MR16, BK_S16, BK_COUNT };
 
-inline int bk_prec(int k) { return k <= BK_T64 ? DD_F64 : k >= BK_R16 ? DD_F16 : DD_F32; }
+inline int bk_prec(int k) { return k <= BK_R64 ? DD_F64 : k >= BK_R16 ? DD_F16 : DD_F32; }
 
 dd_status batch_alloc(dd_ctx *c, int n);
 // field r of kind k
@@ -302,15 +304,14 @@ struct VecJob {
 hipError_t vec_table(dd_ctx *c0, hipStream_t st, int kind, const std::vector<VecJob> &jobs, int nv, double *out);
 
 // r = b - D x (FP64) of every job, |r|^2 to out[3 slot]: launches of up to RESID_MAX entries (all of
-// one lattice where `shared`) whose partials fit c0's, on stream st.  A lattice whose partials alone
-// do not fit is refused (resid_fits).
+// one lattice where `shared`) whose partials fit those of the launch's first entry, on stream st.
+// Timed on c0's timers.
 struct ResidJob {
     dd_ctx *c;
     const void *x, *b;
     void *r;
     int slot;
 };
-bool resid_fits(const dd::Geom &g);
 hipError_t resid_table(dd_ctx *c0, hipStream_t st, const std::vector<ResidJob> &jobs, bool shared, double *out);
 // out = A in for n batched fields at input precision pin (DD_F32 or DD_F16), FP32 output,
 // in tiles of up to 12

@@ -1366,28 +1366,6 @@ __global__ void __launch_bounds__(BLAS_WG) k_start(Geom g, SpinorField<1> src, S
     start_body(g, src, r, p, rt, p16, y, partials, blockIdx.x, gridDim.x);
 }
 
-// r = b - a ; partial |r|^2
-template <int P>
-DD_INL void sub_norm_body(const Geom &g, SpinorField<P> r, SpinorField<P> b, SpinorField<P> a, double *partials, int wid,
-                          int nwg)
-{
-    double v[1] = {0};
-    GRID_STRIDE_W(o, 12 * g.V)
-    {
-        cx<double> d = Elem<P>::get(b, g, o) - Elem<P>::get(a, g, o);
-        Elem<P>::put(r, g, o, d);
-        v[0] += norm2(d);
-    }
-    wg_reduce_store_at<1>(v, partials, wid);
-}
-
-template <int P>
-__global__ void __launch_bounds__(BLAS_WG) k_sub_norm(Geom g, SpinorField<P> r, SpinorField<P> b, SpinorField<P> a,
-                                                      double *partials)
-{
-    sub_norm_body<P>(g, r, b, a, partials, blockIdx.x, gridDim.x);
-}
-
 // takes D x of a site: r = b - D x there, |r|^2 added to sum
 struct ResidOut {
     const double2 *b;
@@ -1458,8 +1436,6 @@ __global__ void __launch_bounds__(BLAS_WG) k_blas_multi(MultiBlasTab t, double *
     };
     if constexpr (KIND == BLAS_NORM2)
         norm2_body<0>(g, f0(0), pp, wid, nwg);
-    else if constexpr (KIND == BLAS_SUB_NORM)
-        sub_norm_body<0>(g, f0(0), f0(1), f0(2), pp, wid, nwg);
     else if constexpr (KIND == BLAS_START)
         start_body(g, f1(0), f1(1), f1(2), f1(3), f2(4), f1(5), pp, wid, nwg);
     else if constexpr (KIND == BLAS_DOT)
@@ -1908,7 +1884,6 @@ hipError_t launch_blas_multi(hipStream_t st, int kind, const MultiBlasTab &t, in
     const dim3 G(total), B(BLAS_WG);
     switch (kind) {
     case BLAS_NORM2: hipLaunchKernelGGL(k_blas_multi<BLAS_NORM2>, G, B, 0, st, t, partials); break;
-    case BLAS_SUB_NORM: hipLaunchKernelGGL(k_blas_multi<BLAS_SUB_NORM>, G, B, 0, st, t, partials); break;
     case BLAS_START: hipLaunchKernelGGL(k_blas_multi<BLAS_START>, G, B, 0, st, t, partials); break;
     case BLAS_DOT: hipLaunchKernelGGL(k_blas_multi<BLAS_DOT>, G, B, 0, st, t, partials); break;
     case BLAS_DOT_NORM: hipLaunchKernelGGL(k_blas_multi<BLAS_DOT_NORM>, G, B, 0, st, t, partials); break;
@@ -2020,10 +1995,6 @@ hipError_t launch_blas(const Geom &g, hipStream_t st, const BlasArgs &a)
             hipLaunchKernelGGL((k_axpby<0, 1>), G, B, 0, st, g, a.c[0], sf<0>(a.v[0], g), a.c[1], sf<1>(a.v[1], g));
         else
             return hipErrorInvalidValue;
-        break;
-    case BLAS_SUB_NORM:  // v0 = v1 - v2 ; |v0|^2 (FP64)
-        hipLaunchKernelGGL((k_sub_norm<0>), G, B, 0, st, g, sf<0>(a.v[0], g), sf<0>(a.v[1], g), sf<0>(a.v[2], g),
-                           a.partials);
         break;
     case BLAS_CONVERT: {  // v1 = v0 with precisions p0 -> p1 (per site)
         const dim3 Gs(grid_sites(g.V, 256)), Bs(256);

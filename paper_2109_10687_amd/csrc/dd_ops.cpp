@@ -1,6 +1,7 @@
 // dd_ops.cpp -- launches of the single-field kernels with their algorithmic
 // byte and flop counts (kernel timing), the vector kernels and reductions, and
 // the sigma blocks of the clover setup.
+#include <algorithm>
 #include <functional>
 
 #include "dd_host.h"
@@ -296,7 +297,6 @@ void blas_cost(const dd::BlasArgs &a, double &rw, double &fl)
     case dd::BLAS_UPDATE2: rw = 2 * P0 + P1 + 4 * P2; fl = 336; break;
     case dd::BLAS_PUPDATE: rw = 4 * P0; fl = 192; break;
     case dd::BLAS_AXPBY: rw = P0 + (a.c[1] != 0.0 ? 2 : 1) * P1; fl = 72; break;
-    case dd::BLAS_SUB_NORM: rw = 3 * P0; fl = 72; break;
     case dd::BLAS_CONVERT: rw = P0 + P1; break;
     case dd::BLAS_CINV_SRC: rw = sp_b(1) + P1 + cl_b(1); fl = CLOVF; break;
     case dd::BLAS_UPDATE1_H: rw = 3 * sp_b(1) + sp_b(2); fl = 144; break;                 // r r/w, q, r16 written
@@ -339,7 +339,7 @@ static void resid_cost(const dd::Geom &g, double &bytes, double &flops)
     flops += V * (hops_in(g) + hops_out(g) + CLOVF + 72);
 }
 
-bool resid_fits(const dd::Geom &g) { return dd::resid_grid(g) <= dd::MAX_PARTIALS; }
+int partials_held(const dd::Geom &g) { return std::max(dd::MAX_PARTIALS, dd::resid_grid(g)); }
 
 hipError_t resid_table(dd_ctx *c0, hipStream_t st, const std::vector<ResidJob> &jobs, bool shared, double *out)
 {
@@ -351,11 +351,12 @@ hipError_t resid_table(dd_ctx *c0, hipStream_t st, const std::vector<ResidJob> &
         int total = 0;
         double bytes = 0, flops = 0;
         t.shared = shared;
+        dd_ctx *own = jobs[i].c;  // its partials hold at least its own sums
+        const int held = partials_held(own->g);
         for (; i < jobs.size() && t.n < dd::RESID_MAX && t.n < dd::MULTI_BLAS_MAX; ++i) {
             const ResidJob &j = jobs[i];
             const int nwg = dd::resid_grid(j.c->g);
-            if (nwg > dd::MAX_PARTIALS) return hipErrorInvalidValue;
-            if (total + nwg > dd::MAX_PARTIALS) break;
+            if (total + nwg > held) break;
             dd::ResidLat &e = t.e[t.n];
             e = resid_lat(j);
             e.item0 = total;
@@ -369,8 +370,8 @@ hipError_t resid_table(dd_ctx *c0, hipStream_t st, const std::vector<ResidJob> &
             resid_cost(j.c->g, bytes, flops);
         }
         f.n = t.n;
-        hipError_t e = timed(c0, DD_KT_DIRAC_F64, bytes, flops, [&] { return dd::launch_resid64(st, t, total, c0->partials); });
-        if (e == hipSuccess) e = dd::launch_finalize_multi(st, f, slot, c0->partials, 1, out);
+        hipError_t e = timed(c0, DD_KT_DIRAC_F64, bytes, flops, [&] { return dd::launch_resid64(st, t, total, own->partials); });
+        if (e == hipSuccess) e = dd::launch_finalize_multi(st, f, slot, own->partials, 1, out);
         if (e != hipSuccess) return e;
     }
     return hipSuccess;
@@ -452,28 +453,23 @@ dd_status copy(dd_ctx *c, void *dst, int pd, void *src, int ps)
 
 
 // r = b - D x (FP64) ; returns |r|^2
-dd_status residual64(dd_ctx *c, void *r, void *b, void *x, void *tmp, double *rn2)
+dd_status residual64(dd_ctx *c, void *r, void *b, void *x, double *rn2)
 {
     Range range("ddsolve: FP64 residual");
+    const ResidJob job = {c, x, b, r, 0};
     const int nts = dd::resid_stream_grid(c->g);
-    if (nts > 0 ? nts <= dd::MAX_PARTIALS : resid_fits(c->g)) {
-        const ResidJob job = {c, x, b, r, 0};
-        if (nts > 0) {
-            double bytes = 0, flops = 0;
-            resid_cost(c->g, bytes, flops);
-            HIPCK(c, timed(c, DD_KT_DIRAC_F64, bytes, flops,
-                           [&] { return dd::launch_resid64_stream(c->stream, resid_lat(job), c->partials); }));
-            HIPCK(c, dd::launch_finalize(c->stream, c->partials, nts, 1, c->red));
-        } else {
-            HIPCK(c, resid_table(c, c->stream, {job}, false, c->red));
-        }
-        HIPCK(c, hipStreamSynchronize(c->stream));
-        *rn2 = c->red_host[0];
-        return DD_OK;
+    if (nts > 0) {
+        double bytes = 0, flops = 0;
+        resid_cost(c->g, bytes, flops);
+        HIPCK(c, timed(c, DD_KT_DIRAC_F64, bytes, flops,
+                       [&] { return dd::launch_resid64_stream(c->stream, resid_lat(job), c->partials); }));
+        HIPCK(c, dd::launch_finalize(c->stream, c->partials, nts, 1, c->red));
+    } else {
+        HIPCK(c, resid_table(c, c->stream, {job}, false, c->red));
     }
-    dd_status st = k_dirac(c, tmp, x, 0, 0, 0, 0);
-    if (st != DD_OK) return st;
-    return reduce(c, mkb(dd::BLAS_SUB_NORM, {r, b, tmp}, {0, 0, 0}), 1, rn2);
+    HIPCK(c, hipStreamSynchronize(c->stream));
+    *rn2 = c->red_host[0];
+    return DD_OK;
 }
 
 // bring nv finalized sums of `partials` (nwg workgroups) to the host

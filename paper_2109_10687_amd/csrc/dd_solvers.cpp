@@ -27,7 +27,7 @@ dd_status solve_plain64(dd_ctx *c, void *x, void *b, double tol, int maxiter, So
     int it = 0;
     for (int restart = 0; restart < 20; ++restart) {
         double rn2;
-        if ((st = residual64(c, r, b, x, q, &rn2)) != DD_OK) return st;
+        if ((st = residual64(c, r, b, x, &rn2)) != DD_OK) return st;
         o.relres = std::sqrt(rn2 / bn2);
         if (o.relres < tol) {
             o.iters = it;
@@ -99,7 +99,7 @@ dd_status solve_plain64(dd_ctx *c, void *x, void *b, double tol, int maxiter, So
     }
     o.iters = it;
     double rn2;
-    if ((st = residual64(c, r, b, x, q, &rn2)) != DD_OK) return st;
+    if ((st = residual64(c, r, b, x, &rn2)) != DD_OK) return st;
     o.relres = std::sqrt(rn2 / bn2);
     return o.relres < tol ? DD_OK : DD_NOT_CONVERGED;
 }
@@ -394,7 +394,7 @@ dd_status solve_fgmres64(dd_ctx *c, void *x, void *b, double bn2, double tol, in
     double rn2 = 0, prev = 0;
     int stall = 0;
     for (int cycle = 0;; ++cycle) {
-        if ((st = residual64(c, c->fv[0], b, x, tmp, &rn2)) != DD_OK) return st;
+        if ((st = residual64(c, c->fv[0], b, x, &rn2)) != DD_OK) return st;
         const double beta = std::sqrt(rn2);
         if (!is_fin(rn2)) {
             o.detail = 4;
