@@ -171,8 +171,8 @@ dd_status solve_batch32(dd_ctx *c, int n, bool sap, std::vector<BRhs> &R, int ma
     std::vector<int> all(n);
     for (int r = 0; r < n; ++r) all[r] = r;
     if ((st = vec(dd::BLAS_START, all, [&](int r) {
-             return mkb(dd::BLAS_START, {bf(c, BK_SRC, r), bf(c, BK_R, r), bf(c, BK_P, r), bf(c, BK_RT, r), bf(c, BK_P16, r),
-                                         bf(c, BK_Y, r)}, {1, 1, 1, 1, 2, 1});
+             return mkb(dd::BLAS_START, {bf(c, BK_SRC, r), bf(c, BK_R, r), bf(c, BK_P, r), bf(c, BK_RT, r),
+                                         sap ? bf(c, BK_P16, r) : nullptr, bf(c, BK_Y, r)}, {1, 1, 1, 1, 2, 1});
          }, 1)) != DD_OK)
         return st;
     if ((st = fetch_red(c, 3 * n, red)) != DD_OK) return st;

@@ -292,7 +292,6 @@ DD_INL void st_stream(float2 *p, float2 x)
     f2nt_t v = {x.x, x.y};
     __builtin_nontemporal_store(v, (f2nt_t *)p);
 }
-DD_INL void st_stream(__half2 *p, __half2 x) { __builtin_nontemporal_store(*reinterpret_cast<unsigned int *>(&x), (unsigned int *)p); }
 DD_INL void st_stream(float *p, float x) { __builtin_nontemporal_store(x, p); }
 
 // ------------------------------------------------------------------ storage

@@ -291,7 +291,7 @@ hipError_t launch_gcr_rupdate(const Geom &g, hipStream_t st, void *z, void *r, d
 // y (FP32) += sum_j coef_j p_j, p_j at precision pp (FP16 or FP32)
 hipError_t launch_multi_axpy(const Geom &g, hipStream_t st, const VecSet &ps, int k, int pp, void *y);
 hipError_t launch_finalize(hipStream_t st, const double *partials, int nwg, int nv, double *out);
-// kind in {BLAS_NORM2 (FP64), BLAS_START (with its FP16 copy), BLAS_DOT, BLAS_DOT_NORM,
+// kind in {BLAS_NORM2 (FP64), BLAS_START, BLAS_DOT, BLAS_DOT_NORM,
 // BLAS_UPDATE1_H, BLAS_UPDATE2_MM (FP16 M p, M r), BLAS_PUPDATE_H} on the entries of t (total
 // workgroups: the sum of their nwg)
 hipError_t launch_blas_multi(hipStream_t st, int kind, const MultiBlasTab &t, int total, double *partials);
