@@ -353,9 +353,8 @@ dd_status dirac_apply_batch(dd_ctx *ctx, void *out_dev, const void *in_dev, int 
  * spinor fields stored one after another ([nrhs][Lt][Lz][Ly][Lx][3][4] complex double, device,
  * caller-owned, x and b must not overlap), with the FP16 storage of sap_precondition at DD_F16.
  * With packed FP16 arithmetic (dd_params.sap_fp16_arith = 1) each half-sweep is one launch for
- * all right-hand sides, every workgroup staging its block's links and C_inv once and sweeping
- * the block for each right-hand side in turn; the result of each equals that of
- * sap_precondition on it alone.  With FP32 arithmetic it runs one SAP per right-hand side.
+ * all right-hand sides, a workgroup per block and right-hand side; the result of each equals that
+ * of sap_precondition on it alone.  With FP32 arithmetic it runs one SAP per right-hand side.
  * The first call allocates the batch work fields (kept until dd_destroy; DD_ERR_NOMEM if that
  * fails).  Asynchronous. */
 dd_status sap_precondition_batch(dd_ctx *ctx, void *x_dev, const void *b_dev, int nrhs);
@@ -452,7 +451,8 @@ dd_status dirac_apply_packed_f16in(dd_ctx *ctx, void *out_f32_internal, const vo
 /* ---- kernel timing for roofline reporting -------------------------------- */
 
 typedef enum {
-    DD_KT_DIRAC_F64 = 0,    /* D or D^dagger, FP64 fields                       */
+    DD_KT_DIRAC_F64 = 0,    /* D or D^dagger, and the solvers' residuals
+                               b - D x in one kernel, FP64 fields               */
     DD_KT_DIRAC_F32 = 1,    /* A, FP32 spinors, links and C_inv                 */
     DD_KT_DIRAC_F16IN = 2,  /* A, FP16 input spinor, FP32 links/C_inv/output    */
     DD_KT_DIRAC_F16 = 3,    /* A, FP16 spinors, 12-real FP16 links, FP16 C_inv  */

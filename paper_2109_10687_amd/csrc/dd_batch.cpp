@@ -192,8 +192,7 @@ dd_status solve_batch32(dd_ctx *c, int n, bool sap, std::vector<BRhs> &R, int ma
     // M = the FP16-storage SAP of each right-hand side (as in the single right-hand-side
     // mixed solver), reading the FP16 copies of r and p that the updates write and writing
     // FP16 fields that the batched A reads as they are
-    // all active right-hand sides in one launch per half-sweep: a block's links and C_inv are
-    // staged once for all of them
+    // all active right-hand sides in one launch per half-sweep, a workgroup per block and right-hand side
     auto precond = [&](int from16, int to16) -> dd_status {
         if (!sap) return DD_OK;
         dd::SapRhs rhs{};

@@ -33,13 +33,15 @@
 //
 // What bounds them (24^4, 332 k sites): k_force_y moves 1.8 kB per site, 605 MB, in 116 us,
 // 5.2 TB/s (with psi and chi packed by kernels of their own and Y stored as full 3x3 matrices
-// the three took 204 us).  k_force_w takes 570 us.  Its arithmetic, 5100 FP64 instructions per
-// wavefront, would take 170 us, and the data it cannot do without 90 us; what it waits for is
-// the L2: a link's six plaquettes read 282 16-byte entries per lane, 7.9 GB over the launch
-// (14 TB/s).  The 64 sites x 4 directions of a workgroup share their lines in the L2 while they
-// are there; in an earlier form the four directions were four passes over the lattice, with
-// nine more entries per Y, 512 registers (one wavefront per SIMD instead of two) and every
-// complex multiply-add in three instructions instead of two: 1404 us.
+// the three took 204 us).  k_force_w takes 550 to 570 us.  Its arithmetic, 5100 FP64 instructions per
+// wavefront, would take 170 us, and the data it cannot do without 90 us; what bounds it is the
+// vector-memory address path of the CUs: a wavefront loads 303 entries of 16 bytes per lane (6.4 GB
+// over the launch), and the address units are busy in 73 % of the cycles, the VALU in 44 %; the 7.4 GB
+// that the L2 serves (13 TB/s) are a third of its rate, and requests do not wait for it.  The 64
+// sites x 4 directions of a workgroup share their lines in the L2 while they are there; in
+// an earlier form the four directions were four passes over the lattice, with nine more
+// entries per Y, 512 registers (one wavefront per SIMD instead of two) and every complex
+// multiply-add in three instructions instead of two: 1404 us.
 #include <mutex>
 
 #include "dd_device.h"

@@ -3,15 +3,16 @@
 //
 //  * pack / unpack between the canonical layout and the block-major internal
 //    layout (FP64, FP32, per-site-scaled FP16);
-//  * link packing (FP64, FP32 18-real, FP16 12-real) and the clover setup
+//  * link packing (FP64 18-real, FP32 and FP16 12-real) and the clover setup
 //    (four-leaf field strength, 1 + C as two 6x6 Hermitian blocks, Cholesky
 //    inverse) in FP64 -- appendix "Clover-Wilson Dirac operator";
 //  * the full-lattice apply of D = 1 + C - kappa H, A = I - kappa C_inv H
 //    (Sec. 3) and gamma_5 D gamma_5: one thread per site, coalesced
 //    block-major loads, spin-projected hops, FP64 or FP32 arithmetic;
 //  * the SAP half-sweep (Alg. 1 with the Jacobi of Alg. 2): one workgroup per
-//    Schwarz block, the block's links and the current Jacobi iterate staged
-//    in LDS, the cross-block term read from the neighbouring blocks;
+//    Schwarz block, a site's own links in registers, the current Jacobi iterate
+//    and the finished backward hop terms in LDS, the cross-block term read from
+//    the neighbouring blocks;
 //  * vector updates and reductions of BiCGStab (Alg. 5) with FP64
 //    accumulation: wavefront shuffles, then LDS, then one partial per
 //    workgroup, summed in a fixed order by a one-workgroup kernel.
@@ -302,8 +303,8 @@ DD_INL void clover_value(const double2 *clov, const Geom &g, int l, int s, doubl
 
 // out = op(in) on the full lattice, one thread per site; op 0 = D, 1 = A, 2 = D^dagger
 // out(i) = op(in)(i) for one site i (out: a field, or ResidOut).  SETTLE (FP64): the sums are settled
-// after each hop and the clover blocks taken one after the other, 222 registers and two wavefronts per
-// SIMD; without it the loads run further ahead in 256 + 74 to 104, one wavefront per SIMD.  Which is
+// after each hop and the clover blocks taken one after the other, 234 registers and two wavefronts per
+// SIMD; without it the loads run further ahead in 256 + 72 to 76, one wavefront per SIMD.  Which is
 // faster depends on where the loads come from: FP64 D on 16^3x32 and 24^4 takes 43 and 121 us without,
 // 53 and 139 with; residuals of eight lattices in one launch 202 and 231; 12 right-hand sides of
 // 16^3x32, whose links and clover blocks are in the L2, 481 and 455.
@@ -405,7 +406,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, WV 
 // lose.
 // The hop order and arithmetic are those of dirac_site; results agree to FP32 (FP64) rounding,
 // not bit for bit, since the compiler fuses multiply-adds differently in the two kernels.
-// In FP64 the sums are settled after each hop and the clover blocks taken one after the other: 226
+// In FP64 the sums are settled after each hop and the clover blocks taken one after the other: 226 or 228
 // registers, two wavefronts per SIMD; 256 and 100 before, one per SIMD (FP64 D on 48^3x96 3.68 ->
 // 3.44 ms, on 64^3x128 11.2 -> 10.7).  OP = 3 (FP64) is the residual r = b - D x with the partial sums of
 // |r|^2, one per workgroup.

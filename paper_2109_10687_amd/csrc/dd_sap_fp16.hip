@@ -457,7 +457,7 @@ DD_INL void recon_mix(int mu, bool fwd, const PC (&k)[3], float f, Spinor<float>
 // A site forms the terms of its own links, which stay in registers: a forward hop takes the
 // neighbour's iterate, a backward hop the neighbour's finished term.  That is 432 bytes of LDS
 // traffic per site and Jacobi step; with the links in LDS and every hop formed by its receiver
-// it was 720 (and 96 instead of 33 LDS reads and writes), 49 KB instead of 37 KB for a 4^4 block,
+// it was 720 (and 96 instead of 31 LDS reads and writes), 49 KB instead of 37 KB for a 4^4 block,
 // and the face terms were formed anew from LDS.  Half-sweeps: 32^3x64 146 -> 142 us, 16^4
 // 19.4 -> 18.5, 2^4 blocks on 12x16x16x24 19.7 -> 16.6, 2x4x4x2 blocks on 8x16^3 21.1 -> 17.4.
 // Small lattices are bound by latency (a step's 600 packed instructions and its LDS round trip on
