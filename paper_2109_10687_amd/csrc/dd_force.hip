@@ -36,7 +36,7 @@
 // the three took 204 us).  k_force_w takes 550 to 570 us.  Its arithmetic, 5100 FP64 instructions per
 // wavefront, would take 170 us, and the data it cannot do without 90 us; what bounds it is the
 // vector-memory address path of the CUs: a wavefront loads 303 entries of 16 bytes per lane (6.4 GB
-// over the launch), and the address units are busy in 73 % of the cycles, the VALU in 44 %; the 7.4 GB
+// over the launch), and the address units are busy in 74 % of the cycles, the VALU in 44 %; the 7.4 GB
 // that the L2 serves (13 TB/s) are a third of its rate, and requests do not wait for it.  The 64
 // sites x 4 directions of a workgroup share their lines in the L2 while they are there; in
 // an earlier form the four directions were four passes over the lattice, with nine more
