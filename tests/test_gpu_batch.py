@@ -260,3 +260,30 @@ def test_residual_of_single_batch_and_multi(dims, block):
         check(xs[k], bs[k], infos[k])
     m.close()
     s.close()
+
+
+def test_solve_multi_does_not_depend_on_the_order_of_the_lattices():
+    """Lattices of 2^4 and 4^4 blocks in one set, listed with either kind first: every solution is the same
+    bit for bit, and reaches the oracle's true residual."""
+    sets = [((12, 12, 12, 12), (2, 2, 2, 2)), ((8, 8, 8, 8), (4, 4, 4, 4)), ((4, 8, 12, 4), (2, 2, 2, 2)),
+            ((8, 8, 16, 8), (4, 4, 4, 4))]
+    par = [dict(dims=d, kappa=0.12, csw=1.4, block=b, phases=(1, np.exp(0.3j), 1, -1), n_sap=2, n_jac=4) for d, b in sets]
+    U = [synth.su3_links(d, 0.3, 361 + k) for k, (d, _) in enumerate(sets)]
+    b = [synth.gaussian_spinor(d, 371 + k) for k, (d, _) in enumerate(sets)]
+    first = None
+    for order in ((0, 1, 2, 3), (1, 0, 3, 2), (3, 1, 2, 0)):
+        m = dd.Multi([dd.Params(**par[k]) for k in order])
+        for i, k in enumerate(order):
+            m.load_gauge(i, U[k].cuda())
+        xs, infos = m.solve([b[k].cuda() for k in order], tol=1e-10)
+        assert all(i["status"] == "DD_OK" for i in infos), infos
+        xs = {k: xs[i].cpu() for i, k in enumerate(order)}
+        m.close()
+        if first is None:
+            first = xs
+        for k in order:
+            assert torch.equal(xs[k], first[k]), (order, k)
+    for k, p in enumerate(par):
+        orc = O.Oracle(O.Params(**p), U[k].numpy())
+        res = np.linalg.norm(orc.D(first[k].numpy()) - b[k].numpy()) / np.linalg.norm(b[k].numpy())
+        assert res < 1e-10, (k, res)
